@@ -1,0 +1,524 @@
+"""Workloads of the library's public entry points, with the arithmetic that says what they must return.
+
+Every workload is a plain dict.  The families, each through the entry point a user's program calls:
+
+  loglike   Context.loglike_grad on a full frequency grid: one event, 1 to 3 detectors, 4 to 128 s segments
+  binned    Context.loglike_grad on a relative-binning event
+  ragged    Context.loglike_grad over several events of different lengths in one call
+  nuts      Context.nuts_step: one NUTS transition per particle on the event likelihood
+  metric    Context.local_metric: the per-particle metric factors of an SMC iteration
+  pool      Context.ps_reweight_resample: one persistent-sampling step over a pool of populations
+  smc       SmcRuns: a population is set up and taken through whole SMC iterations
+
+Inputs are seeded: synthetic events (the repository's recipe: three sites, power-law PSD, Gaussian noise, an
+injection at a given SNR), prior draws, and for the samplers a population tempered to some beta.  Everything a
+case feeds to the library, and everything `exact` returns, comes from the plain 64-bit torch waveform below.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2601_02336_amd import smcgw, synth
+
+DEV = "cuda:0"
+TWO_PI = 2.0 * math.pi
+MOST_ELEMENTS = 12_000_000   # particle-bins handled at once by the 64-bit arithmetic
+
+# Segments of the repository's configurations: (duration [s], f_high [Hz], SNR).
+SEGMENTS = {"quarter": (4.0, 512.0, 20.0), "4s": (4.0, 1024.0, 20.0), "8s": (8.0, 1024.0, 20.0),
+            "16s": (16.0, 2048.0, 20.0), "32s": (32.0, 2048.0, 20.0), "128s": (128.0, 2048.0, 30.0)}
+F_LOW = 20.0
+RAGGED = ("4s", "4s", "8s", "8s", "16s", "16s", "32s", "32s")
+MAX_COST = 16384 * 27349   # particle-bins of the ragged batch, the largest likelihood call
+
+
+def bins_of(segment):
+    t, f_high, _ = SEGMENTS[segment]
+    return synth.n_bins(F_LOW, f_high, 1.0 / t)
+
+
+# ------------------------------------------------------------------ the likelihood in plain 64-bit arithmetic
+class Plain:
+    """One event on its frequency grid (or folded onto relative-binning edges): 64-bit tensors on the GPU."""
+
+    def __init__(self, ev, data=True):
+        self.f = torch.tensor(synth.freq_grid(ev.f_low, ev.df, ev.n), device=DEV)
+        self.t_sun, self.mpc_m, self.c, self.gmst = ev.t_sun, ev.mpc_m, ev.c_light, ev.gmst
+        w = 4.0 * ev.df / torch.tensor(ev.psd, device=DEV)
+        self.weight = w * self.f ** (-7.0 / 3.0)          # of |h|^2, amplitude shape included
+        self.hnorm = self.weight.sum(1)
+        if data:
+            d = torch.tensor(ev.data, device=DEV)
+            self.u = w * d.conj() * self.f ** (-7.0 / 6.0)
+            self.dd = float((w * (d.real ** 2 + d.imag ** 2)).sum())
+        self.sites = [self._site(s) for s in ev.sites]
+
+    @staticmethod
+    def _site(s):
+        cl, sl, co, so = math.cos(s.lat), math.sin(s.lat), math.cos(s.lon), math.sin(s.lon)
+        pos = s.radius * np.array([cl * co, cl * so, sl])
+        east, north = np.array([-so, co, 0.0]), np.array([-sl * co, -sl * so, cl])
+        x = math.cos(s.az_x) * east + math.sin(s.az_x) * north
+        y = math.cos(s.az_y) * east + math.sin(s.az_y) * north
+        return torch.tensor(pos, device=DEV), torch.tensor(0.5 * (np.outer(x, x) - np.outer(y, y)), device=DEV)
+
+    def fold(self, theta0, eps):
+        """Relative binning (Zackay, Dai & Venumadhav 2018): the data on the edges of the phase-difference bound."""
+        f = self.f.cpu().numpy()
+        n = len(f)
+        bound = sum((-(f / f[0]) ** g if g < 0 else (f / f[-1]) ** g)
+                    for g in (-5 / 3, -2 / 3, 1.0, 5 / 3, 7 / 3)) * TWO_PI
+        grown = bound - bound[0]
+        steps = min(max(1, math.ceil(grown[-1] / eps)), n - 1)
+        edges = np.searchsorted(grown, grown[-1] * np.arange(1, steps) / steps)
+        edges = np.unique(np.concatenate([[0], edges[edges < n - 1], [n - 1]]))
+        e = torch.tensor(edges, device=DEV)
+        th0 = torch.tensor(np.asarray(theta0)[None], device=DEV)
+        rot = torch.polar(torch.ones(()).double().to(DEV), self.phase(th0)[0])   # e^{+i Phi0}, [n_det][N]
+        v = self.u * rot.conj()
+        of = torch.bucketize(torch.arange(n, device=DEV), e[1:-1], right=True)   # bin of every grid point
+        nb = len(edges) - 1
+        fe = self.f[e]
+        both = torch.stack([v, v * (self.f - fe[of])])
+        sums = torch.zeros((2, v.shape[0], nb), dtype=v.dtype)
+        sums.index_add_(2, of.cpu(), both.cpu())
+        a0, a1 = sums.to(DEV)
+        slope = a1 / (fe[1:] - fe[:-1])
+        c = torch.zeros((v.shape[0], nb + 1), dtype=v.dtype, device=DEV)
+        c[:, :-1] += a0 - slope
+        c[:, 1:] += slope
+        self.u, self.f = c * rot[:, e], fe
+        return self
+
+    def phase(self, th):
+        """Phase of every detector, [n][n_det][bins] radians: TaylorF2 (3.5PN) with the arrival-time terms."""
+        mc, q, c1, c2 = (th[:, k:k + 1] for k in range(4))
+        eta = q / (1 + q) ** 2
+        delta = (1 - q) / (1 + q)
+        cs, ca = 0.5 * (c1 + c2), 0.5 * (c1 - c2)
+        dca = delta * ca
+        pi = math.pi
+        p2 = 3715 / 756 + 55 / 9 * eta
+        p3 = -16 * pi + 113 / 3 * dca + (113 / 3 - 76 / 3 * eta) * cs
+        p4 = (15293365 / 508032 + 27145 / 504 * eta + 3085 / 72 * eta ** 2 + (-405 / 8 + 200 * eta) * ca ** 2
+              - 405 / 4 * dca * cs + (-405 / 8 + 2.5 * eta) * cs ** 2)
+        p5 = (38645 * pi / 756 - 65 * pi / 9 * eta + (-732985 / 2268 - 140 / 9 * eta) * dca
+              + (-732985 / 2268 + 24260 / 81 * eta + 340 / 9 * eta ** 2) * cs)
+        p6 = (11583231236531 / 4694215680 - 6848 / 21 * (0.57721566490153286061 + math.log(4)) - 640 / 3 * pi ** 2
+              + (-15737765635 / 3048192 + 2255 / 12 * pi ** 2) * eta + 76055 / 1728 * eta ** 2
+              - 127825 / 1296 * eta ** 3 + 2270 / 3 * pi * dca + (2270 / 3 * pi - 520 * pi * eta) * cs)
+        p7 = (77096675 * pi / 254016 + 378515 * pi / 1512 * eta - 74045 * pi / 756 * eta ** 2
+              + (-25150083775 / 3048192 + 26804935 / 6048 * eta - 1985 / 48 * eta ** 2) * dca
+              + (-25150083775 / 3048192 + 10566655595 / 762048 * eta - 1042165 / 3024 * eta ** 2
+                 + 5345 / 36 * eta ** 3) * cs)
+        lnv = (torch.log(pi * mc * eta ** -0.6 * self.t_sun) + torch.log(self.f)) / 3
+        v = torch.exp(lnv)
+        s = p5 * (1 + 3 * lnv) + v * (p6 - 6848 / 21 * lnv + v * p7)
+        s = 1 + v * v * (p2 + v * (p3 + v * (p4 + v * s)))
+        psi = 3 / (128 * eta) * s / v ** 5 - th[:, 10:11] - pi / 4
+        ra, dec = th[:, 7] - self.gmst, th[:, 8]
+        n = torch.stack([torch.cos(dec) * torch.cos(ra), torch.cos(dec) * torch.sin(ra), torch.sin(dec)], 1)
+        delay = torch.stack([th[:, 9] - n @ pos / self.c for pos, _ in self.sites], 1)
+        return psi[:, None, :] + TWO_PI * delay[:, :, None] * self.f
+
+    def projection(self, th):
+        """C_A times the complex projection of every detector, [n][n_det]."""
+        ra, dec, psi2, ci = th[:, 7] - self.gmst, th[:, 8], 2 * th[:, 6], torch.cos(th[:, 5])
+        zero = torch.zeros_like(ra)
+        p = torch.stack([torch.sin(ra), -torch.cos(ra), zero], 1)
+        q = torch.stack([-torch.cos(ra) * torch.sin(dec), -torch.sin(ra) * torch.sin(dec), torch.cos(dec)], 1)
+        amp = math.sqrt(5 / 24) * math.pi ** (-2 / 3) * (th[:, 0] * self.t_sun) ** (5 / 6) * self.c \
+            / (th[:, 4] * self.mpc_m)
+        out = []
+        for _, resp in self.sites:
+            a = ((p @ resp) * p).sum(1) - ((q @ resp) * q).sum(1)
+            b = 2 * ((q @ resp) * p).sum(1)
+            fp, fx = a * torch.cos(psi2) + b * torch.sin(psi2), b * torch.cos(psi2) - a * torch.sin(psi2)
+            out.append(torch.complex(fp * 0.5 * (1 + ci * ci), -fx * ci))
+        return amp[:, None] * torch.stack(out, 1)
+
+    def _loglike(self, th):
+        ph = self.phase(th)
+        cs, sn = torch.cos(ph), torch.sin(ph)
+        z = torch.complex((self.u.real * cs + self.u.imag * sn).sum(2), (self.u.imag * cs - self.u.real * sn).sum(2))
+        pr = self.projection(th)
+        return -0.5 * self.dd + ((pr * z).real - 0.5 * (pr.real ** 2 + pr.imag ** 2) * self.hnorm).sum(1)
+
+    def loglike(self, theta, grad=True):
+        ll = torch.empty(len(theta), dtype=torch.float64, device=DEV)
+        g = torch.empty_like(theta) if grad else None
+        step = max(1, MOST_ELEMENTS // (len(self.f) * len(self.sites)))
+        for i in range(0, len(theta), step):
+            th = theta[i:i + step].detach().clone().requires_grad_(grad)
+            with torch.set_grad_enabled(grad):
+                v = self._loglike(th)
+            ll[i:i + step] = v.detach()
+            if grad:
+                g[i:i + step] = torch.autograd.grad(v.sum(), th)[0]
+        return (ll, g) if grad else ll
+
+    def strain(self, th):
+        """h_d(f) without noise, [n][n_det][bins] complex."""
+        pr = self.projection(th)
+        return pr[:, :, None] * self.f ** (-7.0 / 6.0) * torch.polar(torch.ones_like(self.f), -self.phase(th))
+
+    def fisher(self, theta, stride=1):
+        """<dh/dtheta_k | dh/dtheta_l> by forward-mode tangents, [n][11][11]; with a stride over every so many bins."""
+        kept = self.f, self.weight
+        self.f, self.weight = self.f[::stride].contiguous(), self.weight[:, ::stride].contiguous()
+        shape = (self.weight * stride).sqrt() * self.f ** (7.0 / 6.0)
+        out = torch.empty((len(theta), 11, 11), dtype=torch.float64, device=DEV)
+        step = max(1, MOST_ELEMENTS // (11 * len(self.f) * len(self.sites)))
+        for i in range(0, len(theta), step):
+            th = theta[i:i + step]
+            rows = []
+            for k in range(11):
+                t = torch.zeros_like(th)
+                t[:, k] = 1.0
+                h = torch.func.jvp(self.strain, (th,), (t,))[1] * shape
+                rows.append(torch.view_as_real(h).reshape(len(th), -1))
+            j = torch.stack(rows, 1)
+            for a in range(11):
+                for b in range(a + 1):
+                    out[i:i + step, a, b] = out[i:i + step, b, a] = (j[:, a] * j[:, b]).sum(1)
+        self.f, self.weight = kept
+        return out
+
+
+def prior_precision(bounds):
+    """12 / width^2 of a uniform coordinate, the inverse variance of a log-uniform one."""
+    out = []
+    for b in bounds:
+        if b.prior == synth.PRIOR_LOGUNIFORM:
+            lr = math.log(b.hi / b.lo)
+            m1, m2 = (b.hi - b.lo) / lr, (b.hi ** 2 - b.lo ** 2) / (2 * lr)
+            out.append(1.0 / (m2 - m1 * m1))
+        else:
+            out.append(12.0 / (b.hi - b.lo) ** 2)
+    return np.array(out)
+
+
+def metric_factor(fisher, beta, bounds):
+    """Lower Cholesky factor of (beta F + prior precision)^-1 per particle, [n][11][11] (scaled to unit diagonal first)."""
+    m = beta * fisher.cpu().numpy() + np.diag(prior_precision(bounds))
+    s = 1.0 / np.sqrt(np.einsum("nii->ni", m))
+    inv = np.linalg.inv(m * s[:, :, None] * s[:, None, :])
+    low = np.linalg.cholesky(0.5 * (inv + inv.transpose(0, 2, 1))) * s[:, :, None]
+    return torch.tensor(np.ascontiguousarray(low), device=DEV)
+
+
+# ------------------------------------------------------------------ inputs
+def make_event(segment, n_det, rng):
+    """A synthetic event of the repository's recipe: a prior draw injected at the segment's SNR in Gaussian noise."""
+    t, f_high, snr = SEGMENTS[segment]
+    n = bins_of(segment)
+    f = synth.freq_grid(F_LOW, 1.0 / t, n)
+    psd = np.stack([synth.power_law_psd(f) * s for s in (1.0, 1.0, 2.0)[:n_det]])
+    th = synth.prior_draw(rng, 1, synth.gw_bounds(1.0, 1.0e4))[0]
+    th[4] = 1000.0
+    ev = synth.Event(F_LOW, 1.0 / t, n, synth.synthetic_sites(n_det), np.zeros((n_det, n), complex), psd, th, snr)
+    plain = Plain(ev, data=False)
+    at = torch.tensor(th[None], device=DEV)
+    hh = float((plain.projection(at).abs()[0] ** 2 * plain.hnorm).sum())
+    th[4] *= math.sqrt(hh) / snr
+    at[0, 4] = th[4]
+    h = plain.strain(at)[0].cpu().numpy()
+    return ev.with_data(h + synth.gaussian_noise(rng, psd, ev.df))
+
+
+def tempered(plain, bounds, n, beta, rng):
+    """A population at temperature beta: prior draws resampled with weights L^beta."""
+    x = synth.prior_draw(rng, 4 * n, bounds)
+    ll = plain.loglike(torch.tensor(x, device=DEV), grad=False).cpu().numpy()
+    w = np.exp(beta * (ll - ll.max()))
+    return torch.tensor(x[rng.choice(len(x), n, p=w / w.sum())], device=DEV)
+
+
+def the_event(case, seed):
+    rng = np.random.default_rng([seed, 1])
+    ev = make_event(case["segment"], case["detectors"], rng)
+    return ev, synth.gw_prior_for(ev), rng
+
+
+def plain_of(case, ev):
+    p = Plain(ev)
+    return p.fold(ev.theta_inj, case["eps"]) if case.get("eps") else p
+
+
+def context_for(case, ev, bounds):
+    ctx = smcgw.Context(0)
+    if case.get("eps"):
+        ctx.add_event_rb(ev, ev.theta_inj, case["eps"])
+    else:
+        ctx.add_event(ev)
+    ctx.set_prior(bounds)
+    ctx.set_target(synth.TARGET_GW, 11)
+    return ctx
+
+
+def precision_of(case):
+    return smcgw.MIXED if case["precision"] == "mixed" else smcgw.PLAIN_FP64
+
+
+def likelihood_inputs(case, seed):
+    """(events, prior box, particles, event of each particle) of the likelihood families."""
+    if case["family"] == "ragged":
+        rng = np.random.default_rng([seed, 1])
+        evs = [make_event(s, 3, rng) for s in RAGGED[:case["events"]]]
+        dls = [float(e.theta_inj[4]) for e in evs]
+        bounds = synth.gw_bounds(min(dls) / 5, max(dls) * 5)
+        of = (np.arange(case["particles"]) % len(evs)).astype(np.int32)
+    else:
+        ev, bounds, rng = the_event(case, seed)
+        evs, of = [ev], None
+    x = torch.tensor(synth.prior_draw(rng, case["particles"], bounds), device=DEV)
+    return evs, bounds, x, of
+
+
+def pool_inputs(case, seed):
+    """T populations of a tempering ladder: log-likelihoods of a Gaussian posterior in 11 dimensions at rising beta
+    (log L falls by a gamma variate of the tempered posterior's chi-square), the exact log Z of each."""
+    rng = np.random.default_rng([seed, 2])
+    t, n = case["populations"], case["particles"]
+    betas = np.concatenate([[0.0], np.geomspace(1e-3, 0.5, t - 1)]) if t > 1 else np.zeros(1)
+    # prior N(0, 1), likelihood N(0, s^2) per coordinate: p_beta = N(0, v_beta), v = 1 / (1 + beta / s^2)
+    s2 = 1.0 / case["peak"]
+    var = 1.0 / (1.0 + betas / s2)
+    x = rng.standard_normal((t, n, 11)) * np.sqrt(var)[:, None, None]
+    ll = -0.5 * (x ** 2).sum(2) / s2
+    logz = 11 * 0.5 * np.log(var)
+    return x.reshape(t * n, 11), ll.reshape(t * n), -x.reshape(t * n, 11) / s2, betas.tolist(), logz.tolist()
+
+
+def prepare(case, seed):
+    fam = case["family"]
+    s = {"case": case}
+    if fam in ("loglike", "binned", "ragged"):
+        evs, _, s["theta"], of = likelihood_inputs(case, seed)
+        s["ctx"] = ctx = smcgw.Context(0)
+        for ev in evs:
+            if fam == "binned":
+                ctx.add_event_rb(ev, ev.theta_inj, case["eps"])
+            else:
+                ctx.add_event(ev)
+        s["event"] = None if of is None else torch.tensor(of, device=DEV)
+    elif fam == "nuts":
+        ev, bounds, rng = the_event(case, seed)
+        full, target = Plain(ev), plain_of(case, ev)
+        s["theta"] = x = tempered(target, bounds, case["particles"], case["beta"], rng)
+        s["logl"], s["grad"] = target.loglike(x)
+        s["chol"] = metric_factor(full.fisher(x, stride=8), case["beta"], bounds)
+        s["ctx"] = context_for(case, ev, bounds)
+        s["work"] = [torch.empty_like(s[k]) for k in ("theta", "logl", "grad")]
+        s["seed"] = seed
+    elif fam == "metric":
+        ev, bounds, rng = the_event(case, seed)
+        s["theta"] = torch.tensor(synth.prior_draw(rng, case["particles"], bounds), device=DEV)
+        s["ctx"] = context_for(case, ev, bounds)
+    elif fam == "pool":
+        x, ll, g, s["betas"], s["logz"] = pool_inputs(case, seed)
+        s["pool"] = [torch.tensor(v, device=DEV) for v in (x, ll, g)]
+        s["ctx"] = smcgw.Context(0)
+        n = case["particles"]
+        s["out"] = [torch.empty((n, 11), dtype=torch.float64, device=DEV), torch.empty(n, dtype=torch.float64, device=DEV),
+                    torch.empty((n, 11), dtype=torch.float64, device=DEV)]
+        s["seed"] = seed
+    elif fam == "smc":
+        ev, bounds, rng = the_event(case, seed)
+        s["theta"] = torch.tensor(synth.prior_draw(rng, case["runs"] * case["particles"], bounds), device=DEV)
+        s["ctx"] = context_for(case, ev, bounds)
+        s["seed"] = seed
+    else:
+        raise ValueError(fam)
+    return s
+
+
+def run(s):
+    case, ctx = s["case"], s["ctx"]
+    fam = case["family"]
+    if fam in ("loglike", "binned", "ragged"):
+        out = ctx.loglike_grad(s["theta"], want_grad=case["grad"], event_of_particle=s["event"],
+                               precision=precision_of(case))
+        return {"logl": out[0], "grad": out[1]} if case["grad"] else {"logl": out}
+    if fam == "nuts":
+        # a transition replaces the population: it works on a copy, so that the pass can be repeated
+        for dst, src in zip(s["work"], (s["theta"], s["logl"], s["grad"])):
+            dst.copy_(src)
+        x, ll, g = s["work"]
+        out = ctx.nuts_step(x, ll, g, s["chol"], step=case["step"], beta=case["beta"], seed=s["seed"], iteration=1,
+                            max_depth=case["max_depth"], precision=precision_of(case))
+        return {"theta": x, "logl": ll, "grad": g, **out}
+    if fam == "metric":
+        chol, _, status = ctx.local_metric(s["theta"], case["beta"])
+        return {"chol": chol, "status": status}
+    if fam == "pool":
+        x, ll, g = s["out"]
+        beta, logz, anc = ctx.ps_reweight_resample(*s["pool"], s["betas"], s["logz"], case["alpha"], s["seed"], 1,
+                                                   x, ll, g)
+        return {"beta": beta, "logz": logz, "theta": x, "logl": ll, "grad": g, "ancestors": anc}
+    runs = smcgw.SmcRuns(ctx, s["theta"], case["runs"], alpha=case["alpha"], step=case["step"],
+                         max_depth=case["max_depth"], shrink=0.0, seed=s["seed"], precision=precision_of(case),
+                         metric=case["metric"], history_cap=case["iterations"])
+    for _ in range(case["iterations"]):
+        runs.step()
+    return {"theta": runs.theta, "logl": runs.logl, "grad": runs.grad, "ancestors": runs.ancestors,
+            "state": runs.state_dev, "history": runs.history_dev}
+
+
+def exact(case, seed):
+    fam = case["family"]
+    if fam in ("loglike", "binned", "ragged"):
+        evs, _, x, of = likelihood_inputs(case, seed)
+        ll = torch.empty(len(x), dtype=torch.float64, device=DEV)
+        g = torch.empty_like(x)
+        for k, ev in enumerate(evs):
+            rows = slice(None) if of is None else torch.tensor(np.nonzero(of == k)[0], device=DEV)
+            if case["grad"]:
+                ll[rows], g[rows] = plain_of(case, ev).loglike(x[rows])
+            else:
+                ll[rows] = plain_of(case, ev).loglike(x[rows], grad=False)
+        return {"logl": ll, "grad": g} if case["grad"] else {"logl": ll}
+    if fam == "metric":
+        ev, bounds, rng = the_event(case, seed)
+        x = torch.tensor(synth.prior_draw(rng, case["particles"], bounds), device=DEV)
+        if len(x) * ev.n * ev.n_det > 2.5e8:
+            return None   # the tangents over every bin take too long
+        return {"chol": metric_factor(Plain(ev).fisher(x), case["beta"], bounds), "status": None}
+    if fam == "pool":
+        _, ll, _, betas, logz = pool_inputs(case, seed)
+        n, t = case["particles"], case["populations"]
+        terms = np.array(betas)[:, None] * ll - np.array(logz)[:, None]
+        top = terms.max(0)
+        mix = top + np.log(np.exp(terms - top).sum(0)) - math.log(t)
+
+        def weights(beta):
+            v = beta * ll - mix
+            return np.exp(v - v.max()), v.max()
+
+        def ess(beta):
+            w, _ = weights(beta)
+            return w.sum() ** 2 / (w * w).sum()
+
+        lo, hi = betas[-1], 1.0
+        if ess(1.0) >= case["alpha"] * n:
+            lo = 1.0
+        for _ in range(100):
+            if hi - lo <= 1e-14 or lo == 1.0:
+                break
+            mid = 0.5 * (lo + hi)
+            lo, hi = (mid, hi) if ess(mid) >= case["alpha"] * n else (lo, mid)
+        w, top = weights(lo)
+        return {"beta": lo, "logz": top + math.log(w.sum()) - math.log(n * t), "theta": None, "logl": None,
+                "grad": None, "ancestors": None}
+    return None   # sampled trajectories: no closed value
+
+
+def work(case):
+    """Every input read once and every output written once; the arithmetic of the bin sums (an FMA is two
+    operations, a sine or cosine one) where the path runs over bins."""
+    fam, p = case["family"], case["particles"]
+    if fam == "pool":
+        t = case["populations"]
+        return {"bytes": 8.0 * (t * p * 1 + p * 23 * 2) + 4.0 * p, "flops": t * p * (4.0 * t + 60.0)}
+    d = case.get("detectors", 3)
+    segs = RAGGED[:case["events"]] if fam == "ragged" else (case["segment"],)
+    n = sum(bins_of(s) for s in segs) / len(segs)
+    if case.get("eps"):
+        n = min(n, 31.0 / case["eps"])
+    per_bin = 16 + 16 * d + (18 + 7 * d if case.get("grad", True) else 0)
+    table = len(segs) * n * (24 + (8 if case.get("precision") == "mixed" else 16) * d)
+    if fam in ("loglike", "binned", "ragged"):
+        return {"bytes": p * 8.0 * (11 + 1 + (11 if case["grad"] else 0)) + table, "flops": p * n * per_bin}
+    if fam == "metric":
+        return {"bytes": p * 8.0 * (11 + 121) + d * 800.0, "flops": p * 20000.0}
+    # samplers: leaves of a tree of the usual depth (6 to 7 doublings unless the limit is lower)
+    leaves = 2.0 ** min(case["max_depth"], 6.5) - 1
+    if fam == "nuts":
+        return {"bytes": p * 8.0 * (23 * 2 + 121 + 3) + table, "flops": p * leaves * (n * per_bin + 3000.0)}
+    r, it = case["runs"], case["iterations"]
+    return {"bytes": r * p * 8.0 * (11 + it * (23 * 4 + 2 * 121)) + table,
+            "flops": r * p * it * (leaves * (n * per_bin + 3000.0) + 20000.0)}
+
+
+# ------------------------------------------------------------------ the cases
+def listed():
+    return [
+        # a single point: the call inside an optimiser or a check, where only latency counts
+        {"name": "one point 8s", "family": "loglike", "segment": "8s", "detectors": 3, "particles": 1,
+         "precision": "mixed", "grad": True},
+        # a few chains on the long segment: few particles, many bins
+        {"name": "few points 128s", "family": "loglike", "segment": "128s", "detectors": 3, "particles": 37,
+         "precision": "mixed", "grad": True},
+        # the batched likelihood and gradient of one SMC population, the benchmark's size
+        {"name": "batch 8s", "family": "loglike", "segment": "8s", "detectors": 3, "particles": 4096,
+         "precision": "mixed", "grad": True},
+        # the 64-bit form, as a check of a mixed-precision result or a reference run; an odd population
+        {"name": "plain 16s", "family": "loglike", "segment": "16s", "detectors": 2, "particles": 1001,
+         "precision": "plain", "grad": True},
+        # values only over many points, as in importance sampling, on the one-detector event
+        {"name": "values quarter", "family": "loglike", "segment": "quarter", "detectors": 1, "particles": 20000,
+         "precision": "mixed", "grad": False},
+        # the long-segment mitigation: a folded event of about 300 edges
+        {"name": "binned 8s", "family": "binned", "segment": "8s", "detectors": 3, "particles": 6000, "eps": 0.1,
+         "precision": "mixed", "grad": True},
+        # the batch of eight events of different lengths in one call
+        {"name": "ragged batch", "family": "ragged", "events": 8, "detectors": 3, "particles": 16384,
+         "precision": "mixed", "grad": True},
+        # the mutation of an SMC iteration on the full grid, as in the benchmark (one run's population)
+        {"name": "nuts 8s", "family": "nuts", "segment": "8s", "detectors": 3, "particles": 2048, "beta": 0.05,
+         "step": 0.08, "max_depth": 10, "precision": "mixed"},
+        # the mutation on a folded event, three runs' particles
+        {"name": "nuts binned", "family": "nuts", "segment": "8s", "detectors": 3, "particles": 6144, "eps": 0.1,
+         "beta": 0.05, "step": 0.1, "max_depth": 10, "precision": "mixed"},
+        # the per-particle metric of three runs
+        {"name": "metric 8s", "family": "metric", "segment": "8s", "detectors": 3, "particles": 6144, "beta": 0.05},
+        # persistent sampling: the step over a pool of thirty populations
+        {"name": "pool 30x2048", "family": "pool", "populations": 30, "particles": 2048, "peak": 1000.0,
+         "alpha": 0.95},
+        # whole SMC iterations from the prior on a folded event, three runs in one call
+        {"name": "smc binned", "family": "smc", "segment": "8s", "detectors": 3, "runs": 3, "particles": 2048,
+         "eps": 0.1, "iterations": 2, "alpha": 0.95, "step": 0.1, "max_depth": 10, "metric": "local",
+         "precision": "mixed"},
+    ]
+
+
+def spread(rng, lo, hi):
+    """A whole number between lo and hi, even over its logarithm."""
+    return max(lo, min(hi, round(math.exp(rng.uniform(math.log(lo), math.log(hi))))))
+
+
+def draw(rng):
+    fam = rng.choice(["loglike", "loglike", "loglike", "binned", "ragged", "nuts", "nuts", "metric", "pool", "smc"])
+    seg = rng.choice(list(SEGMENTS))
+    det = rng.choice([1, 2, 3, 3])
+    prec = rng.choice(["mixed", "mixed", "plain"])
+    if fam == "loglike":
+        most = MAX_COST // bins_of(seg) // (4 if prec == "plain" else 1)
+        return {"family": fam, "segment": seg, "detectors": det, "particles": spread(rng, 1, min(20000, most)),
+                "precision": prec, "grad": rng.random() < 0.75}
+    if fam == "binned":
+        return {"family": fam, "segment": seg, "detectors": det, "particles": spread(rng, 1, 20000),
+                "eps": round(rng.uniform(0.05, 0.5), 3), "precision": prec, "grad": rng.random() < 0.75}
+    if fam == "ragged":
+        return {"family": fam, "events": rng.randint(2, 8), "detectors": 3, "particles": spread(rng, 64, 16384),
+                "precision": "mixed", "grad": rng.random() < 0.75}
+    if fam == "nuts":
+        binned = rng.random() < 0.5
+        c = {"family": fam, "segment": rng.choice(["quarter", "4s", "8s"]), "detectors": det,
+             "particles": spread(rng, 16, 6144 if binned else 2048), "beta": round(rng.uniform(0.01, 0.15), 4),
+             "step": 0.1 if binned else 0.08, "max_depth": rng.randint(4, 10), "precision": "mixed"}
+        if binned:
+            c["eps"] = round(rng.uniform(0.1, 0.5), 3)
+        return c
+    if fam == "metric":
+        return {"family": fam, "segment": seg, "detectors": det, "particles": spread(rng, 8, 8192),
+                "beta": round(rng.uniform(0.0, 1.0), 3)}
+    if fam == "pool":
+        return {"family": fam, "populations": rng.randint(1, 32), "particles": spread(rng, 128, 4096),
+                "peak": round(rng.uniform(100.0, 10000.0), 1), "alpha": rng.choice([0.5, 0.9, 0.95])}
+    runs = rng.randint(1, 4)
+    return {"family": fam, "segment": rng.choice(["quarter", "4s", "8s"]), "detectors": det, "runs": runs,
+            "particles": spread(rng, 128, 6144 // max(runs, 3)), "eps": round(rng.uniform(0.1, 0.5), 3), "iterations": 2,
+            "alpha": rng.choice([0.5, 0.9, 0.95]), "step": 0.1, "max_depth": rng.randint(4, 10),
+            "metric": rng.choice(["local", "population"]), "precision": "mixed"}
