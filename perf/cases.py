@@ -8,7 +8,7 @@ Every workload is a plain dict.  The families, each through the entry point a us
   nuts      Context.nuts_step: one NUTS transition per particle on the event likelihood
   metric    Context.local_metric: the per-particle metric factors of an SMC iteration
   pool      Context.ps_reweight_resample: one persistent-sampling step over a pool of populations
-  smc       SmcRuns: a population is set up and taken through whole SMC iterations
+  smc       SmcRuns: a population is set up and taken through a whole SMC iteration
 
 Inputs are seeded: synthetic events (the repository's recipe: three sites, power-law PSD, Gaussian noise, an
 injection at a given SNR), prior draws, and for the samplers a population tempered to some beta.  Everything a
@@ -476,9 +476,11 @@ def listed():
         # persistent sampling: the step over a pool of thirty populations
         {"name": "pool 30x2048", "family": "pool", "populations": 30, "particles": 2048, "peak": 1000.0,
          "alpha": 0.95},
-        # whole SMC iterations from the prior on a folded event, three runs in one call
+        # a run's set-up and first whole SMC iteration from the prior on a folded event, three runs in one call; the
+        # trees stay short: on this posterior longer trajectories blow a last-bit change of beta or of the metric up
+        # until two correct results no longer resemble each other
         {"name": "smc binned", "family": "smc", "segment": "8s", "detectors": 3, "runs": 3, "particles": 2048,
-         "eps": 0.1, "iterations": 2, "alpha": 0.95, "step": 0.1, "max_depth": 10, "metric": "local",
+         "eps": 0.1, "iterations": 1, "alpha": 0.95, "step": 0.1, "max_depth": 4, "metric": "local",
          "precision": "mixed"},
     ]
 
@@ -519,6 +521,6 @@ def draw(rng):
                 "peak": round(rng.uniform(100.0, 10000.0), 1), "alpha": rng.choice([0.5, 0.9, 0.95])}
     runs = rng.randint(1, 4)
     return {"family": fam, "segment": rng.choice(["quarter", "4s", "8s"]), "detectors": det, "runs": runs,
-            "particles": spread(rng, 128, 6144 // max(runs, 3)), "eps": round(rng.uniform(0.1, 0.5), 3), "iterations": 2,
-            "alpha": rng.choice([0.5, 0.9, 0.95]), "step": 0.1, "max_depth": rng.randint(4, 10),
+            "particles": spread(rng, 128, 6144 // max(runs, 3)), "eps": round(rng.uniform(0.1, 0.5), 3), "iterations": 1,
+            "alpha": rng.choice([0.5, 0.9, 0.95]), "step": 0.1, "max_depth": rng.randint(2, 4),
             "metric": rng.choice(["local", "population"]), "precision": "mixed"}
