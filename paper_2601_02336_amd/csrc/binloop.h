@@ -27,6 +27,9 @@ __device__ __forceinline__ double uniform_d(double v) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+__device__ __forceinline__ float uniform_f(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
 
 // sin(2 pi x), cos(2 pi x) for 0 <= x < 1 on the hardware transcendental unit
 // (v_sin_f32 / v_cos_f32 take their argument in revolutions).
@@ -66,6 +69,7 @@ constexpr int BUF_RSRC_WORD3 = 0x00020000;
 struct TableView {
     __amdgpu_buffer_rsrc_t fwl, u;
     int npad;
+    int chunks;   // chunks that hold a bin
 };
 
 // The pointer and size are made wave-uniform first: a resource must sit in
@@ -143,20 +147,28 @@ __device__ __forceinline__ void load_chunk(BinPair<NDET, double2>& x, const Tabl
 // bin of a block starts the per-lane partial sums and the block ends with
 // their flush.  A lane adds its bins in chunk order, each chunk's pair in bin
 // order.
+//
+// The table's last block ends with the chunk that holds the last bin: a chunk
+// of padding alone (u = 0) adds only zeros, so it is not visited.  Of a
+// folded event's ~310 edges that skips one chunk in four, of the 8033-bin
+// grid's 64 chunks one.
 template <class In, class Acc>
-__device__ __forceinline__ void bin_loop(Acc& A, const BinCoef& k, const TableView& t, int blk0, int blk_step,
-                                         int nblk) {
+__device__ __forceinline__ void bin_loop(Acc& A, const BinCoef& k, const TableView& t, int blk0, int blk_step) {
     static_assert(BLK_CHUNKS % 2 == 0, "a block holds a whole number of buffer pairs");
     const unsigned lane = threadIdx.x & 63;
+    const int nblk = t.npad / TABLE_PAD;
     const int nb = blk0 < nblk ? (nblk - blk0 + blk_step - 1) / blk_step : 0;   // this wave's blocks
     if (nb == 0) return;
-    const int last = nb * BLK_CHUNKS - 1;                                      // this wave's last chunk
+    const int lastblk = blk0 + (nb - 1) * blk_step;
+    const int rem = lastblk == nblk - 1 ? t.chunks - lastblk * BLK_CHUNKS : BLK_CHUNKS;   // its chunks in the last one
+    const int full = rem == BLK_CHUNKS ? nb : nb - 1;
+    const int last = (nb - 1) * BLK_CHUNKS + rem - 1;                           // this wave's last chunk
     auto base_of = [&](int c) {
         return (blk0 + (c / BLK_CHUNKS) * blk_step) * TABLE_PAD + CHUNK_BINS * (c % BLK_CHUNKS);
     };
     In a, b;
     load_chunk(a, t, base_of(0), lane);
-    for (int blk = 0; blk < nb; ++blk) {
+    for (int blk = 0; blk < full; ++blk) {
 #pragma unroll
         for (int pr = 0; pr < BLK_CHUNKS / 2; ++pr) {
             const int c = blk * BLK_CHUNKS + 2 * pr;
@@ -169,36 +181,57 @@ __device__ __forceinline__ void bin_loop(Acc& A, const BinCoef& k, const TableVi
         }
         A.flush();
     }
+    if (full < nb) {
+        A.clear();
+        for (int c = full * BLK_CHUNKS; c <= last; c += 2) {
+            load_chunk(b, t, base_of(min(c + 1, last)), lane);
+            A.bin(k, a.b[0], false);
+            A.bin(k, a.b[1], false);
+            if (c == last) break;
+            load_chunk(a, t, base_of(min(c + 2, last)), lane);
+            A.bin(k, b.b[0], false);
+            A.bin(k, b.b[1], false);
+        }
+        A.flush();
+    }
 }
 
 // Moments of NDET detectors from a wavefront's per-lane sums into a moment
-// block (MOM_SIZE entries, those of absent detectors zero).
+// block.
 template <int NDET>
 __device__ __forceinline__ void store_moments(const double (&Zr)[NDET], const double (&Zi)[NDET],
                                               const double (&T)[NDET], const double (&G)[NCOEF], double* out) {
-    constexpr int K = 3 * NDET + NCOEF;
+    constexpr int K = mom_g(NDET, NCOEF);
     double v[K];
-    int idx[K];
 #pragma unroll
     for (int d = 0; d < NDET; ++d) {
-        v[d] = Zr[d]; idx[d] = MOM_ZR + d;
-        v[NDET + d] = Zi[d]; idx[NDET + d] = MOM_ZI + d;
-        v[2 * NDET + d] = T[d]; idx[2 * NDET + d] = MOM_T + d;
+        v[mom_zr(NDET, d)] = Zr[d];
+        v[mom_zi(NDET, d)] = Zi[d];
+        v[mom_t(NDET, d)] = T[d];
     }
 #pragma unroll
-    for (int b = 0; b < NCOEF; ++b) { v[3 * NDET + b] = G[b]; idx[3 * NDET + b] = MOM_G + b; }
-    wave_totals_to<K>(v, idx, out);
+    for (int b = 0; b < NCOEF; ++b) v[mom_g(NDET, b)] = G[b];
+    wave_totals_to<K>(v, out);
+}
+
+// The Z moments alone (a value without its gradient), each summed over the
+// lanes in the order of its place in store_moments' list, so that the value is
+// the same with and without the gradient.
+template <int NDET>
+__device__ __forceinline__ void store_values(const double (&Zr)[NDET], const double (&Zi)[NDET], double* out) {
+    constexpr int K = mom_g(NDET, NCOEF);
     const int lane = threadIdx.x & 63;
-    constexpr int ABSENT = MAXDET - NDET;
-    if (lane >= 8 && lane < 8 + 3 * ABSENT) {
-        const int j = lane - 8, d = NDET + j % (ABSENT > 0 ? ABSENT : 1), which = j / (ABSENT > 0 ? ABSENT : 1);
-        out[(which == 0 ? MOM_ZR : which == 1 ? MOM_ZI : MOM_T) + d] = 0.0;
+#pragma unroll
+    for (int k = 0; k < 2 * NDET; ++k) {   // mom_zr, then mom_zi
+        const double t = wave_total_as<K>(k < NDET ? Zr[k % NDET] : Zi[k % NDET], k);
+        if (lane == 0) out[k] = t;
     }
 }
 
 // MIXED: FP64 phase and argument reduction, FP32 sin/cos, complex products and
 // per-lane partial sums (flushed into FP64 once per block), FP64 basis moments.
-template <int NDET>
+// GRAD = false keeps only Z (the value needs no more).
+template <int NDET, bool GRAD = true>
 struct MixedAcc {
     float pr[NDET], pim[NDET];
     double Zr[NDET], Zi[NDET], T[NDET], G[NCOEF];
@@ -224,14 +257,23 @@ struct MixedAcc {
             const float si = fmaf(x.u[d].y, cs, -x.u[d].x * sn);
             zr[d] = first ? sr : zr[d] + sr;
             zi[d] = first ? si : zi[d] + si;
-            const float q = fmaf(pr[d], si, pim[d] * sr);
-            psib = (d == 0) ? q : psib + q;
-            tq[d] = first ? q * ff : fmaf(q, ff, tq[d]);
+            if (GRAD) {
+                const float q = fmaf(pr[d], si, pim[d] * sr);
+                psib = (d == 0) ? q : psib + q;
+                tq[d] = first ? q * ff : fmaf(q, ff, tq[d]);
+            }
         }
+        if (!GRAD) return;
         const double pb = (double)psib;
         G[0] += pb;
 #pragma unroll
         for (int b = 0; b < NBASIS; ++b) G[1 + b] = fma(pb, B[b], G[1 + b]);
+    }
+
+    // Block start with zeros instead of the first bin (the same sums).
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int d = 0; d < NDET; ++d) { zr[d] = 0.f; zi[d] = 0.f; tq[d] = 0.f; }
     }
 
     // Block end: the block's FP32 partials into the FP64 sums (the next block's
@@ -239,31 +281,34 @@ struct MixedAcc {
     __device__ __forceinline__ void flush() {
 #pragma unroll
         for (int d = 0; d < NDET; ++d) {
-            Zr[d] += zr[d]; Zi[d] += zi[d]; T[d] += tq[d];
+            Zr[d] += zr[d]; Zi[d] += zi[d];
+            if (GRAD) T[d] += tq[d];
         }
     }
 };
 
-template <int NDET>
+template <int NDET, bool GRAD = true>
 __device__ __forceinline__ void bins_mixed_wave(const DevEvent* __restrict__ ev, const BinCoef& k, int blk0,
                                                 int blk_step, double* mom) {
     const int npad = __builtin_amdgcn_readfirstlane(ev->n_pad);
-    MixedAcc<NDET> A;
+    MixedAcc<NDET, GRAD> A;
 #pragma unroll
     for (int d = 0; d < NDET; ++d) {
-        A.pr[d] = (float)k.pr[d]; A.pim[d] = (float)k.pi[d];
+        A.pr[d] = uniform_f((float)k.pr[d]); A.pim[d] = uniform_f((float)k.pi[d]);
         A.Zr[d] = 0.0; A.Zi[d] = 0.0; A.T[d] = 0.0;
     }
 #pragma unroll
     for (int b = 0; b < NCOEF; ++b) A.G[b] = 0.0;
     const TableView t{raw_rsrc(ev->fwl, (size_t)NROWS * npad * sizeof(double)),
-                      raw_rsrc(ev->u32, (size_t)NDET * npad * sizeof(float2)), npad};
-    bin_loop<BinPair<NDET, float2>>(A, k, t, blk0, blk_step, npad / TABLE_PAD);
-    store_moments<NDET>(A.Zr, A.Zi, A.T, A.G, mom);
+                      raw_rsrc(ev->u32, (size_t)NDET * npad * sizeof(float2)), npad,
+                      (__builtin_amdgcn_readfirstlane(ev->n_bins) + CHUNK_BINS - 1) / CHUNK_BINS};
+    bin_loop<BinPair<NDET, float2>>(A, k, t, blk0, blk_step);
+    if (GRAD) store_moments<NDET>(A.Zr, A.Zi, A.T, A.G, mom);
+    else store_values<NDET>(A.Zr, A.Zi, mom);
 }
 
 // PLAIN_FP64: the same algebra in FP64 throughout.
-template <int NDET>
+template <int NDET, bool GRAD = true>
 struct Fp64Acc {
     double Zr[NDET], Zi[NDET], T[NDET], G[NCOEF];
 
@@ -284,31 +329,50 @@ struct Fp64Acc {
             const double si = fma(x.u[d].y, cs, -x.u[d].x * sn);
             Zr[d] += sr;
             Zi[d] += si;
-            const double q = fma(k.pr[d], si, k.pi[d] * sr);
-            psib = (d == 0) ? q : psib + q;
-            T[d] = fma(q, x.f, T[d]);
+            if (GRAD) {
+                const double q = fma(k.pr[d], si, k.pi[d] * sr);
+                psib = (d == 0) ? q : psib + q;
+                T[d] = fma(q, x.f, T[d]);
+            }
         }
+        if (!GRAD) return;
         G[0] += psib;
 #pragma unroll
         for (int b = 0; b < NBASIS; ++b) G[1 + b] = fma(psib, B[b], G[1 + b]);
     }
 
+    __device__ __forceinline__ void clear() {}
     __device__ __forceinline__ void flush() {}
 };
 
-template <int NDET>
+template <int NDET, bool GRAD = true>
 __device__ __forceinline__ void bins_fp64_wave(const DevEvent* __restrict__ ev, const BinCoef& k, int blk0,
                                                int blk_step, double* mom) {
     const int npad = __builtin_amdgcn_readfirstlane(ev->n_pad);
-    Fp64Acc<NDET> A;
+    Fp64Acc<NDET, GRAD> A;
 #pragma unroll
     for (int d = 0; d < NDET; ++d) { A.Zr[d] = 0.0; A.Zi[d] = 0.0; A.T[d] = 0.0; }
 #pragma unroll
     for (int b = 0; b < NCOEF; ++b) A.G[b] = 0.0;
     const TableView t{raw_rsrc(ev->fwl, (size_t)NROWS * npad * sizeof(double)),
-                      raw_rsrc(ev->u64, (size_t)NDET * npad * sizeof(double2)), npad};
-    bin_loop<BinPair<NDET, double2>>(A, k, t, blk0, blk_step, npad / TABLE_PAD);
-    store_moments<NDET>(A.Zr, A.Zi, A.T, A.G, mom);
+                      raw_rsrc(ev->u64, (size_t)NDET * npad * sizeof(double2)), npad,
+                      (__builtin_amdgcn_readfirstlane(ev->n_bins) + CHUNK_BINS - 1) / CHUNK_BINS};
+    bin_loop<BinPair<NDET, double2>>(A, k, t, blk0, blk_step);
+    if (GRAD) store_moments<NDET>(A.Zr, A.Zi, A.T, A.G, mom);
+    else store_values<NDET>(A.Zr, A.Zi, mom);
+}
+
+// logL from the Z moments alone (the sum of finish_particle, term by term).
+__device__ __forceinline__ double finish_value(const DevEvent& ev, const double* c, const double* m) {
+    double ll = -0.5 * ev.dd;
+    const double amp = c[CB_AMP];
+    for (int d = 0; d < ev.n_det; ++d) {
+        const double pr = c[CB_PR + d] * amp, pi = c[CB_PI + d] * amp;
+        const double re = pr * m[mom_zr(ev.n_det, d)] - pi * m[mom_zi(ev.n_det, d)];
+        const double p2 = pr * pr + pi * pi;
+        ll += re - 0.5 * p2 * ev.hnorm[d];
+    }
+    return ll;
 }
 
 // logL and its gradient with respect to the 11 source parameters from the
@@ -322,7 +386,7 @@ __device__ __forceinline__ double finish_particle(const DevEvent& ev, const doub
     for (int k = 0; k < NPAR; ++k) g[k] = 0.0;
     for (int d = 0; d < ev.n_det; ++d) {
         const double pr = c[CB_PR + d] * amp, pi = c[CB_PI + d] * amp;
-        const double zr = m[MOM_ZR + d], zi = m[MOM_ZI + d], h = ev.hnorm[d];
+        const double zr = m[mom_zr(ev.n_det, d)], zi = m[mom_zi(ev.n_det, d)], h = ev.hnorm[d];
         const double re = pr * zr - pi * zi;
         const double p2 = pr * pr + pi * pi;
         ll += re - 0.5 * p2 * h;
@@ -330,7 +394,7 @@ __device__ __forceinline__ double finish_particle(const DevEvent& ev, const doub
         const double ar = zr - h * pr, ai = -zi - h * pi;   // dlogL / d(Re P', Im P')
 #pragma unroll
         for (int k = 0; k < 4; ++k) gp[k] += amp * (ar * c[CB_DPR + 4 * d + k] + ai * c[CB_DPI + 4 * d + k]);
-        const double t = m[MOM_T + d];
+        const double t = m[mom_t(ev.n_det, d)];
         sum_t += t;
         g[P_RA] += TWO_PI * t * c[CB_DTAU + 2 * d];
         g[P_DEC] += TWO_PI * t * c[CB_DTAU + 2 * d + 1];
@@ -338,7 +402,7 @@ __device__ __forceinline__ double finish_particle(const DevEvent& ev, const doub
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         double s = 0.0;
-        for (int b = 0; b < NCOEF; ++b) s += c[CB_DC + 4 * b + k] * m[MOM_G + b];
+        for (int b = 0; b < NCOEF; ++b) s += c[CB_DC + 4 * b + k] * m[mom_g(ev.n_det, b)];
         g[k] = TWO_PI * s;   // Mc, q, chi1, chi2 through the phase
     }
     g[P_MC] += dlnca * c[CB_DLNCA_MC];
@@ -348,7 +412,7 @@ __device__ __forceinline__ double finish_particle(const DevEvent& ev, const doub
     g[P_RA] += gp[2];
     g[P_DEC] += gp[3];
     g[P_TC] = TWO_PI * sum_t;
-    g[P_PHIC] = -m[MOM_G + 0];
+    g[P_PHIC] = -m[mom_g(ev.n_det, 0)];
     return ll;
 }
 

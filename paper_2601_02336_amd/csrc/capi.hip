@@ -66,20 +66,15 @@ int ctx_reserve(smcgw_ctx* c, int P) {
 int ctx_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
                 int precision) {
     if (c->events.empty()) return SMCGW_ERR_NOT_INIT;
-    int rc = ctx_reserve(c, P);
-    if (rc) return rc;
-    {
-        TimedLaunch t(c, SMCGW_KERNEL_PREP);
-        if (launch_prep(c->d_events, (int)c->events.size(), ev_of_p, c->pmap, P, theta, c->d_cb, c->stream) != hipSuccess)
-            return SMCGW_ERR_HIP;
+    if (lengths_differ(c, ev_of_p) && P > c->sort_cap) {
+        const int cap = std::max(P, std::max(2 * c->sort_cap, 256));
+        (void)hipFree(c->d_sort);
+        c->d_sort = nullptr;
+        c->sort_cap = 0;
+        if (hipMalloc(&c->d_sort, (size_t)cap * sizeof(int32_t)) != hipSuccess) return SMCGW_ERR_OOM;
+        c->sort_cap = cap;
     }
-    {
-        TimedLaunch t(c, SMCGW_KERNEL_BINS);
-        if (launch_bins(c->d_events, (int)c->events.size(), ev_of_p, c->pmap, P, c->n_det, precision, c->d_cb, logl,
-                        grad, c->stream) != hipSuccess)
-            return SMCGW_ERR_HIP;
-    }
-    return SMCGW_OK;
+    return queue_loglike(c, P, ev_of_p, theta, logl, grad, precision, c->d_sort);
 }
 
 }  // namespace smcgw
@@ -119,6 +114,7 @@ extern "C" int smcgw_destroy(smcgw_ctx* c) {
     (void)hipFree(c->d_events);
     (void)hipFree(c->d_small);
     (void)hipFree(c->d_cb);
+    (void)hipFree(c->d_sort);
     (void)hipFree(c->d_tan);
     c->sweep_free();
     c->sampler_free();

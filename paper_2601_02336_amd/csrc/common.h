@@ -67,8 +67,8 @@ __device__ __forceinline__ double wave_total(double v) {
     return v;
 }
 
-// Wavefront totals of K per-lane values, written to out[idx[k]] (any address
-// space) by lanes 0..7.  Three halving steps over lane bits 0-2 scatter the
+// Wavefront totals of K per-lane values, entry k written to out[k stride] (any
+// address space) by lanes 0..7.  Three halving steps over lane bits 0-2 scatter the
 // values: at each step a lane keeps one half of its list (by its lane bit) and
 // adds the partner lane's copy of that half, the partner being the lane with the
 // opposite bit and the same lower bits (xor 1, xor 2, a rotation by 4 inside
@@ -81,7 +81,7 @@ __device__ __forceinline__ double wave_total(double v) {
 // 7 (K/2 + K/4 + K/8) + 9 K/8 instructions instead of 18 K for K separate
 // wavefront sums.
 template <int K>
-__device__ __forceinline__ void wave_totals_to(const double (&v)[K], const int (&idx)[K], double* out) {
+__device__ __forceinline__ void wave_totals_to(const double (&v)[K], double* out, int stride = 1) {
     constexpr int M1 = (K + 1) / 2, M2 = (M1 + 1) / 2, M3 = (M2 + 1) / 2;
     const int lane = threadIdx.x & 63;
     const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
@@ -111,15 +111,31 @@ __device__ __forceinline__ void wave_totals_to(const double (&v)[K], const int (
         t += __shfl_xor(t, 32, 64);
         c3[k] = t;
     }
+    // entry k of the lane's list is entry (its bits' offsets) + k of the whole
+    // one: one base per lane, no lookup per entry
     if (lane < 8) {
+        const int p2 = b2 ? M3 : 0, p1 = p2 + (b1 ? M2 : 0), p0 = p1 + (b0 ? M1 : 0);
 #pragma unroll
-        for (int k = 0; k < M3; ++k) {
-            const int p2 = b2 ? k + M3 : k;
-            const int p1 = b1 ? p2 + M2 : p2;
-            const int p0 = b0 ? p1 + M1 : p1;
-            if (p2 < M2 && p1 < M1 && p0 < K) out[idx[p0]] = c3[k];
-        }
+        for (int k = 0; k < M3; ++k)
+            if (p2 + k < M2 && p1 + k < M1 && p0 + k < K) out[(p0 + k) * stride] = c3[k];
     }
+}
+
+// Total of one value over the lanes, valid in every lane, added in the order
+// wave_totals_to<K> adds entry k of its list.  That order depends on the entry
+// only where the quads of a row of 16 are paired: entries that end up on lanes
+// with bit 2 clear pair quads (0, 3) and (1, 2), the others (0, 1) and (2, 3).
+template <int K>
+__device__ __forceinline__ double wave_total_as(double v, int k) {
+    constexpr int M1 = (K + 1) / 2, M2 = (M1 + 1) / 2, M3 = (M2 + 1) / 2;
+    const int p1 = k % M1, p2 = p1 % M2;
+    v += dpp_move<0xb1>(v);   // quad_perm [1,0,3,2]
+    v += dpp_move<0x4e>(v);   // quad_perm [2,3,0,1]
+    v += p2 < M3 ? dpp_move<0x140>(v) : dpp_move<0x141>(v);   // row_mirror / row_half_mirror
+    v += dpp_move<0x128>(v);  // row_ror:8
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    return v;
 }
 
 __device__ __forceinline__ double wave_max_total(double v) {
@@ -181,15 +197,16 @@ enum {
 };
 static_assert(CB_AMP < CB_SIZE, "coefficient block overflow");
 
-// Per-particle bin moments written by the bin loop (FP64).
-enum {
-    MOM_ZR = 0,                 // MAXDET: Re Z_d = Re sum_j u_dj e^{-2 pi i Phi_dj}
-    MOM_ZI = MOM_ZR + MAXDET,   // MAXDET: Im Z_d
-    MOM_G = MOM_ZI + MAXDET,    // NCOEF: sum_j psibar_j B_b(f_j) (b = const first)
-    MOM_T = MOM_G + NCOEF,      // MAXDET: sum_j q_dj f_j
-    MOM_SIZE = 24
-};
-static_assert(MOM_T + MAXDET <= MOM_SIZE, "moment block overflow");
+// Per-particle bin moments written by the bin loop (FP64), for n detectors, in
+// the order in which store_moments reduces them:
+//   Re Z_d, Im Z_d (d < n; Z_d = sum_j u_dj e^{-2 pi i Phi_dj}), T_d = sum_j q_dj f_j,
+//   then NCOEF basis sums G_b = sum_j psibar_j B_b(f_j), the constant first.
+__device__ constexpr int mom_zr(int, int d) { return d; }
+__device__ constexpr int mom_zi(int n, int d) { return n + d; }
+__device__ constexpr int mom_t(int n, int d) { return 2 * n + d; }
+__device__ constexpr int mom_g(int n, int b) { return 3 * n + b; }
+constexpr int MOM_SIZE = 24;
+static_assert(mom_g(MAXDET, NCOEF) <= MOM_SIZE, "moment block overflow");
 
 // Event index of particle p (out-of-range indices are clamped to a valid event).
 __device__ __forceinline__ int event_index(const int32_t* ev_of_p, int p, int n_events) {
@@ -210,9 +227,20 @@ hipError_t launch_build_tables(const double* d_data, const double* d_psd, int n_
                                double* wa2, double* sums, hipStream_t s);
 hipError_t launch_prep(const DevEvent* d_events, int n_events, const int32_t* ev_of_p, const ParamMap& pm, int P,
                        const double* theta, double* cb, hipStream_t s);
-// The bin loop and the epilogue of every particle: logl [P] and grad [P][pm.dim] (grad may be NULL).
-hipError_t launch_bins(const DevEvent* d_events, int n_events, const int32_t* ev_of_p, const ParamMap& pm, int P,
-                       int n_det, int precision, const double* cb, double* logl, double* grad, hipStream_t s);
+// One batched likelihood launch: logl [P] and grad [P][pm.dim] (NULL: values
+// only) of theta [P][pm.dim]; order [P] (NULL: index order) is the start order,
+// longest the largest n_pad among the events.
+struct LoglikeCall {
+    const DevEvent* events;
+    int n_events;
+    const int32_t* ev_of_p;
+    const int32_t* order;
+    ParamMap pm;
+    int P, longest;
+    const double* theta;
+    double *logl, *grad;
+};
+hipError_t launch_loglike(const LoglikeCall& a, int n_det, int precision, hipStream_t s);
 hipError_t launch_waveform(const DevEvent* d_events, int event_id, const double* cb, double* h_reim, int n_bins,
                            int n_det, hipStream_t s);
 int noalloc_init(int device);   // the fixed scratch of smcgw_loglike_grad_noalloc on this device

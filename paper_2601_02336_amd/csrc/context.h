@@ -35,6 +35,8 @@ struct smcgw_ctx {
     // likelihood scratch, sized for `cap` particles
     double* d_cb = nullptr;
     int cap = 0;
+    int32_t* d_sort = nullptr;             // start order of a batch over events of different lengths
+    int sort_cap = 0;
     double* d_tan = nullptr;               // tangent moment blocks of the plain form, [tan_cap][12]
     int tan_cap = 0;
     // sampler state
@@ -130,6 +132,9 @@ int tangent_reserve(smcgw_ctx* c, int P);
 int queue_loglike_tangent(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, const uint8_t* active,
                           double* logl, double* grad);
 bool tangent_supported(const smcgw_ctx* c);
+bool lengths_differ(const smcgw_ctx* c, const int32_t* ev_of_p);
+int queue_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
+                  int precision, int32_t* order);
 int ctx_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
                 int precision);
 }  // namespace smcgw

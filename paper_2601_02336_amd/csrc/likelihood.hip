@@ -13,12 +13,19 @@
 // prologue's Jacobians.
 //
 // Kernels:
-//   prep (eight lanes per particle): coefficient block, FP64 dual numbers with
-//        one tangent per lane.
-//   bins (one wavefront per particle): lanes stride the frequency bins, the
-//        shared per-bin tables are read coalesced and each lane keeps its own
-//        partial sums; a wavefront shuffle tree reduces them in FP64 into LDS,
-//        and lane 0 forms logL and the gradient from them (FP64).
+//   bins (one wavefront per particle): the workgroup builds the coefficient
+//        blocks of its particles in LDS (eight lanes per particle, FP64 dual
+//        numbers with one tangent per lane), then each wavefront walks the bins
+//        of its particles (lanes stride the frequency bins, the shared per-bin
+//        tables are read coalesced, each lane keeps its own partial sums) and one
+//        lane per particle forms logL and the gradient from the moments.
+//   prep: the coefficient blocks alone, in global memory, for the plain
+//        comparison form and the waveform.
+//   sort_events: start order of a batch over events of different lengths.
+#include <algorithm>
+#include <functional>
+#include <vector>
+
 #include "binloop.h"
 #include "coeffs.h"
 #include "common.h"
@@ -26,97 +33,197 @@
 
 namespace smcgw {
 
-constexpr int BINS_WAVES = 4;   // wavefronts (particles) per workgroup
+constexpr int LL_WAVES = 4;   // wavefronts per workgroup
 
 // Eight lanes per particle, as the persistent NUTS kernel splits a leaf's
 // prologue: lanes 0-3 carry one intrinsic tangent each (Mc, q, chi1, chi2)
 // while lanes 4-7 take the sines and cosines of the four extrinsic angles;
 // then lane 4k + d (k = 0, 1) builds detector d with its ra (k = 0) or dec
 // (k = 1) tangent, and lane 0 the amplitude.  One particle's chain is a
-// quarter of the one-lane prologue's.
+// quarter of the one-lane prologue's.  Called by every thread of the
+// workgroup (it holds a barrier); ang is the particle's exchange of the angles.
 constexpr int PREP_LANES = 8;
 constexpr int PREP_PER_BLOCK = 256 / PREP_LANES;
 static_assert(2 * MAXDET == PREP_LANES && ANG_COUNT == PREP_LANES - 4, "prologue lane split");
 
-__global__ __launch_bounds__(256) void prep_kernel(const DevEvent* __restrict__ evs, int n_events,
-                                                   const int32_t* __restrict__ ev_of_p, ParamMap pm, int P,
-                                                   const double* __restrict__ theta, double* __restrict__ cb) {
-    __shared__ double ang_sh[PREP_PER_BLOCK][ANG_COUNT][2];
-    const int g = threadIdx.x / PREP_LANES, j = threadIdx.x % PREP_LANES;
-    const int p = blockIdx.x * PREP_PER_BLOCK + g;
-    const bool live = p < P;
+__device__ __forceinline__ void prologue_lanes(const DevEvent& ev, const ParamMap& pm, const double* __restrict__ x,
+                                               double* c, double (*ang_sh)[2], int j, bool live) {
     double th[NPAR];
-    const DevEvent& ev = evs[event_index(ev_of_p, live ? p : 0, n_events)];
-    double* c = cb + (size_t)(live ? p : 0) * CB_SIZE;
     if (live) {
-        expand_params(pm, theta + (size_t)p * pm.dim, th);
+        expand_params(pm, x, th);
         if (j < 4) {
             prep_intrinsic_n<1>(ev, th, c, j, j == 0);
         } else {
             double sn, cs;
             sincos(extrinsic_angle(ev, th, j - 4), &sn, &cs);
-            ang_sh[g][j - 4][0] = sn;
-            ang_sh[g][j - 4][1] = cs;
+            ang_sh[j - 4][0] = sn;
+            ang_sh[j - 4][1] = cs;
         }
     }
     __syncthreads();
     if (live) {
         ExtAngles ang;
 #pragma unroll
-        for (int k = 0; k < ANG_COUNT; ++k) { ang.sc[k][0] = ang_sh[g][k][0]; ang.sc[k][1] = ang_sh[g][k][1]; }
+        for (int k = 0; k < ANG_COUNT; ++k) { ang.sc[k][0] = ang_sh[k][0]; ang.sc[k][1] = ang_sh[k][1]; }
         const int k = j / MAXDET, d = j % MAXDET;
         prep_extrinsic_det_n<1>(ev, th, ang, c, d, k, k == 0);
         if (j == 0) prep_extrinsic_common(ev, th, c);
     }
 }
 
-// One wavefront per particle over all bins of its event, then the epilogue:
-// the wavefront's coefficient block and moments sit in LDS and lane 0 forms
-// logL and the gradient over the sampled coordinates.
-template <int NDET, int PREC>
-__device__ __forceinline__ void bins_and_finish(const DevEvent* __restrict__ evs, int n_events,
-                                                const int32_t* __restrict__ ev_of_p, const ParamMap& pm, int P,
-                                                const double* __restrict__ cb, double* __restrict__ logl,
-                                                double* __restrict__ grad) {
-    __shared__ double cb_sh[BINS_WAVES][CB_SIZE];
-    __shared__ double mom_sh[BINS_WAVES][MOM_SIZE];
+__global__ __launch_bounds__(256) void prep_kernel(const DevEvent* __restrict__ evs, int n_events,
+                                                   const int32_t* __restrict__ ev_of_p, ParamMap pm, int P,
+                                                   const double* __restrict__ theta, double* __restrict__ cb) {
+    __shared__ double ang_sh[PREP_PER_BLOCK][ANG_COUNT][2];
+    const int g = threadIdx.x / PREP_LANES;
+    const int p = blockIdx.x * PREP_PER_BLOCK + g;
+    const int q = p < P ? p : 0;
+    prologue_lanes(evs[event_index(ev_of_p, q, n_events)], pm, theta + (size_t)q * pm.dim, cb + (size_t)q * CB_SIZE,
+                   ang_sh[g], threadIdx.x % PREP_LANES, p < P);
+}
+
+// Particles [LL_WAVES per_wave blockIdx.x, ...) of the start order (order NULL:
+// index order), per_wave <= 8 for each wavefront.  Bound by the VALU issue rate
+// of the bin loop; the coefficient blocks and moments stay in LDS, so a call is
+// one launch (a prologue launch of its own cost 6 to 17 us a call: 4096 particles
+// of 3 x 8033 bins took 83.3 us with it and take 77.6 without, 6000 of a folded
+// event 25.0 and 18.0).  GRAD = false leaves the gradient's moments out; logL is
+// the same bit for bit.
+struct LoglikeShared {   // one per particle of the workgroup (dynamic LDS)
+    double cb[CB_SIZE];
+    double mom[MOM_SIZE];
+    double ang[ANG_COUNT][2];
+};
+
+template <int NDET, int PREC, bool GRAD>
+__device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ evs, int n_events,
+                                                  const int32_t* __restrict__ ev_of_p,
+                                                  const int32_t* __restrict__ order, const ParamMap& pm, int P,
+                                                  int per_wave, const double* __restrict__ theta,
+                                                  double* __restrict__ logl, double* __restrict__ grad) {
+    extern __shared__ LoglikeShared sh[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int p = blockIdx.x * BINS_WAVES + wave;
-    if (p >= P) return;   // the whole wavefront: there is no workgroup barrier below
-    const int e = __builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events));
-    for (int i = lane; i < CB_SIZE; i += 64) cb_sh[wave][i] = cb[(size_t)p * CB_SIZE + i];
+    const int first = blockIdx.x * LL_WAVES * per_wave;
+    {
+        // prologue: the workgroup's particles on consecutive groups of eight lanes
+        const int g = threadIdx.x / PREP_LANES;
+        const bool live = g < LL_WAVES * per_wave && first + g < P;
+        const int i = live ? first + g : 0, p = order ? order[i] : i;
+        LoglikeShared& s = sh[live ? g : 0];
+        prologue_lanes(evs[event_index(ev_of_p, p, n_events)], pm, theta + (size_t)p * pm.dim, s.cb, s.ang,
+                       threadIdx.x % PREP_LANES, live);
+    }
+    __syncthreads();
+    // wavefront w takes the particles w per_wave, ... of the workgroup
+    const int g0 = wave * per_wave;
+    const int n = min(per_wave, P - first - g0);
+    for (int g = g0; g < g0 + n; ++g) {
+        const int p = order ? order[first + g] : first + g;
+        const int e = __builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events));
+        const BinCoef k = load_coef(sh[g].cb);
+        if (PREC == SMCGW_MIXED)
+            bins_mixed_wave<NDET, GRAD>(evs + e, k, 0, 1, sh[g].mom);
+        else
+            bins_fp64_wave<NDET, GRAD>(evs + e, k, 0, 1, sh[g].mom);
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    const BinCoef k = load_coef(cb_sh[wave]);
-    if (PREC == SMCGW_MIXED)
-        bins_mixed_wave<NDET>(evs + e, k, 0, 1, mom_sh[wave]);
-    else
-        bins_fp64_wave<NDET>(evs + e, k, 0, 1, mom_sh[wave]);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (lane == 0) {
-        double g[NPAR];
-        logl[p] = finish_particle(evs[e], cb_sh[wave], mom_sh[wave], g);
-        if (grad)
+    if (lane < n) {
+        const LoglikeShared& s = sh[g0 + lane];
+        const int i = first + g0 + lane, p = order ? order[i] : i;
+        const DevEvent& ev = evs[event_index(ev_of_p, p, n_events)];
+        if (GRAD) {
+            double g[NPAR];
+            logl[p] = finish_particle(ev, s.cb, s.mom, g);
             for (int q = 0; q < pm.dim; ++q) grad[(size_t)p * pm.dim + q] = g[pm.idx[q]];
+        } else {
+            logl[p] = finish_value(ev, s.cb, s.mom);
+        }
     }
 }
 
-template <int NDET>
-__global__ __launch_bounds__(256) void bins_mixed_kernel(const DevEvent* __restrict__ evs, int n_events,
-                                                         const int32_t* __restrict__ ev_of_p, ParamMap pm, int P,
-                                                         const double* __restrict__ cb, double* __restrict__ logl,
-                                                         double* __restrict__ grad) {
-    bins_and_finish<NDET, SMCGW_MIXED>(evs, n_events, ev_of_p, pm, P, cb, logl, grad);
+// Wavefronts per SIMD the register budget is sized for: four (128 registers)
+// where the loop's sums fit, so that a launch of one particle per wavefront
+// keeps 4096 particles on the chip at once.
+template <int NDET, bool GRAD>
+__global__ __launch_bounds__(64 * LL_WAVES, NDET < 4 ? 4 : 3) void bins_mixed_kernel(
+    const DevEvent* __restrict__ evs, int n_events, const int32_t* __restrict__ ev_of_p,
+    const int32_t* __restrict__ order, ParamMap pm, int P, int per_wave, const double* __restrict__ theta,
+    double* __restrict__ logl, double* __restrict__ grad) {
+    loglike_workgroup<NDET, SMCGW_MIXED, GRAD>(evs, n_events, ev_of_p, order, pm, P, per_wave, theta, logl, grad);
 }
 
-template <int NDET>
-__global__ __launch_bounds__(256) void bins_fp64_kernel(const DevEvent* __restrict__ evs, int n_events,
-                                                        const int32_t* __restrict__ ev_of_p, ParamMap pm, int P,
-                                                        const double* __restrict__ cb, double* __restrict__ logl,
-                                                        double* __restrict__ grad) {
-    bins_and_finish<NDET, SMCGW_PLAIN_FP64>(evs, n_events, ev_of_p, pm, P, cb, logl, grad);
+template <int NDET, bool GRAD>
+__global__ __launch_bounds__(64 * LL_WAVES, NDET == 1 || !GRAD ? 4 : 3) void bins_fp64_kernel(
+    const DevEvent* __restrict__ evs, int n_events, const int32_t* __restrict__ ev_of_p,
+    const int32_t* __restrict__ order, ParamMap pm, int P, int per_wave, const double* __restrict__ theta,
+    double* __restrict__ logl, double* __restrict__ grad) {
+    loglike_workgroup<NDET, SMCGW_PLAIN_FP64, GRAD>(evs, n_events, ev_of_p, order, pm, P, per_wave, theta, logl, grad);
+}
+
+// Start order of a batch whose events differ in length: particles by falling
+// table length (rank[e] of event e, 0 the longest), index order inside a rank.
+// A wavefront walks one particle's bins alone, so a workgroup lasts as long as
+// its longest event: equal lengths side by side leave no wavefront waiting, and
+// with the longest first the short ones fill the end of the launch (16384
+// particles over eight events of 4017 to 64897 bins: 1523 us a call in index
+// order, 1010 sorted, the sort included).  One workgroup; wavefront w owns the
+// contiguous index range w.
+constexpr int SORT_MIN_P = 1024;   // the SIMDs of the GPU
+struct EventRanks { uint8_t rank[SMCGW_MAX_EVENTS]; };
+constexpr int SORT_THREADS = 1024;
+constexpr int SORT_WAVES = SORT_THREADS / 64;
+
+__global__ __launch_bounds__(SORT_THREADS) void sort_events_kernel(const int32_t* __restrict__ ev_of_p, int n_events,
+                                                                   EventRanks er, int P, int32_t* __restrict__ order) {
+    // counts, then running positions, of every (rank, wavefront)
+    __shared__ int pos[SMCGW_MAX_EVENTS][SORT_WAVES];
+    __shared__ int part[SORT_WAVES];
+    __shared__ uint8_t rank[SMCGW_MAX_EVENTS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(SMCGW_MAX_EVENTS * SORT_WAVES == SORT_THREADS, "one scan entry per thread");
+    (&pos[0][0])[tid] = 0;
+    if (tid < SMCGW_MAX_EVENTS) rank[tid] = er.rank[tid];
+    __syncthreads();
+    const int per = ((P + SORT_WAVES - 1) / SORT_WAVES + 63) & ~63;
+    const int i0 = min(P, wave * per), i1 = min(P, i0 + per);
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int b = i0; b < i1; b += 64) {
+            const int i = b + lane;
+            const bool in = i < i1;
+            const int r = in ? rank[event_index(ev_of_p, i, n_events)] : -1;
+            unsigned long long todo = __ballot(in);
+            while (todo) {   // one turn per rank among the 64 particles
+                const int l = __builtin_ctzll(todo);
+                const int v = __shfl(r, l, 64);
+                const unsigned long long same = __ballot(r == v);
+                const int at = pos[v][wave];   // this wavefront's entry alone
+                if (pass == 1 && r == v) order[at + __popcll(same & ((1ull << lane) - 1))] = i;
+                __builtin_amdgcn_wave_barrier();
+                if (lane == l) pos[v][wave] = at + __popcll(same);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                todo &= ~same;
+            }
+        }
+        __syncthreads();
+        if (pass == 0) {   // exclusive scan over (rank, wavefront)
+            const int c = (&pos[0][0])[tid];
+            int inc = c;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_up(inc, o);
+                if (lane >= o) inc += t;
+            }
+            if (lane == 63) part[wave] = inc;
+            __syncthreads();
+            int before = 0;
+            for (int w = 0; w < wave; ++w) before += part[w];
+            (&pos[0][0])[tid] = before + inc - c;
+            __syncthreads();
+        }
+    }
 }
 
 // Projected strain of one parameter point (FP64), h_reim [n_det][N][2].
@@ -144,16 +251,15 @@ __global__ __launch_bounds__(256) void waveform_kernel(const DevEvent* __restric
 }
 
 // ------------------------------------------------------------- fixed scratch
-// Coefficient blocks of smcgw_loglike_grad_noalloc, for at most
-// SMCGW_NOALLOC_MAX_P particles (13 MiB).  Every GPU the library runs on
-// holds its own copy until the process ends.  Host code must not pass the
-// array's name to a kernel (it is a host-side stand-in there): the device
-// address of each GPU's copy is looked up once per device at context set-up
-// and kept in noalloc_base.
-static __device__ __align__(256) double scratch[(size_t)SMCGW_NOALLOC_MAX_P * CB_SIZE];
+// Start order of smcgw_loglike_grad_noalloc, for at most SMCGW_NOALLOC_MAX_P
+// particles.  Every GPU the library runs on holds its own copy until the
+// process ends.  Host code must not pass the array's name to a kernel (it is a
+// host-side stand-in there): the device address of each GPU's copy is looked up
+// once per device at context set-up and kept in noalloc_base.
+static __device__ __align__(256) int32_t scratch[SMCGW_NOALLOC_MAX_P];
 
 constexpr int NOALLOC_DEVICES = 64;
-static double* noalloc_base[NOALLOC_DEVICES] = {};
+static int32_t* noalloc_base[NOALLOC_DEVICES] = {};
 
 // Resolves this device's scratch address (the device must be current).
 int noalloc_init(int device) {
@@ -161,7 +267,7 @@ int noalloc_init(int device) {
     if (noalloc_base[device]) return SMCGW_OK;
     void* ptr = nullptr;
     if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return SMCGW_ERR_HIP;
-    noalloc_base[device] = (double*)ptr;
+    noalloc_base[device] = (int32_t*)ptr;
     return SMCGW_OK;
 }
 
@@ -174,25 +280,42 @@ hipError_t launch_prep(const DevEvent* d_events, int n_events, const int32_t* ev
     return hipGetLastError();
 }
 
-template <int NDET>
-hipError_t launch_bins_ndet(const DevEvent* d_events, int n_events, const int32_t* ev_of_p, const ParamMap& pm,
-                            int P, int precision, const double* cb, double* logl, double* grad, hipStream_t s) {
-    const dim3 grid((P + BINS_WAVES - 1) / BINS_WAVES), block(64 * BINS_WAVES);
+// Particles per wavefront of the batched likelihood.  One keeps the most
+// wavefronts in flight, and while they do not fill the chip that is what counts:
+// on a folded event of 310 edges 700 particles take 10.7 us with one per
+// wavefront, 12.4 with two, 16.3 with four.  Once the chip is full, more of them
+// share a prologue (eight lanes each, so a wavefront's instructions serve up to
+// eight particles): 6000 particles take 23.4, 18.0 and 21.8 us, 20000 take 61.6,
+// 44.7 and 39.9.  On events of more than SHORT_BINS bins the prologue is a few
+// per cent of a wavefront's work and one per wavefront stays.
+constexpr int SHORT_BINS = 4 * TABLE_PAD;
+int per_wave_of(int P, int longest) {
+    if (longest > SHORT_BINS) return 1;
+    return P >= 16384 ? 4 : P >= 2048 ? 2 : 1;
+}
+
+template <int NDET, bool GRAD>
+hipError_t launch_loglike_ndet(const LoglikeCall& a, int precision, hipStream_t s) {
+    const int per_wave = per_wave_of(a.P, a.longest);
+    const int n = LL_WAVES * per_wave;
+    const dim3 grid((a.P + n - 1) / n), block(64 * LL_WAVES);
+    const size_t lds = n * sizeof(LoglikeShared);
     if (precision == SMCGW_MIXED)
-        hipLaunchKernelGGL(bins_mixed_kernel<NDET>, grid, block, 0, s, d_events, n_events, ev_of_p, pm, P, cb, logl, grad);
+        hipLaunchKernelGGL((bins_mixed_kernel<NDET, GRAD>), grid, block, lds, s, a.events, a.n_events,
+                           a.ev_of_p, a.order, a.pm, a.P, per_wave, a.theta, a.logl, a.grad);
     else
-        hipLaunchKernelGGL(bins_fp64_kernel<NDET>, grid, block, 0, s, d_events, n_events, ev_of_p, pm, P, cb, logl, grad);
+        hipLaunchKernelGGL((bins_fp64_kernel<NDET, GRAD>), grid, block, lds, s, a.events, a.n_events,
+                           a.ev_of_p, a.order, a.pm, a.P, per_wave, a.theta, a.logl, a.grad);
     return hipGetLastError();
 }
 
-hipError_t launch_bins(const DevEvent* d_events, int n_events, const int32_t* ev_of_p, const ParamMap& pm, int P,
-                       int n_det, int precision, const double* cb, double* logl, double* grad, hipStream_t s) {
-    if (P <= 0) return hipSuccess;
+hipError_t launch_loglike(const LoglikeCall& a, int n_det, int precision, hipStream_t s) {
+    if (a.P <= 0) return hipSuccess;
     switch (n_det) {
-    case 1: return launch_bins_ndet<1>(d_events, n_events, ev_of_p, pm, P, precision, cb, logl, grad, s);
-    case 2: return launch_bins_ndet<2>(d_events, n_events, ev_of_p, pm, P, precision, cb, logl, grad, s);
-    case 3: return launch_bins_ndet<3>(d_events, n_events, ev_of_p, pm, P, precision, cb, logl, grad, s);
-    case 4: return launch_bins_ndet<4>(d_events, n_events, ev_of_p, pm, P, precision, cb, logl, grad, s);
+    case 1: return a.grad ? launch_loglike_ndet<1, true>(a, precision, s) : launch_loglike_ndet<1, false>(a, precision, s);
+    case 2: return a.grad ? launch_loglike_ndet<2, true>(a, precision, s) : launch_loglike_ndet<2, false>(a, precision, s);
+    case 3: return a.grad ? launch_loglike_ndet<3, true>(a, precision, s) : launch_loglike_ndet<3, false>(a, precision, s);
+    case 4: return a.grad ? launch_loglike_ndet<4, true>(a, precision, s) : launch_loglike_ndet<4, false>(a, precision, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -208,9 +331,43 @@ hipError_t launch_waveform(const DevEvent* d_events, int event_id, const double*
 
 using namespace smcgw;
 
-// The batched likelihood of smcgw_loglike_grad with its per-particle coefficient
-// blocks in the fixed scratch array: no allocation, no event, no host
-// synchronisation.
+namespace smcgw {
+// A batch spans events of different table lengths.
+bool lengths_differ(const smcgw_ctx* c, const int32_t* ev_of_p) {
+    if (!ev_of_p) return false;
+    for (const DevEvent& e : c->events)
+        if (e.n_pad != c->events[0].n_pad) return true;
+    return false;
+}
+
+// The batched likelihood on the context's stream; order: scratch for P start
+// positions (used only when the events differ in length).
+int queue_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
+                  int precision, int32_t* order) {
+    LoglikeCall a{c->d_events, (int)c->events.size(), ev_of_p, nullptr, c->pmap, P, 0, theta, logl, grad};
+    for (const DevEvent& e : c->events) a.longest = std::max(a.longest, e.n_pad);
+    // up to one wavefront per SIMD they all start at once, and an order changes nothing
+    if (P > SORT_MIN_P && lengths_differ(c, ev_of_p)) {
+        std::vector<int> len;
+        for (const DevEvent& e : c->events) len.push_back(e.n_pad);
+        std::sort(len.begin(), len.end(), std::greater<int>());
+        len.erase(std::unique(len.begin(), len.end()), len.end());
+        EventRanks er{};
+        for (size_t e = 0; e < c->events.size(); ++e)
+            er.rank[e] = (uint8_t)(std::find(len.begin(), len.end(), c->events[e].n_pad) - len.begin());
+        TimedLaunch t(c, SMCGW_KERNEL_PREP);
+        hipLaunchKernelGGL(sort_events_kernel, dim3(1), dim3(SORT_THREADS), 0, c->stream, ev_of_p, a.n_events, er, P,
+                           order);
+        if (hipGetLastError() != hipSuccess) return SMCGW_ERR_HIP;
+        a.order = order;
+    }
+    TimedLaunch t(c, SMCGW_KERNEL_BINS);
+    return launch_loglike(a, c->n_det, precision, c->stream) == hipSuccess ? SMCGW_OK : SMCGW_ERR_HIP;
+}
+}  // namespace smcgw
+
+// The batched likelihood of smcgw_loglike_grad with its start order in the
+// fixed scratch array: no allocation, no event, no host synchronisation.
 extern "C" int smcgw_loglike_grad_noalloc(smcgw_ctx* c, int P, const int32_t* event_of_particle, const double* theta,
                                           double* logl, double* grad, int precision) {
     if (!c || P < 0 || (P > 0 && (!theta || !logl))) return SMCGW_ERR_INVALID;
@@ -220,11 +377,5 @@ extern "C" int smcgw_loglike_grad_noalloc(smcgw_ctx* c, int P, const int32_t* ev
     if (P == 0) return SMCGW_OK;
     if (c->device < 0 || c->device >= NOALLOC_DEVICES || !noalloc_base[c->device]) return SMCGW_ERR_NOT_INIT;
     if (hipSetDevice(c->device) != hipSuccess) return SMCGW_ERR_HIP;
-    double* cb = noalloc_base[c->device];
-    const int ne = (int)c->events.size();
-    if (launch_prep(c->d_events, ne, event_of_particle, c->pmap, P, theta, cb, c->stream) != hipSuccess ||
-        launch_bins(c->d_events, ne, event_of_particle, c->pmap, P, c->n_det, precision, cb, logl, grad,
-                    c->stream) != hipSuccess)
-        return SMCGW_ERR_HIP;
-    return SMCGW_OK;
+    return queue_loglike(c, P, event_of_particle, theta, logl, grad, precision, noalloc_base[c->device]);
 }

@@ -654,7 +654,7 @@ constexpr int FIN_LL_LANE = NPAR;
 template <int NDET, int WAVES>
 __device__ __noinline__ void leaf_finish(const DevEvent* ev, NutsShared& S, NutsState& T, int D, int lane) {
     // wavefront totals of the moments, in wavefront order, into S.mom[0]
-    if (lane < MOM_SIZE) {
+    if (lane < mom_g(NDET, NCOEF)) {
         double s = S.mom[0][lane];
 #pragma unroll
         for (int w = 1; w < WAVES; ++w) s += S.mom[w][lane];
@@ -667,13 +667,13 @@ __device__ __noinline__ void leaf_finish(const DevEvent* ev, NutsShared& S, Nuts
     if (lane < 4) {
         double s = 0.0;
 #pragma unroll
-        for (int b = 0; b < NCOEF; ++b) s += c[CB_DC + 4 * b + lane] * m[MOM_G + b];
+        for (int b = 0; b < NCOEF; ++b) s += c[CB_DC + 4 * b + lane] * m[mom_g(NDET, b)];
         S.fin_phase[lane] = TWO_PI * s;
     } else if (lane < 4 + NDET) {
         const int d = lane - 4;
         const double amp = c[CB_AMP];
         const double pr = c[CB_PR + d] * amp, pi = c[CB_PI + d] * amp;
-        const double zr = m[MOM_ZR + d], zi = m[MOM_ZI + d], h = ev->hnorm[d];
+        const double zr = m[mom_zr(NDET, d)], zi = m[mom_zi(NDET, d)], h = ev->hnorm[d];
         const double re = pr * zr - pi * zi;
         const double p2 = pr * pr + pi * pi;
         double* o = S.fin_det[d];
@@ -682,7 +682,7 @@ __device__ __noinline__ void leaf_finish(const DevEvent* ev, NutsShared& S, Nuts
         const double ar = zr - h * pr, ai = -zi - h * pi;   // dlogL / d(Re P', Im P')
 #pragma unroll
         for (int k = 0; k < 4; ++k) o[FD_GP + k] = amp * (ar * c[CB_DPR + 4 * d + k] + ai * c[CB_DPI + 4 * d + k]);
-        const double t = m[MOM_T + d];
+        const double t = m[mom_t(NDET, d)];
         o[FD_T] = t;
         o[FD_RA] = TWO_PI * t * c[CB_DTAU + 2 * d];
         o[FD_DEC] = TWO_PI * t * c[CB_DTAU + 2 * d + 1];
@@ -717,7 +717,7 @@ __device__ __noinline__ void leaf_finish(const DevEvent* ev, NutsShared& S, Nuts
     v = lane == P_RA ? g_ra : v;
     v = lane == P_DEC ? g_dec : v;
     v = lane == P_TC ? g_tc : v;
-    v = lane == P_PHIC ? -m[MOM_G + 0] : v;
+    v = lane == P_PHIC ? -m[mom_g(NDET, 0)] : v;
     if (lane <= FIN_LL_LANE) S.fin_g[lane] = v;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();

@@ -134,12 +134,10 @@ __global__ __launch_bounds__(64 * TAN_WAVES) void bins_tangent_kernel(const DevE
         }
     }
     double v[TD];
-    int idx[TD];
     v[0] = acc.v;
-    idx[0] = 0;
 #pragma unroll
-    for (int k = 0; k < NT; ++k) { v[1 + k] = acc.d[k]; idx[1 + k] = 1 + k; }
-    wave_totals_to<TD>(v, idx, mom + (size_t)p * TD);
+    for (int k = 0; k < NT; ++k) v[1 + k] = acc.d[k];
+    wave_totals_to<TD>(v, mom + (size_t)p * TD);
 }
 
 // logL = -<d|d>/2 + the bin sum; the gradient over the sampled coordinates.

@@ -40,10 +40,7 @@ constexpr double SKIP_NONE = 0.0, SKIP_DONE = 1.0, SKIP_STALL = 2.0;
 template <int K>
 __device__ __forceinline__ void block_sums(double (&v)[K], double* red, double* tot) {
     const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    int idx[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) idx[k] = k * nw;
-    wave_totals_to<K>(v, idx, red + wave);
+    wave_totals_to<K>(v, red + wave, nw);
     __syncthreads();
     if ((int)threadIdx.x < K) {
         double s = 0.0;

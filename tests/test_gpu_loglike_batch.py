@@ -1,0 +1,89 @@
+"""The batched likelihood kernel at the edges of its launch: partial workgroups and wavefronts, several particles
+per wavefront, tables whose last block holds one to four chunks of bins, values without gradients, and batches
+over events of different lengths."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_02336_amd import synth
+from oracle import oracle as O
+
+from helpers import TOL, event, grad_err, logl_rel_err, widths
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def smc():
+    from paper_2601_02336_amd import smcgw
+    return smcgw
+
+
+def _spec(n, n_det, seed):
+    return synth.EventSpec(20.0, 20.0 + (n - 1) * 0.5, 0.5, n_det, 20.0, seed)
+
+
+@pytest.mark.parametrize("n_det", [1, 2, 3])
+@pytest.mark.parametrize("n", [100, 128, 129, 257, 384, 385, 512, 513, 1153])
+def test_last_block(smc, n, n_det):
+    """The last block's chunks (one to four of 128 bins; also the only block, and a full one), with and without the
+    gradient, against the oracle; the value does not depend on whether the gradient is asked for."""
+    ev = event(_spec(n, n_det, 40 + n))
+    b = synth.gw_prior_for(ev)
+    x = synth.prior_draw(np.random.default_rng(n), 9, b)
+    ll_ref, g_ref = O.loglike_grad(O.gw_target(ev), x)
+    c = smc.Context(0)
+    c.add_event(ev)
+    xt = torch.tensor(x, device="cuda")
+    for name, prec in (("plain", smc.PLAIN_FP64), ("mixed", smc.MIXED)):
+        ll, g = c.loglike_grad(xt, precision=prec)
+        value = c.loglike_grad(xt, want_grad=False, precision=prec)
+        assert logl_rel_err(ll.cpu().numpy(), ll_ref) <= TOL[name]["logl"]
+        assert grad_err(g.cpu().numpy(), g_ref, widths(b)) <= TOL[name]["grad"]
+        assert torch.equal(value, ll)
+    c.close()
+
+
+@pytest.mark.parametrize("n", [310, 3000])
+def test_batch_size_changes_nothing(smc, n):
+    """A particle's value and gradient are the same bits in every batch: one particle up to several per wavefront,
+    full and partial workgroups."""
+    ev = event(_spec(n, 3, 50))
+    x = torch.tensor(synth.prior_draw(np.random.default_rng(1), 16400, synth.gw_prior_for(ev)), device="cuda")
+    c = smc.Context(0)
+    c.add_event(ev)
+    ll, g = c.loglike_grad(x)
+    for P in (1, 3, 4, 5, 31, 2047, 2048, 2049, 16383, 16384):
+        a, b = c.loglike_grad(x[:P].contiguous())
+        assert torch.equal(a, ll[:P]) and torch.equal(b, g[:P]), P
+    pick = np.array([0, 1, 2047, 16399])
+    ll_ref, g_ref = O.loglike_grad(O.gw_target(ev), x[pick].cpu().numpy())
+    assert logl_rel_err(ll[pick].cpu().numpy(), ll_ref) <= TOL["mixed"]["logl"]
+    assert grad_err(g[pick].cpu().numpy(), g_ref, widths(synth.gw_prior_for(ev))) <= TOL["mixed"]["grad"]
+    c.close()
+
+
+@pytest.mark.parametrize("P", [1, 63, 65, 1000, 5003])
+def test_events_of_different_lengths(smc, P):
+    """A batch over four events of three lengths in a random map (indices beyond the events are clamped): every
+    particle gets, bit for bit, what its event alone gives."""
+    evs = [event(_spec(n, 2, 60 + n)) for n in (700, 2500, 100, 2501)]
+    rng = np.random.default_rng(P)
+    of = rng.integers(-1, 6, P).astype(np.int32)
+    x = torch.tensor(synth.prior_draw(rng, P, synth.gw_prior_for(evs[0])), device="cuda")
+    c = smc.Context(0)
+    for e in evs:
+        c.add_event(e)
+    oft = torch.tensor(of, device="cuda")
+    ll, g = c.loglike_grad(x, event_of_particle=oft)
+    ll2, g2 = torch.empty_like(ll), torch.empty_like(g)
+    assert c.loglike_grad_noalloc(x, ll2, g2, event_of_particle=oft) == smc.OK
+    assert torch.equal(ll, ll2) and torch.equal(g, g2)
+    for k, e in enumerate(evs):
+        rows = torch.tensor(np.nonzero(np.clip(of, 0, 3) == k)[0], device="cuda")
+        one = smc.Context(0)
+        one.add_event(e)
+        a, b = one.loglike_grad(x[rows].contiguous())
+        assert torch.equal(a, ll[rows]) and torch.equal(b, g[rows])
+        one.close()
+    c.close()
