@@ -139,8 +139,8 @@ __device__ __forceinline__ void load_chunk(BinPair<NDET, double2>& x, const Tabl
     }
 }
 
-// A wavefront visits the blocks blk0, blk0 + blk_step, ... of the padded
-// table; each block is BLK_CHUNKS chunks.  The chunks run through two register
+// A wavefront visits the blocks blk0, blk0 + blk_step, ... below blk_end of the
+// padded table; each block is BLK_CHUNKS chunks.  The chunks run through two register
 // buffers in turn: while one buffer is computed the other one's table entries
 // are in flight.  Every prefetch is unconditional (the one past the last chunk
 // re-reads the last chunk), so the buffers need no register copies.  The first
@@ -152,15 +152,18 @@ __device__ __forceinline__ void load_chunk(BinPair<NDET, double2>& x, const Tabl
 // of padding alone (u = 0) adds only zeros, so it is not visited.  Of a
 // folded event's ~310 edges that skips one chunk in four, of the 8033-bin
 // grid's 64 chunks one.
-template <class In, class Acc>
-__device__ __forceinline__ void bin_loop(Acc& A, const BinCoef& k, const TableView& t, int blk0, int blk_step) {
+//
+// SEG: after every `seg` blocks, except the last one's, end_segment() is called:
+// it takes A's sums and clears them.
+template <class In, bool SEG, class Acc, class F>
+__device__ __forceinline__ void bin_loop(Acc& A, const BinCoef& k, const TableView& t, int blk0, int blk_step,
+                                         int blk_end, int seg, F&& end_segment) {
     static_assert(BLK_CHUNKS % 2 == 0, "a block holds a whole number of buffer pairs");
-    const unsigned lane = threadIdx.x & 63;
-    const int nblk = t.npad / TABLE_PAD;
-    const int nb = blk0 < nblk ? (nblk - blk0 + blk_step - 1) / blk_step : 0;   // this wave's blocks
+    const unsigned lane = lane_here();
+    const int nb = blk0 < blk_end ? (blk_end - blk0 + blk_step - 1) / blk_step : 0;   // this wave's blocks
     if (nb == 0) return;
     const int lastblk = blk0 + (nb - 1) * blk_step;
-    const int rem = lastblk == nblk - 1 ? t.chunks - lastblk * BLK_CHUNKS : BLK_CHUNKS;   // its chunks in the last one
+    const int rem = lastblk == t.npad / TABLE_PAD - 1 ? t.chunks - lastblk * BLK_CHUNKS : BLK_CHUNKS;   // its chunks in the last one
     const int full = rem == BLK_CHUNKS ? nb : nb - 1;
     const int last = (nb - 1) * BLK_CHUNKS + rem - 1;                           // this wave's last chunk
     auto base_of = [&](int c) {
@@ -180,6 +183,7 @@ __device__ __forceinline__ void bin_loop(Acc& A, const BinCoef& k, const TableVi
             A.bin(k, b.b[1], false);
         }
         A.flush();
+        if (SEG && (blk + 1) % seg == 0 && blk + 1 < nb) end_segment();
     }
     if (full < nb) {
         A.clear();
@@ -220,7 +224,7 @@ __device__ __forceinline__ void store_moments(const double (&Zr)[NDET], const do
 template <int NDET>
 __device__ __forceinline__ void store_values(const double (&Zr)[NDET], const double (&Zi)[NDET], double* out) {
     constexpr int K = mom_g(NDET, NCOEF);
-    const int lane = threadIdx.x & 63;
+    const int lane = lane_here();
 #pragma unroll
     for (int k = 0; k < 2 * NDET; ++k) {   // mom_zr, then mom_zi
         const double t = wave_total_as<K>(k < NDET ? Zr[k % NDET] : Zi[k % NDET], k);
@@ -237,14 +241,30 @@ struct MixedAcc {
     double Zr[NDET], Zi[NDET], T[NDET], G[NCOEF];
     float zr[NDET], zi[NDET], tq[NDET];
 
-    __device__ __forceinline__ void bin(const BinCoef& k, const BinIn<NDET, float2>& x, bool first) {
-        double B[NBASIS];
+    __device__ __forceinline__ void start(const BinCoef& k) {
+#pragma unroll
+        for (int d = 0; d < NDET; ++d) {
+            pr[d] = uniform_f((float)k.pr[d]); pim[d] = uniform_f((float)k.pi[d]);
+            Zr[d] = 0.0; Zi[d] = 0.0; T[d] = 0.0;
+        }
+#pragma unroll
+        for (int b = 0; b < NCOEF; ++b) G[b] = 0.0;
+    }
+
+    __device__ __forceinline__ void store(double* mom) const {
+        if (GRAD) store_moments<NDET>(Zr, Zi, T, G, mom);
+        else store_values<NDET>(Zr, Zi, mom);
+    }
+
+    // One bin's FP32 terms into the partial sums; returns psibar_j.  B: the bin's basis rows.
+    __device__ __forceinline__ float terms(const BinCoef& k, const BinIn<NDET, float2>& x, bool first,
+                                           double (&B)[NBASIS]) {
         basis_rows(x.f, x.w, x.l, B);
         double ph = k.c[0];
 #pragma unroll
         for (int b = 0; b < NBASIS; ++b) ph = fma(k.c[1 + b], B[b], ph);
         const float ff = (float)x.f;
-        float psib;
+        float psib = 0.f;
 #pragma unroll
         for (int d = 0; d < NDET; ++d) {
             // fractional part of the phase in one FP64 instruction (exact); as a float
@@ -263,6 +283,12 @@ struct MixedAcc {
                 tq[d] = first ? q * ff : fmaf(q, ff, tq[d]);
             }
         }
+        return psib;
+    }
+
+    __device__ __forceinline__ void bin(const BinCoef& k, const BinIn<NDET, float2>& x, bool first) {
+        double B[NBASIS];
+        const float psib = terms(k, x, first, B);
         if (!GRAD) return;
         const double pb = (double)psib;
         G[0] += pb;
@@ -287,30 +313,40 @@ struct MixedAcc {
     }
 };
 
-template <int NDET, bool GRAD = true>
-__device__ __forceinline__ void bins_mixed_wave(const DevEvent* __restrict__ ev, const BinCoef& k, int blk0,
-                                                int blk_step, double* mom) {
+template <int NDET>
+__device__ __forceinline__ TableView mixed_tables(const DevEvent* __restrict__ ev) {
     const int npad = __builtin_amdgcn_readfirstlane(ev->n_pad);
+    return TableView{raw_rsrc(ev->fwl, (size_t)NROWS * npad * sizeof(double)),
+                     raw_rsrc(ev->u32, (size_t)NDET * npad * sizeof(float2)), npad,
+                     (__builtin_amdgcn_readfirstlane(ev->n_bins) + CHUNK_BINS - 1) / CHUNK_BINS};
+}
+
+// The moments of the blocks blk0, blk0 + blk_step, ... from one wavefront.
+template <int NDET, bool GRAD = true>
+__device__ __forceinline__ void bins_mixed_wave(const TableView& t, const BinCoef& k, int blk0, int blk_step,
+                                                int blk_end, double* mom) {
     MixedAcc<NDET, GRAD> A;
-#pragma unroll
-    for (int d = 0; d < NDET; ++d) {
-        A.pr[d] = uniform_f((float)k.pr[d]); A.pim[d] = uniform_f((float)k.pi[d]);
-        A.Zr[d] = 0.0; A.Zi[d] = 0.0; A.T[d] = 0.0;
-    }
-#pragma unroll
-    for (int b = 0; b < NCOEF; ++b) A.G[b] = 0.0;
-    const TableView t{raw_rsrc(ev->fwl, (size_t)NROWS * npad * sizeof(double)),
-                      raw_rsrc(ev->u32, (size_t)NDET * npad * sizeof(float2)), npad,
-                      (__builtin_amdgcn_readfirstlane(ev->n_bins) + CHUNK_BINS - 1) / CHUNK_BINS};
-    bin_loop<BinPair<NDET, float2>>(A, k, t, blk0, blk_step);
-    if (GRAD) store_moments<NDET>(A.Zr, A.Zi, A.T, A.G, mom);
-    else store_values<NDET>(A.Zr, A.Zi, mom);
+    A.start(k);
+    bin_loop<BinPair<NDET, float2>, false>(A, k, t, blk0, blk_step, blk_end, 0, [] {});
+    A.store(mom);
 }
 
 // PLAIN_FP64: the same algebra in FP64 throughout.
 template <int NDET, bool GRAD = true>
 struct Fp64Acc {
     double Zr[NDET], Zi[NDET], T[NDET], G[NCOEF];
+
+    __device__ __forceinline__ void start(const BinCoef&) {
+#pragma unroll
+        for (int d = 0; d < NDET; ++d) { Zr[d] = 0.0; Zi[d] = 0.0; T[d] = 0.0; }
+#pragma unroll
+        for (int b = 0; b < NCOEF; ++b) G[b] = 0.0;
+    }
+
+    __device__ __forceinline__ void store(double* mom) const {
+        if (GRAD) store_moments<NDET>(Zr, Zi, T, G, mom);
+        else store_values<NDET>(Zr, Zi, mom);
+    }
 
     __device__ __forceinline__ void bin(const BinCoef& k, const BinIn<NDET, double2>& x, bool) {
         double B[NBASIS];
@@ -345,21 +381,62 @@ struct Fp64Acc {
     __device__ __forceinline__ void flush() {}
 };
 
-template <int NDET, bool GRAD = true>
-__device__ __forceinline__ void bins_fp64_wave(const DevEvent* __restrict__ ev, const BinCoef& k, int blk0,
-                                               int blk_step, double* mom) {
+template <int NDET>
+__device__ __forceinline__ TableView fp64_tables(const DevEvent* __restrict__ ev) {
     const int npad = __builtin_amdgcn_readfirstlane(ev->n_pad);
+    return TableView{raw_rsrc(ev->fwl, (size_t)NROWS * npad * sizeof(double)),
+                     raw_rsrc(ev->u64, (size_t)NDET * npad * sizeof(double2)), npad,
+                     (__builtin_amdgcn_readfirstlane(ev->n_bins) + CHUNK_BINS - 1) / CHUNK_BINS};
+}
+
+template <int NDET, bool GRAD = true>
+__device__ __forceinline__ void bins_fp64_wave(const TableView& t, const BinCoef& k, int blk0, int blk_step,
+                                               int blk_end, double* mom) {
     Fp64Acc<NDET, GRAD> A;
-#pragma unroll
-    for (int d = 0; d < NDET; ++d) { A.Zr[d] = 0.0; A.Zi[d] = 0.0; A.T[d] = 0.0; }
-#pragma unroll
-    for (int b = 0; b < NCOEF; ++b) A.G[b] = 0.0;
-    const TableView t{raw_rsrc(ev->fwl, (size_t)NROWS * npad * sizeof(double)),
-                      raw_rsrc(ev->u64, (size_t)NDET * npad * sizeof(double2)), npad,
-                      (__builtin_amdgcn_readfirstlane(ev->n_bins) + CHUNK_BINS - 1) / CHUNK_BINS};
-    bin_loop<BinPair<NDET, double2>>(A, k, t, blk0, blk_step);
-    if (GRAD) store_moments<NDET>(A.Zr, A.Zi, A.T, A.G, mom);
-    else store_values<NDET>(A.Zr, A.Zi, mom);
+    A.start(k);
+    bin_loop<BinPair<NDET, double2>, false>(A, k, t, blk0, blk_step, blk_end, 0, [] {});
+    A.store(mom);
+}
+
+// A particle's moments are summed in segments of blocks of bins: a segment's
+// moments over one wavefront's lanes, then the segments in order.  So they come
+// out the same, bit for bit, whether one wavefront walks them all or each has a
+// wavefront of its own (a particle's value may not depend on the size of its
+// batch).  Events of up to 8192 bins are one segment.  A segment's end costs its
+// wavefront about 200 of the 9000 (or 18000) instructions of its bins, so longer
+// tables take longer segments.
+__host__ __device__ constexpr int segment_blocks(int npad) { return npad <= 64 * TABLE_PAD ? 16 : 32; }
+__host__ __device__ constexpr int segments(int npad) {
+    return (npad / TABLE_PAD + segment_blocks(npad) - 1) / segment_blocks(npad);
+}
+__device__ constexpr int moments(int n_det, bool grad) { return grad ? mom_g(n_det, NCOEF) : 2 * n_det; }
+
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// All segments from one wavefront into mom (LDS; seg: scratch of the same size).
+template <int NDET, bool GRAD, class In, class Acc>
+__device__ __forceinline__ void event_moments(const TableView& t, const BinCoef& k, double* mom, double* seg) {
+    Acc A;
+    A.start(k);
+    bool first = true;
+    auto end = [&] {
+        if (first) {
+            A.store(mom);
+        } else {
+            A.store(seg);
+            wave_lds_fence();
+            const int l = lane_here();
+            if (l < moments(NDET, GRAD)) mom[l] += seg[l];
+        }
+        wave_lds_fence();
+        first = false;
+        A.start(k);
+    };
+    bin_loop<In, true>(A, k, t, 0, 1, t.npad / TABLE_PAD, segment_blocks(t.npad), end);
+    end();
 }
 
 // logL from the Z moments alone (the sum of finish_particle, term by term).

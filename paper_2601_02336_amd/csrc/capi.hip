@@ -66,15 +66,27 @@ int ctx_reserve(smcgw_ctx* c, int P) {
 int ctx_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
                 int precision) {
     if (c->events.empty()) return SMCGW_ERR_NOT_INIT;
-    if (lengths_differ(c, ev_of_p) && P > c->sort_cap) {
-        const int cap = std::max(P, std::max(2 * c->sort_cap, 256));
-        (void)hipFree(c->d_sort);
-        c->d_sort = nullptr;
-        c->sort_cap = 0;
-        if (hipMalloc(&c->d_sort, (size_t)cap * sizeof(int32_t)) != hipSuccess) return SMCGW_ERR_OOM;
-        c->sort_cap = cap;
+    // Scratch that only speeds the call up: without it (no memory left, or a stream being captured, where nothing
+    // can be allocated) the call takes the path that needs none, with the same results.
+    const int sort_need = lengths_differ(c, ev_of_p) ? P : 0;
+    const size_t few_need = loglike_scratch_bytes(c, P, ev_of_p, precision);
+    if (sort_need > c->sort_cap || (few_need && !c->d_few)) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+            if (sort_need > c->sort_cap) {
+                const int n = std::max(sort_need, std::max(2 * c->sort_cap, 4096));
+                (void)hipFree(c->d_sort);
+                c->d_sort = nullptr;
+                c->sort_cap = 0;
+                if (hipMalloc(&c->d_sort, (size_t)n * sizeof(int32_t)) == hipSuccess) c->sort_cap = n;
+                else c->d_sort = nullptr;
+            }
+            if (few_need && !c->d_few && hipMalloc(&c->d_few, few_need) != hipSuccess) c->d_few = nullptr;
+            (void)hipGetLastError();   // a refused allocation is no error of the call
+        }
     }
-    return queue_loglike(c, P, ev_of_p, theta, logl, grad, precision, c->d_sort);
+    return queue_loglike(c, P, ev_of_p, theta, logl, grad, precision, sort_need <= c->sort_cap ? c->d_sort : nullptr,
+                         c->d_few);
 }
 
 }  // namespace smcgw
@@ -115,6 +127,7 @@ extern "C" int smcgw_destroy(smcgw_ctx* c) {
     (void)hipFree(c->d_small);
     (void)hipFree(c->d_cb);
     (void)hipFree(c->d_sort);
+    (void)hipFree(c->d_few);
     (void)hipFree(c->d_tan);
     c->sweep_free();
     c->sampler_free();

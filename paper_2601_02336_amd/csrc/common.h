@@ -52,6 +52,15 @@ __device__ __forceinline__ double dpp_move(double v) {
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// This lane's index, computed anew at every call: lane masks and addresses made
+// from it are not carried in registers through the loops around the call (in the
+// bin loops that costs spills).
+__device__ __forceinline__ int lane_here() {
+    unsigned zero = 0;
+    __asm__ volatile("" : "+s"(zero));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
 // Sum over the 64 lanes of a wavefront in a fixed order: pairs and quads
 // (quad permutations), rows of 16 (row rotations by 4 and 8), then the rows
 // through the row-15 and row-31 broadcasts.  The total is valid in lane 63
@@ -83,7 +92,7 @@ __device__ __forceinline__ double wave_total(double v) {
 template <int K>
 __device__ __forceinline__ void wave_totals_to(const double (&v)[K], double* out, int stride = 1) {
     constexpr int M1 = (K + 1) / 2, M2 = (M1 + 1) / 2, M3 = (M2 + 1) / 2;
-    const int lane = threadIdx.x & 63;
+    const int lane = lane_here();
     const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
     double c1[M1], c2[M2], c3[M3];
 #pragma unroll
@@ -229,14 +238,14 @@ hipError_t launch_prep(const DevEvent* d_events, int n_events, const int32_t* ev
                        const double* theta, double* cb, hipStream_t s);
 // One batched likelihood launch: logl [P] and grad [P][pm.dim] (NULL: values
 // only) of theta [P][pm.dim]; order [P] (NULL: index order) is the start order,
-// longest the largest n_pad among the events.
+// longest and max_seg the largest n_pad and segment count among the events.
 struct LoglikeCall {
     const DevEvent* events;
     int n_events;
     const int32_t* ev_of_p;
     const int32_t* order;
     ParamMap pm;
-    int P, longest;
+    int P, longest, max_seg;
     const double* theta;
     double *logl, *grad;
 };

@@ -37,6 +37,7 @@ struct smcgw_ctx {
     int cap = 0;
     int32_t* d_sort = nullptr;             // start order of a batch over events of different lengths
     int sort_cap = 0;
+    void* d_few = nullptr;                 // segments of the few-particle likelihood (13.6 MiB, on its first use)
     double* d_tan = nullptr;               // tangent moment blocks of the plain form, [tan_cap][12]
     int tan_cap = 0;
     // sampler state
@@ -134,7 +135,8 @@ int queue_loglike_tangent(smcgw_ctx* c, int P, const int32_t* ev_of_p, const dou
 bool tangent_supported(const smcgw_ctx* c);
 bool lengths_differ(const smcgw_ctx* c, const int32_t* ev_of_p);
 int queue_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
-                  int precision, int32_t* order);
+                  int precision, int32_t* order, void* few);
+size_t loglike_scratch_bytes(const smcgw_ctx* c, int P, const int32_t* ev_of_p, int precision);
 int ctx_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
                 int precision);
 }  // namespace smcgw

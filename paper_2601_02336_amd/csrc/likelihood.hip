@@ -19,6 +19,8 @@
 //        of its particles (lanes stride the frequency bins, the shared per-bin
 //        tables are read coalesced, each lane keeps its own partial sums) and one
 //        lane per particle forms logL and the gradient from the moments.
+//   point, segment, finish (few particles): a particle's bins spread over
+//        wavefronts.
 //   prep: the coefficient blocks alone, in global memory, for the plain
 //        comparison form and the waveform.
 //   sort_events: start order of a batch over events of different lengths.
@@ -82,6 +84,20 @@ __global__ __launch_bounds__(256) void prep_kernel(const DevEvent* __restrict__ 
                    ang_sh[g], threadIdx.x % PREP_LANES, p < P);
 }
 
+// logL and gradient of particle p from its coefficient block and moments (one lane).
+template <bool GRAD>
+__device__ __forceinline__ void write_result(const DevEvent& ev, const ParamMap& pm, const double* cb,
+                                             const double* mom, int p, double* __restrict__ logl,
+                                             double* __restrict__ grad) {
+    if (GRAD) {
+        double g[NPAR];
+        logl[p] = finish_particle(ev, cb, mom, g);
+        for (int q = 0; q < pm.dim; ++q) grad[(size_t)p * pm.dim + q] = g[pm.idx[q]];
+    } else {
+        logl[p] = finish_value(ev, cb, mom);
+    }
+}
+
 // Particles [LL_WAVES per_wave blockIdx.x, ...) of the start order (order NULL:
 // index order), per_wave <= 8 for each wavefront.  Bound by the VALU issue rate
 // of the bin loop; the coefficient blocks and moments stay in LDS, so a call is
@@ -92,7 +108,10 @@ __global__ __launch_bounds__(256) void prep_kernel(const DevEvent* __restrict__ 
 struct LoglikeShared {   // one per particle of the workgroup (dynamic LDS)
     double cb[CB_SIZE];
     double mom[MOM_SIZE];
-    double ang[ANG_COUNT][2];
+    union {
+        double ang[ANG_COUNT][2];   // prologue
+        double seg[MOM_SIZE];       // bins
+    };
 };
 
 template <int NDET, int PREC, bool GRAD>
@@ -103,7 +122,6 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
                                                   double* __restrict__ logl, double* __restrict__ grad) {
     extern __shared__ LoglikeShared sh[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
     const int first = blockIdx.x * LL_WAVES * per_wave;
     {
         // prologue: the workgroup's particles on consecutive groups of eight lanes
@@ -122,24 +140,17 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
         const int p = order ? order[first + g] : first + g;
         const int e = __builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events));
         const BinCoef k = load_coef(sh[g].cb);
+        const TableView t = PREC == SMCGW_MIXED ? mixed_tables<NDET>(evs + e) : fp64_tables<NDET>(evs + e);
         if (PREC == SMCGW_MIXED)
-            bins_mixed_wave<NDET, GRAD>(evs + e, k, 0, 1, sh[g].mom);
+            event_moments<NDET, GRAD, BinPair<NDET, float2>, MixedAcc<NDET, GRAD>>(t, k, sh[g].mom, sh[g].seg);
         else
-            bins_fp64_wave<NDET, GRAD>(evs + e, k, 0, 1, sh[g].mom);
+            event_moments<NDET, GRAD, BinPair<NDET, double2>, Fp64Acc<NDET, GRAD>>(t, k, sh[g].mom, sh[g].seg);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    const int lane = lane_here();
     if (lane < n) {
         const LoglikeShared& s = sh[g0 + lane];
         const int i = first + g0 + lane, p = order ? order[i] : i;
-        const DevEvent& ev = evs[event_index(ev_of_p, p, n_events)];
-        if (GRAD) {
-            double g[NPAR];
-            logl[p] = finish_particle(ev, s.cb, s.mom, g);
-            for (int q = 0; q < pm.dim; ++q) grad[(size_t)p * pm.dim + q] = g[pm.idx[q]];
-        } else {
-            logl[p] = finish_value(ev, s.cb, s.mom);
-        }
+        write_result<GRAD>(evs[event_index(ev_of_p, p, n_events)], pm, s.cb, s.mom, p, logl, grad);
     }
 }
 
@@ -160,6 +171,300 @@ __global__ __launch_bounds__(64 * LL_WAVES, NDET == 1 || !GRAD ? 4 : 3) void bin
     const int32_t* __restrict__ order, ParamMap pm, int P, int per_wave, const double* __restrict__ theta,
     double* __restrict__ logl, double* __restrict__ grad) {
     loglike_workgroup<NDET, SMCGW_PLAIN_FP64, GRAD>(evs, n_events, ev_of_p, order, pm, P, per_wave, theta, logl, grad);
+}
+
+// ------------------------------------------------------------ few particles
+// A launch of one wavefront per particle leaves most of the chip idle when
+// there are few particles: one particle of 3 x 8033 bins kept one SIMD busy for
+// 20 us, 37 of a 259585-bin event 37 of 1024 SIMDs for 630.  Two ways to spread
+// a particle, both to the same bits:
+//   segment_kernel: a wavefront per segment (those 37 particles: 636 -> 54 us);
+//   point_kernel:   a workgroup of 16 wavefronts per segment, for so few that even
+//       the segments leave compute units idle (one particle of 8033 bins:
+//       29.9 -> 15.8 us, of 259585 bins: 630 -> 31).  A lane adds its FP64 terms
+//       one after the other over the segment's blocks, so the work is split by
+//       kind: first every wavefront takes one block's bins (FP32 terms, their
+//       partial sums over the block, psibar of every bin, all into LDS), then one
+//       wavefront per moment adds its lanes' terms in block order.
+// Events of one segment finish there; of more, finish_kernel adds the segments.
+constexpr int PT_WAVES = 16;
+constexpr int PT_BLOCKS = PT_WAVES;   // blocks in LDS at once; a segment is one or two such rounds
+constexpr int PT_THREADS = 64 * PT_WAVES;
+
+template <int NDET>
+struct PointPartials {      // one block's terms
+    float z[3 * NDET][64];  // zr, zi, tq of every lane, in mom_* order
+};
+
+// Prologue on three wavefronts of the workgroup; the caller's barrier follows.
+__device__ __forceinline__ void point_prologue(const DevEvent& ev, const ParamMap& pm, const double* __restrict__ x,
+                                               double* cb, double (*ang_sh)[2], int wave, int lane) {
+    if (wave > 2 || lane >= PREP_LANES) return;
+    double th[NPAR];
+    expand_params(pm, x, th);
+    if (wave == 0 && lane < 4) prep_intrinsic_n<1>(ev, th, cb, lane, lane == 0);
+    if (wave == 1) {
+        if (lane < ANG_COUNT) {
+            double sn, cs;
+            sincos(extrinsic_angle(ev, th, lane), &sn, &cs);
+            ang_sh[lane][0] = sn;
+            ang_sh[lane][1] = cs;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        ExtAngles ang;
+#pragma unroll
+        for (int k = 0; k < ANG_COUNT; ++k) { ang.sc[k][0] = ang_sh[k][0]; ang.sc[k][1] = ang_sh[k][1]; }
+        const int k = lane / MAXDET;
+        prep_extrinsic_det_n<1>(ev, th, ang, cb, lane % MAXDET, k, k == 0);
+    }
+    if (wave == 2 && lane == 0) prep_extrinsic_common(ev, th, cb);
+}
+
+// Terms of block blk (its chunks below t.chunks): psibar of every bin to psi and
+// its f^1/3 to u, the block's partial sums to part.
+template <int NDET, bool GRAD>
+__device__ __forceinline__ void point_terms(const TableView& t, const BinCoef& k, int blk, float* psi, double* u,
+                                            PointPartials<NDET>& part) {
+    const unsigned lane = threadIdx.x & 63;
+    MixedAcc<NDET, GRAD> A;
+#pragma unroll
+    for (int d = 0; d < NDET; ++d) { A.pr[d] = uniform_f((float)k.pr[d]); A.pim[d] = uniform_f((float)k.pi[d]); }
+    A.clear();
+    const int n = min(BLK_CHUNKS, t.chunks - blk * BLK_CHUNKS);
+    constexpr int DEPTH = NDET < 3 ? 4 : 3;   // chunks in flight, by the registers there are
+    BinPair<NDET, float2> x[DEPTH];
+#pragma unroll
+    for (int c = 0; c < DEPTH; ++c) load_chunk(x[c], t, blk * TABLE_PAD + CHUNK_BINS * min(c, n - 1), lane);
+#pragma unroll
+    for (int c = 0; c < BLK_CHUNKS; ++c)
+        if (c < n) {
+            double Ba[NBASIS], Bb[NBASIS];
+            const float a = A.terms(k, x[c % DEPTH].b[0], c == 0, Ba);
+            const float b = A.terms(k, x[c % DEPTH].b[1], false, Bb);
+            if (c + DEPTH < BLK_CHUNKS)
+                load_chunk(x[c % DEPTH], t, blk * TABLE_PAD + CHUNK_BINS * min(c + DEPTH, n - 1), lane);
+            if (GRAD) {
+                *(float2*)(psi + CHUNK_BINS * c + 2 * lane) = make_float2(a, b);
+                *(double2*)(u + CHUNK_BINS * c + 2 * lane) = make_double2(Ba[B_P13], Bb[B_P13]);
+            }
+        }
+#pragma unroll
+    for (int d = 0; d < NDET; ++d) {
+        part.z[mom_zr(NDET, d)][lane] = A.zr[d];
+        part.z[mom_zi(NDET, d)][lane] = A.zi[d];
+        if (GRAD) part.z[mom_t(NDET, d)][lane] = A.tq[d];
+    }
+}
+
+// One bin's term onto the lane sum s of basis moment B (0: the constant), with
+// the basis row as basis_rows forms it from w, ln f and u = f^1/3.
+template <int B>
+__device__ __forceinline__ double point_add(double s, float psib, double w, double l, double u) {
+    const double pb = (double)psib;
+    if (B == 0) return s + pb;
+    const double w2 = w * w, w3 = w2 * w;
+    const double row = B == 1 + B_M53 ? w3 * w2 : B == 1 + B_M1 ? w3 : B == 1 + B_M23 ? w2 : B == 1 + B_M13 ? w
+                     : B == 1 + B_LN ? l : B == 1 + B_P13 ? u : B == 1 + B_P13LN ? u * l : u * u;
+    return fma(pb, row, s);
+}
+
+// Calls f.run<B>() for the wave-uniform B = wave < NCOEF.
+template <class F>
+__device__ __forceinline__ void for_basis(int wave, F& f) {
+    switch (wave) {
+    case 0: f.template run<0>(); break;
+    case 1: f.template run<1>(); break;
+    case 2: f.template run<2>(); break;
+    case 3: f.template run<3>(); break;
+    case 4: f.template run<4>(); break;
+    case 5: f.template run<5>(); break;
+    case 6: f.template run<6>(); break;
+    case 7: f.template run<7>(); break;
+    case 8: f.template run<8>(); break;
+    default: break;
+    }
+}
+static_assert(NCOEF == 9, "for_basis lists the basis moments");
+
+// Lane sums of a basis moment over n chunks from chunk c0 in the bin loop's
+// order: psibar and f^1/3 from LDS, at most one table row from the cache (the
+// terms have just read it; a second row would halve the chunks in flight).
+struct PointBasisSum {
+    const TableView& t;
+    const float* psi;
+    const double* u;
+    int c0, n;
+    double s;
+    template <int B>
+    __device__ __forceinline__ void run() {
+        const unsigned lane = threadIdx.x & 63;
+        constexpr bool W = B >= 1 && B <= 1 + B_M13, L = B == 1 + B_LN || B == 1 + B_P13LN, U = B >= 1 + B_P13;
+        constexpr int DEPTH = 8;   // chunks in flight
+        double2 x[DEPTH];
+        auto load = [&](double2& v, int c) {
+            if (W || L) v = buf_f64x2(t.fwl, lane * 16u, ((W ? ROW_W : ROW_LN) * t.npad + (c0 + c) * CHUNK_BINS) * 8);
+        };
+        auto add = [&](const double2& v, int c) {
+            const float2 p = *(const float2*)(psi + c * CHUNK_BINS + 2 * lane);
+            double2 q = make_double2(0.0, 0.0);
+            if (U) q = *(const double2*)(u + c * CHUNK_BINS + 2 * lane);
+            s = point_add<B>(s, p.x, v.x, v.x, q.x);
+            s = point_add<B>(s, p.y, v.y, v.y, q.y);
+        };
+        const int last = n - 1;
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) load(x[d], min(d, last));
+        int c = 0;
+        for (; c + DEPTH <= n; c += DEPTH) {
+#pragma unroll
+            for (int d = 0; d < DEPTH; ++d) {
+                add(x[d], c + d);
+                load(x[d], min(c + d + DEPTH, last));
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d)
+            if (c + d < n) add(x[d], c + d);
+    }
+};
+static_assert(B_M53 == 0 && B_M13 == 3 && B_P13 == 5 && B_P23 == 7, "the rows a moment needs go by its place");
+
+struct PointShared {
+    double cb[CB_SIZE], mom[MOM_SIZE], ang[ANG_COUNT][2];
+    double row[mom_g(MAXDET, NCOEF)][64];   // lane sums of every moment
+};
+
+// Where the few-particle kernels leave what finish_kernel needs, for calls on
+// events of more than one segment: per particle a coefficient block and max_seg
+// moment blocks.
+struct SegmentScratch {
+    double *cb, *mom;
+    int max_seg;
+};
+
+// Segment blockIdx.x of particle blockIdx.y.
+template <int NDET, bool GRAD>
+__global__ __launch_bounds__(PT_THREADS) void point_kernel(const DevEvent* __restrict__ evs, int n_events,
+                                                           const int32_t* __restrict__ ev_of_p, ParamMap pm,
+                                                           SegmentScratch scr, const double* __restrict__ theta,
+                                                           double* __restrict__ logl, double* __restrict__ grad) {
+    __shared__ PointShared S;
+    __shared__ PointPartials<NDET> part[PT_BLOCKS];
+    __shared__ float psi[PT_BLOCKS * TABLE_PAD];
+    __shared__ double u[GRAD ? PT_BLOCKS * TABLE_PAD : 1];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int seg = blockIdx.x, p = blockIdx.y;
+    const DevEvent& ev = evs[__builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events))];
+    const TableView t = mixed_tables<NDET>(&ev);
+    if (seg >= segments(t.npad)) return;   // a shorter event of the batch
+    point_prologue(ev, pm, theta + (size_t)p * pm.dim, S.cb, S.ang, wave, lane);
+    const int seg0 = seg * segment_blocks(t.npad), seg1 = min(t.npad / TABLE_PAD, seg0 + segment_blocks(t.npad));
+    constexpr int W0 = GRAD ? NCOEF : 0, ROWS = GRAD ? 3 * NDET : 2 * NDET;   // partials' rows, their first wavefront
+    constexpr int RPW = (ROWS + PT_WAVES - W0 - 1) / (PT_WAVES - W0);
+    double sum = 0.0, zsum[RPW];
+#pragma unroll
+    for (int q = 0; q < RPW; ++q) zsum[q] = 0.0;
+    for (int b0 = seg0; b0 < seg1; b0 += PT_BLOCKS) {
+        const int nblk = min(seg1 - b0, PT_BLOCKS);
+        __syncthreads();   // the prologue, or the last round's readers
+        if (wave < nblk)
+            point_terms<NDET, GRAD>(t, load_coef(S.cb), b0 + wave, psi + wave * TABLE_PAD,
+                                    u + (GRAD ? wave * TABLE_PAD : 0), part[wave]);
+        __syncthreads();
+        if (GRAD && wave < NCOEF) {
+            PointBasisSum b{t, psi, u, b0 * BLK_CHUNKS, min(t.chunks - b0 * BLK_CHUNKS, nblk * BLK_CHUNKS), sum};
+            for_basis(wave, b);
+            sum = b.s;
+        } else {
+#pragma unroll
+            for (int q = 0; q < RPW; ++q) {
+                const int r = min(wave - W0 + q * (PT_WAVES - W0), ROWS - 1);
+#pragma unroll
+                for (int b = 0; b < PT_BLOCKS; ++b)
+                    if (b < nblk) zsum[q] += part[b].z[r][lane];
+            }
+        }
+    }
+    if (GRAD && wave < NCOEF) {
+        S.row[mom_g(NDET, wave)][lane] = sum;
+    } else {
+#pragma unroll
+        for (int q = 0; q < RPW; ++q) {
+            const int r = wave - W0 + q * (PT_WAVES - W0);
+            if (r < ROWS) S.row[r][lane] = zsum[q];
+        }
+    }
+    __syncthreads();
+    if (wave != 0) {
+        if (scr.max_seg > 1 && seg == 0 && wave == 1)
+            for (int e = lane; e < CB_SIZE; e += 64) scr.cb[(size_t)p * CB_SIZE + e] = S.cb[e];
+        return;
+    }
+    double* mom = scr.max_seg > 1 ? scr.mom + ((size_t)p * scr.max_seg + seg) * MOM_SIZE : S.mom;
+    if (GRAD) {
+        constexpr int K = mom_g(NDET, NCOEF);
+        double v[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = S.row[k][lane];
+        wave_totals_to<K>(v, mom);
+    } else {
+        double zr[NDET], zi[NDET];
+#pragma unroll
+        for (int d = 0; d < NDET; ++d) { zr[d] = S.row[mom_zr(NDET, d)][lane]; zi[d] = S.row[mom_zi(NDET, d)][lane]; }
+        store_values<NDET>(zr, zi, mom);
+    }
+    if (scr.max_seg > 1) return;
+    wave_lds_fence();
+    if (lane == 0) write_result<GRAD>(ev, pm, S.cb, S.mom, p, logl, grad);
+}
+
+// Segments [LL_WAVES blockIdx.x, ...) of particle blockIdx.y, one per wavefront.
+template <int NDET, int PREC, bool GRAD>
+__global__ __launch_bounds__(64 * LL_WAVES, 3) void segment_kernel(
+    const DevEvent* __restrict__ evs, int n_events, const int32_t* __restrict__ ev_of_p, ParamMap pm,
+    SegmentScratch scr, const double* __restrict__ theta) {
+    __shared__ double cb[CB_SIZE], ang[ANG_COUNT][2];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int p = blockIdx.y, seg = blockIdx.x * LL_WAVES + wave;
+    const DevEvent& ev = evs[__builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events))];
+    const TableView t = PREC == SMCGW_MIXED ? mixed_tables<NDET>(&ev) : fp64_tables<NDET>(&ev);
+    const int nseg = segments(t.npad);
+    if ((int)blockIdx.x * LL_WAVES >= nseg) return;
+    point_prologue(ev, pm, theta + (size_t)p * pm.dim, cb, ang, wave, lane);
+    __syncthreads();
+    if (blockIdx.x == 0)
+        for (int e = threadIdx.x; e < CB_SIZE; e += 64 * LL_WAVES) scr.cb[(size_t)p * CB_SIZE + e] = cb[e];
+    if (seg >= nseg) return;
+    double* mom = scr.mom + ((size_t)p * scr.max_seg + seg) * MOM_SIZE;
+    const int b0 = seg * segment_blocks(t.npad), b1 = min(t.npad / TABLE_PAD, b0 + segment_blocks(t.npad));
+    if (PREC == SMCGW_MIXED)
+        bins_mixed_wave<NDET, GRAD>(t, load_coef(cb), b0, 1, b1, mom);
+    else
+        bins_fp64_wave<NDET, GRAD>(t, load_coef(cb), b0, 1, b1, mom);
+}
+
+// Results of the particles whose segments the kernels above left in scratch:
+// a wavefront per particle adds the segments in order, one lane finishes.
+template <bool GRAD>
+__global__ __launch_bounds__(64) void finish_kernel(const DevEvent* __restrict__ evs, int n_events,
+                                                    const int32_t* __restrict__ ev_of_p, ParamMap pm,
+                                                    SegmentScratch scr, double* __restrict__ logl,
+                                                    double* __restrict__ grad) {
+    __shared__ double cb[CB_SIZE], mom[MOM_SIZE];
+    const int lane = threadIdx.x, p = blockIdx.x;
+    const DevEvent& ev = evs[__builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events))];
+    for (int e = lane; e < CB_SIZE; e += 64) cb[e] = scr.cb[(size_t)p * CB_SIZE + e];
+    const double* m = scr.mom + (size_t)p * scr.max_seg * MOM_SIZE;
+    if (lane < moments(ev.n_det, GRAD)) {
+        double s = m[lane];
+        const int n = segments(ev.n_pad);
+#pragma unroll 8
+        for (int k = 1; k < n; ++k) s += m[(size_t)k * MOM_SIZE + lane];
+        mom[lane] = s;
+    }
+    wave_lds_fence();
+    if (lane == 0) write_result<GRAD>(ev, pm, cb, mom, p, logl, grad);
 }
 
 // Start order of a batch whose events differ in length: particles by falling
@@ -320,6 +625,62 @@ hipError_t launch_loglike(const LoglikeCall& a, int n_det, int precision, hipStr
     }
 }
 
+// The few-particle paths, and where they end.  POINT: MIXED calls on events of
+// POINT_MIN_BLOCKS blocks and more, while every segment gets a compute unit of
+// its own (256 particles of 8033 bins: 18.7 us, 33.3 with a wavefront each; 400,
+// in two rounds of workgroups: 38 against 31).  SEGMENTS: events of more than one
+// segment while one wavefront per particle does not fill the chip's SIMDs twice
+// (32449 bins, 1500 particles: 254 us against 301; 2500: 430 against 423); their
+// scratch is bounded by SEGMENT_MAX.
+constexpr int POINT_MIN_BLOCKS = 8;
+constexpr int POINT_WORKGROUPS = 256;   // compute units
+constexpr int SEGMENT_MAX_P = 2048;
+constexpr int SEGMENT_MAX = 65536;      // segments of a call (192 B each)
+enum LoglikePath { PATH_BATCH, PATH_POINT, PATH_SEGMENTS };
+
+static LoglikePath loglike_path(int P, int longest, int nseg, int precision) {
+    if ((long)P * nseg > SEGMENT_MAX) return PATH_BATCH;
+    if (precision == SMCGW_MIXED && longest >= POINT_MIN_BLOCKS * TABLE_PAD && P * nseg <= POINT_WORKGROUPS)
+        return PATH_POINT;
+    return nseg > 1 && P < SEGMENT_MAX_P ? PATH_SEGMENTS : PATH_BATCH;
+}
+
+static size_t segment_scratch_bytes() {
+    return (SEGMENT_MAX * (size_t)MOM_SIZE + SEGMENT_MAX_P * (size_t)CB_SIZE) * sizeof(double);
+}
+
+template <int NDET, bool GRAD>
+hipError_t launch_few_ndet(const LoglikeCall& a, LoglikePath path, int precision, void* scratch, hipStream_t s) {
+    const int nseg = a.max_seg;
+    SegmentScratch scr{(double*)scratch, (double*)scratch + (size_t)SEGMENT_MAX_P * CB_SIZE, nseg};
+    const dim3 segs((nseg + LL_WAVES - 1) / LL_WAVES, a.P), block(64 * LL_WAVES);
+    if (path == PATH_POINT)
+        hipLaunchKernelGGL((point_kernel<NDET, GRAD>), dim3(nseg, a.P), dim3(PT_THREADS), 0, s, a.events, a.n_events,
+                           a.ev_of_p, a.pm, scr, a.theta, a.logl, a.grad);
+    else if (precision == SMCGW_MIXED)
+        hipLaunchKernelGGL((segment_kernel<NDET, SMCGW_MIXED, GRAD>), segs, block, 0, s, a.events, a.n_events,
+                           a.ev_of_p, a.pm, scr, a.theta);
+    else
+        hipLaunchKernelGGL((segment_kernel<NDET, SMCGW_PLAIN_FP64, GRAD>), segs, block, 0, s, a.events, a.n_events,
+                           a.ev_of_p, a.pm, scr, a.theta);
+    if (nseg > 1)
+        hipLaunchKernelGGL(finish_kernel<GRAD>, dim3(a.P), dim3(64), 0, s, a.events, a.n_events, a.ev_of_p, a.pm, scr,
+                           a.logl, a.grad);
+    return hipGetLastError();
+}
+
+hipError_t launch_few(const LoglikeCall& a, LoglikePath path, int n_det, int precision, void* scratch,
+                      hipStream_t s) {
+    const bool g = a.grad != nullptr;
+    switch (n_det) {
+    case 1: return g ? launch_few_ndet<1, true>(a, path, precision, scratch, s) : launch_few_ndet<1, false>(a, path, precision, scratch, s);
+    case 2: return g ? launch_few_ndet<2, true>(a, path, precision, scratch, s) : launch_few_ndet<2, false>(a, path, precision, scratch, s);
+    case 3: return g ? launch_few_ndet<3, true>(a, path, precision, scratch, s) : launch_few_ndet<3, false>(a, path, precision, scratch, s);
+    case 4: return g ? launch_few_ndet<4, true>(a, path, precision, scratch, s) : launch_few_ndet<4, false>(a, path, precision, scratch, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_waveform(const DevEvent* d_events, int event_id, const double* cb, double* h_reim, int n_bins,
                            int n_det, hipStream_t s) {
     hipLaunchKernelGGL(waveform_kernel, dim3((n_bins + 255) / 256), dim3(256), 0, s, d_events, event_id, cb, h_reim,
@@ -340,14 +701,39 @@ bool lengths_differ(const smcgw_ctx* c, const int32_t* ev_of_p) {
     return false;
 }
 
+// The longest table and the most segments among the events a call can meet.
+static void event_extent(const smcgw_ctx* c, const int32_t* ev_of_p, int& longest, int& max_seg) {
+    longest = c->events[0].n_pad;
+    max_seg = segments(longest);
+    if (ev_of_p)
+        for (const DevEvent& e : c->events) {
+            longest = std::max(longest, e.n_pad);
+            max_seg = std::max(max_seg, segments(e.n_pad));
+        }
+}
+
+// Scratch the call would use on the few-particle paths (0: none).
+size_t loglike_scratch_bytes(const smcgw_ctx* c, int P, const int32_t* ev_of_p, int precision) {
+    int longest, nseg;
+    event_extent(c, ev_of_p, longest, nseg);
+    return loglike_path(P, longest, nseg, precision) != PATH_BATCH && nseg > 1 ? segment_scratch_bytes() : 0;
+}
+
 // The batched likelihood on the context's stream; order: scratch for P start
-// positions (used only when the events differ in length).
+// positions (NULL: index order), few: loglike_scratch_bytes of scratch for the
+// few-particle paths (NULL: they are taken only where they need none).  Every
+// path gives the same bits.
 int queue_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
-                  int precision, int32_t* order) {
-    LoglikeCall a{c->d_events, (int)c->events.size(), ev_of_p, nullptr, c->pmap, P, 0, theta, logl, grad};
-    for (const DevEvent& e : c->events) a.longest = std::max(a.longest, e.n_pad);
+                  int precision, int32_t* order, void* few) {
+    LoglikeCall a{c->d_events, (int)c->events.size(), ev_of_p, nullptr, c->pmap, P, 0, 0, theta, logl, grad};
+    event_extent(c, ev_of_p, a.longest, a.max_seg);
+    const LoglikePath path = loglike_path(P, a.longest, a.max_seg, precision);
+    if (path != PATH_BATCH && (few || a.max_seg == 1)) {
+        TimedLaunch t(c, SMCGW_KERNEL_BINS);
+        return launch_few(a, path, c->n_det, precision, few, c->stream) == hipSuccess ? SMCGW_OK : SMCGW_ERR_HIP;
+    }
     // up to one wavefront per SIMD they all start at once, and an order changes nothing
-    if (P > SORT_MIN_P && lengths_differ(c, ev_of_p)) {
+    if (order && P > SORT_MIN_P && lengths_differ(c, ev_of_p)) {
         std::vector<int> len;
         for (const DevEvent& e : c->events) len.push_back(e.n_pad);
         std::sort(len.begin(), len.end(), std::greater<int>());
@@ -377,5 +763,5 @@ extern "C" int smcgw_loglike_grad_noalloc(smcgw_ctx* c, int P, const int32_t* ev
     if (P == 0) return SMCGW_OK;
     if (c->device < 0 || c->device >= NOALLOC_DEVICES || !noalloc_base[c->device]) return SMCGW_ERR_NOT_INIT;
     if (hipSetDevice(c->device) != hipSuccess) return SMCGW_ERR_HIP;
-    return queue_loglike(c, P, event_of_particle, theta, logl, grad, precision, noalloc_base[c->device]);
+    return queue_loglike(c, P, event_of_particle, theta, logl, grad, precision, noalloc_base[c->device], nullptr);
 }

@@ -899,10 +899,11 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 1 ? 2 : NUTS_WAVES_PER_SIMD))
             if (TK == SMCGW_TARGET_GW) {
                 {
                     const BinCoef k = load_coef(S.cb);
+                    const TableView t = PREC == SMCGW_MIXED ? mixed_tables<NDET>(ev) : fp64_tables<NDET>(ev);
                     if (PREC == SMCGW_MIXED)
-                        bins_mixed_wave<NDET>(ev, k, wave, WAVES, S.mom[wave]);
+                        bins_mixed_wave<NDET>(t, k, wave, WAVES, t.npad / TABLE_PAD, S.mom[wave]);
                     else
-                        bins_fp64_wave<NDET>(ev, k, wave, WAVES, S.mom[wave]);
+                        bins_fp64_wave<NDET>(t, k, wave, WAVES, t.npad / TABLE_PAD, S.mom[wave]);
                 }
                 __syncthreads();
                 if (wave == 0) leaf_finish<NDET, WAVES>(ev, S, T, D, lane);

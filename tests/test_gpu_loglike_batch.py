@@ -44,18 +44,25 @@ def test_last_block(smc, n, n_det):
     c.close()
 
 
-@pytest.mark.parametrize("n", [310, 3000])
+@pytest.mark.parametrize("n", [310, 3000, 3585, 8192, 8193, 20001])
 def test_batch_size_changes_nothing(smc, n):
-    """A particle's value and gradient are the same bits in every batch: one particle up to several per wavefront,
-    full and partial workgroups."""
+    """A particle's value and gradient are the same bits in every batch: a workgroup per segment of 16 blocks of bins
+    (from 8 blocks on, up to 256 segments), a wavefront per segment, one particle per wavefront, several; full and
+    partial workgroups."""
     ev = event(_spec(n, 3, 50))
     x = torch.tensor(synth.prior_draw(np.random.default_rng(1), 16400, synth.gw_prior_for(ev)), device="cuda")
     c = smc.Context(0)
     c.add_event(ev)
     ll, g = c.loglike_grad(x)
-    for P in (1, 3, 4, 5, 31, 2047, 2048, 2049, 16383, 16384):
+    llp, gp = c.loglike_grad(x[:2100].contiguous(), precision=smc.PLAIN_FP64)
+    for P in (1, 3, 4, 5, 31, 85, 86, 256, 257, 2047, 2048, 2049, 16383, 16384):
         a, b = c.loglike_grad(x[:P].contiguous())
         assert torch.equal(a, ll[:P]) and torch.equal(b, g[:P]), P
+        assert torch.equal(c.loglike_grad(x[:P].contiguous(), want_grad=False), ll[:P]), P
+        if P in (1, 31, 257, 2047):
+            a, b = c.loglike_grad(x[:P].contiguous(), precision=smc.PLAIN_FP64)
+            assert torch.equal(a, llp[:P]) and torch.equal(b, gp[:P]), P
+            assert torch.equal(c.loglike_grad(x[:P].contiguous(), want_grad=False, precision=smc.PLAIN_FP64), llp[:P])
     pick = np.array([0, 1, 2047, 16399])
     ll_ref, g_ref = O.loglike_grad(O.gw_target(ev), x[pick].cpu().numpy())
     assert logl_rel_err(ll[pick].cpu().numpy(), ll_ref) <= TOL["mixed"]["logl"]
@@ -63,11 +70,36 @@ def test_batch_size_changes_nothing(smc, n):
     c.close()
 
 
+def test_captured_call(smc):
+    """A call captured without its scratch (nothing can be allocated in a capture), replayed with eager work between
+    the replays; then a capture that uses it."""
+    ev = event(_spec(9000, 2, 51))
+    x = torch.tensor(synth.prior_draw(np.random.default_rng(2), 40, synth.gw_prior_for(ev)), device="cuda")
+    c = smc.Context(0)
+    c.add_event(ev)
+    ll, g = torch.zeros(40, dtype=torch.float64, device="cuda"), torch.zeros_like(x)
+    for _ in range(2):
+        graph = torch.cuda.CUDAGraph()
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.graph(graph, stream=s):
+            c.loglike_grad(x, ll, g)
+        for _ in range(3):
+            ll.zero_()
+            g.zero_()
+            graph.replay()
+            ref = c.loglike_grad(x)   # the first of these allocates the scratch
+            torch.cuda.synchronize()
+            assert torch.equal(ll, ref[0]) and torch.equal(g, ref[1])
+    c.close()
+
+
 @pytest.mark.parametrize("P", [1, 63, 65, 1000, 5003])
-def test_events_of_different_lengths(smc, P):
+@pytest.mark.parametrize("longest", [2501, 4200, 9000])
+def test_events_of_different_lengths(smc, longest, P):
     """A batch over four events of three lengths in a random map (indices beyond the events are clamped): every
     particle gets, bit for bit, what its event alone gives."""
-    evs = [event(_spec(n, 2, 60 + n)) for n in (700, 2500, 100, 2501)]
+    evs = [event(_spec(n, 2, 60 + n)) for n in (700, longest - 1, 100, longest)]
     rng = np.random.default_rng(P)
     of = rng.integers(-1, 6, P).astype(np.int32)
     x = torch.tensor(synth.prior_draw(rng, P, synth.gw_prior_for(evs[0])), device="cuda")
