@@ -236,64 +236,408 @@ __global__ __launch_bounds__(RW_THREADS) void reweight_kernel(const double* __re
     }
 }
 
-// Ancestor of particle i: first k with cum_k / cum_{P-1} > u_i (last entry forced to 1).
-// Run r = blockIdx.y draws n_draw ancestors among its P weights with key
-// seed + r and, with a run state, the iteration index state[NEXT].
-__global__ __launch_bounds__(256) void ancestors_kernel(const double* __restrict__ cum, const double* __restrict__ out,
-                                                        int P, int n_draw, uint64_t seed, uint64_t iteration,
-                                                        int32_t* __restrict__ anc, const double* __restrict__ st) {
+// ------------------------------------------------ reweighting of large pools
+// One workgroup walks a population of two thousand points quickly, a pool of many
+// populations slowly (61440 points: 1131 us, most of it serial sweeps of 120
+// exponentials a thread).  Above RW_SINGLE_MAX points the same
+// computation runs as a chain of launches over RWM_BLOCKS workgroups: the
+// maxima, RWM_PASSES passes of the bisection and the weights.  Each launch
+// begins by adding the previous one's partials in workgroup order, every
+// workgroup for itself (same order, same result), so a pass is one launch
+// without atomics or a wait between workgroups.  A pass resolves RWM_LEVELS
+// bisection levels: four wavefronts share a point's RWM_CAND grid slots, 16
+// each.  The walk compares as the sequential bisection does; only the order of
+// the sums differs from the one-workgroup kernel's.  A whole call with its draw:
+// 4096 points 115 -> 72 us, 61440 points 961 -> 105, a pool of 30 x 2048 1205 ->
+// 128; at 2048 points both take 69.  Bound by the launches: a pass is 6 to 9 us.
+constexpr int RW_SINGLE_MAX = 2560;
+constexpr int RWM_LEVELS = 6;
+constexpr int RWM_CAND = 1 << RWM_LEVELS;
+constexpr int RWM_PASSES = 8;      // 48 levels: [0, 1] is below the 1e-14 width after 47
+constexpr int RWM_BLOCKS = 128;      // most workgroups of a pass (64 up to RWM_WIDE points: fewer partials to add)
+constexpr int RWM_WIDE = 32768;
+constexpr int RWM_MAX_BLOCKS = 256;  // most workgroups of the maxima
+constexpr int RWM_THREADS = 512;
+constexpr int RWM_WAVES = RWM_THREADS / 64;
+constexpr int RWM_QUADS = RWM_CAND / RW_CAND;   // wavefronts that share a point
+constexpr int RWM_SUMS = 2 * RWM_CAND;
+static_assert(RWM_THREADS == 4 * RWM_SUMS && RWM_WAVES % RWM_QUADS == 0, "partials: four threads a sum");
+
+// The state of one run's search between launches.
+struct RwState {
+    double lo, hi, it;
+    double beta;         // < 0 while the search goes on
+    double lmax, gmax;
+    double skip;         // SKIP_* of a run that is not reweighted at all
+    double beta_prev;
+};
+
+// Scratch of one run; two states and sets of partials, by pass parity.
+struct RwScratch {
+    RwState state[2];
+    double max[RWM_MAX_BLOCKS][2];
+    double part[2][RWM_BLOCKS][RWM_SUMS];
+    double total[RWM_BLOCKS];   // weight sums of the workgroups' ranges
+};
+
+struct RwArgs {
+    const double* logl;
+    int P;
+    double beta_prev, alpha;
+    double* lofs;        // log mixture density per point (persistent sampling; NULL: standard)
+    int n_target;
+    const double* st;    // run states (NULL: none)
+    RwScratch* scr;
+    int max_blocks;      // workgroups of rwm_max_kernel
+};
+
+// Temperatures and log evidences of a pool's populations, as a kernel argument.
+constexpr int RWM_ARG_T = 96;
+struct PoolLadder {
+    int T;
+    const double* dev;   // betas, then logz (device) when T > RWM_ARG_T
+    double b[RWM_ARG_T], z[RWM_ARG_T];
+};
+
+// log((1/T) sum_t L^beta_t / Z_t) for one point of log-likelihood l.
+__device__ __forceinline__ double log_mixture(double l, const double* betas, const double* logz, int T) {
+    double m = -INFINITY;
+    for (int t = 0; t < T; ++t) m = fmax(m, betas[t] * l - logz[t]);
+    double s = 0.0;
+    for (int t = 0; t < T; ++t) s += exp(betas[t] * l - logz[t] - m);
+    return m + log(s) - log((double)T);
+}
+
+// The same over a pool's ladder; 0 for a point of no finite likelihood (not used).
+__device__ __forceinline__ double pool_mixture(double l, const PoolLadder& p) {
+    if (!(l > -INFINITY)) return 0.0;
+    return p.dev ? log_mixture(l, p.dev, p.dev + p.T, p.T) : log_mixture(l, p.b, p.z, p.T);
+}
+
+// Largest log-likelihood and base log weight of the workgroup's points; with a
+// pool, every point's log mixture density first.
+__global__ __launch_bounds__(RWM_THREADS) void rwm_max_kernel(RwArgs a, PoolLadder pool) {
+    __shared__ double red[RWM_WAVES];
     const int run = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    out += (size_t)run * OUT_SIZE;
-    if (i >= n_draw || out[OUT_SKIP] != SKIP_NONE) return;
-    cum += (size_t)run * P;
-    anc += (size_t)run * n_draw;
-    if (st) iteration = (uint64_t)st[(size_t)run * SMCGW_STATE_SIZE + SMCGW_ST_NEXT];
-    double u, u1;
-    rng_uniform2(seed + (uint64_t)run, 0u, (uint32_t)i, iteration, RNG_RESAMPLE, u, u1);
-    const double total = out[2];
-    int lo = 0, hi = P - 1;   // search the first index with normalised cum > u
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        const double c = (mid == P - 1) ? 1.0 : cum[mid] / total;
-        if (c > u) hi = mid; else lo = mid + 1;
+    const double* logl = a.logl + (size_t)run * a.P;
+    const double beta_prev = a.st ? a.st[(size_t)run * SMCGW_STATE_SIZE + SMCGW_ST_BETA] : a.beta_prev;
+    double lm = -INFINITY, gm = -INFINITY;
+    for (int i = blockIdx.x * RWM_THREADS + threadIdx.x; i < a.P; i += gridDim.x * RWM_THREADS) {
+        const double l = ll_at(logl, i);
+        lm = fmax(lm, l);
+        if (a.lofs) {
+            double o = 0.0;
+            if (l > -INFINITY) {
+                o = pool_mixture(l, pool);
+                gm = fmax(gm, beta_prev * l - o);
+            }
+            a.lofs[i] = o;
+        }
     }
-    anc[i] = lo;
+    const double lmax = block_max(lm, red), gmax = a.lofs ? block_max(gm, red) : 0.0;
+    if (threadIdx.x == 0) {
+        a.scr[run].max[blockIdx.x][0] = lmax;
+        a.scr[run].max[blockIdx.x][1] = gmax;
+    }
 }
 
-// Gather of run r = blockIdx.y: P particles drawn from its n_src candidates
-// (n_src = P for standard SMC, the pool for persistent sampling).
-__global__ __launch_bounds__(256) void gather_kernel(const int32_t* __restrict__ anc, int P, int D, int n_src,
-                                                     const double* __restrict__ x, const double* __restrict__ ll,
-                                                     const double* __restrict__ g, const int32_t* __restrict__ cy,
-                                                     double* __restrict__ xo, double* __restrict__ llo,
-                                                     double* __restrict__ go, int32_t* __restrict__ cyo,
-                                                     const double* __restrict__ out) {
+// The run's state at the start of launch `pass` (RWM_PASSES: the weights), from
+// the previous launch's state and partials; all threads, uniform.  tot:
+// RWM_SUMS doubles, red: RWM_THREADS doubles of LDS.
+__device__ RwState rwm_resume(const RwArgs& a, int run, int pass, double* tot, double* red) {
+    RwScratch& scr = a.scr[run];
+    RwState s;
+    if (pass == 0) {
+        const double* st = a.st ? a.st + (size_t)run * SMCGW_STATE_SIZE : nullptr;
+        s.beta_prev = st ? st[SMCGW_ST_BETA] : a.beta_prev;
+        s.lo = s.beta_prev; s.hi = 1.0; s.it = 0.0; s.beta = -1.0; s.skip = SKIP_NONE;
+        double lm = -INFINITY, gm = -INFINITY;
+        for (int b = threadIdx.x; b < a.max_blocks; b += RWM_THREADS) { lm = scr.max[b][0]; gm = scr.max[b][1]; }
+        static_assert(RWM_MAX_BLOCKS <= RWM_THREADS, "a thread per maximum");
+        lm = block_max(lm, red);
+        gm = block_max(gm, red);
+        s.lmax = lm;
+        s.gmax = a.lofs ? gm : 0.0;
+        if (st && (st[SMCGW_ST_DONE] != 0.0 || (st[SMCGW_ST_BETA] >= 1.0 && st[SMCGW_ST_NEXT] > 0.0))) {
+            s.skip = SKIP_DONE;
+            s.beta = s.beta_prev;
+        } else if (!(lm > -INFINITY)) {   // no particle with a finite likelihood: nothing to reweight
+            s.beta = s.beta_prev;
+        }
+    } else {
+        // sum k from four threads, each a quarter of the workgroups in order, then the quarters in order (read
+        // before the state says whether they are needed: one round trip less)
+        const int k = threadIdx.x % RWM_SUMS, q = threadIdx.x / RWM_SUMS;
+        const int n = gridDim.x, b0 = q * n / 4, b1 = (q + 1) * n / 4;
+        s = scr.state[(pass - 1) & 1];
+        double v = 0.0;
+#pragma unroll 16
+        for (int b = b0; b < b1; ++b) v += scr.part[(pass - 1) & 1][b][k];
+        if (s.beta < 0.0) {
+            red[threadIdx.x] = v;
+            __syncthreads();
+            if (q == 0) tot[k] = ((red[k] + red[RWM_SUMS + k]) + red[2 * RWM_SUMS + k]) + red[3 * RWM_SUMS + k];
+            __syncthreads();
+            // every slot's comparison at once, one per lane; the walk then only reads bits
+            const double target = a.alpha * (double)(a.lofs ? a.n_target : a.P);
+            const int lane = threadIdx.x & 63;
+            static_assert(RWM_CAND == 64, "a slot per lane");
+            const unsigned long long ok = __ballot(tot[2 * lane] * tot[2 * lane] / tot[2 * lane + 1] >= target);
+            if (pass == 1 && (ok & 1)) s.beta = 1.0;
+            int n1 = 1;
+            for (int lev = 0; lev < RWM_LEVELS && s.beta < 0.0; ++lev) {
+                if (!(s.it < 100.0 && s.hi - s.lo > 1e-14)) break;
+                const int slot = (2 * (n1 - (1 << lev)) + 1) << (RWM_LEVELS - 1 - lev);   // grid slot of node n1
+                const double mid = 0.5 * (s.lo + s.hi);
+                if ((ok >> slot) & 1) { s.lo = mid; n1 = 2 * n1 + 1; }
+                else { s.hi = mid; n1 = 2 * n1; }
+                s.it += 1.0;
+            }
+        }
+    }
+    if (s.beta < 0.0 && !(s.it < 100.0 && s.hi - s.lo > 1e-14)) s.beta = s.lo;
+    if (blockIdx.x == 0 && threadIdx.x == 0) scr.state[pass & 1] = s;
+    return s;
+}
+
+__global__ __launch_bounds__(RWM_THREADS) void rwm_pass_kernel(RwArgs a, int pass) {
+    __shared__ double tot[RWM_SUMS];
+    __shared__ double red[2 * RW_CAND * RWM_WAVES > RWM_THREADS ? 2 * RW_CAND * RWM_WAVES : RWM_THREADS];
     const int run = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= P || out[(size_t)run * OUT_SIZE + OUT_SKIP] != SKIP_NONE) return;
-    const size_t src = (size_t)run * n_src + anc[(size_t)run * P + i], dst = (size_t)run * P + i;
-    for (int k = 0; k < D; ++k) xo[dst * D + k] = x[src * D + k];
-    llo[dst] = ll[src];
-    if (g)
-        for (int k = 0; k < D; ++k) go[dst * D + k] = g[src * D + k];
-    if (cy) cyo[dst] = cy[src];
+    const RwState s = rwm_resume(a, run, pass, tot, red);
+    if (s.beta >= 0.0) return;   // settled: the launches left pass the state on
+    const double* logl = a.logl + (size_t)run * a.P;
+    // the grid lo + k h of the next RWM_LEVELS levels' midpoints; this wavefront's slots are 16 quad + 0..15
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int quad = wave % RWM_QUADS, group = wave / RWM_QUADS;
+    constexpr int GROUPS = RWM_WAVES / RWM_QUADS;
+    const double h = (s.hi - s.lo) * (1.0 / RWM_CAND);
+    const double d0 = s.lo - s.beta_prev + (double)(quad * RW_CAND) * h;
+    double v[2 * RW_CAND];
+#pragma unroll
+    for (int k = 0; k < 2 * RW_CAND; ++k) v[k] = 0.0;
+    for (int i = (blockIdx.x * GROUPS + group) * 64 + lane; i < a.P; i += gridDim.x * GROUPS * 64) {
+        const double l = ll_at(logl, i);
+        const double e = l - s.lmax;
+        if (e == -INFINITY) continue;   // zero weight at every candidate (db > 0)
+        const double g = a.lofs ? s.beta_prev * l - a.lofs[i] - s.gmax : 0.0;
+        const double r = exp(h * e);
+        double w = exp(g + d0 * e);
+        if (quad != 0) {
+            v[0] += w;
+            v[1] += w * w;
+        } else if (pass == 0) {   // slot 0 of the first pass holds beta = 1
+            const double w1 = exp(g + (1.0 - s.beta_prev) * e);
+            v[0] += w1;
+            v[1] += w1 * w1;
+        }
+#pragma unroll
+        for (int k = 1; k < RW_CAND; ++k) {
+            w *= r;
+            v[2 * k] += w;
+            v[2 * k + 1] += w * w;
+        }
+    }
+    __syncthreads();   // red's readers in rwm_resume
+    wave_totals_to<2 * RW_CAND>(v, red + wave, RWM_WAVES);
+    __syncthreads();
+    if (threadIdx.x < RWM_SUMS) {
+        const int k = threadIdx.x % (2 * RW_CAND), qd = threadIdx.x / (2 * RW_CAND);
+        double t = 0.0;
+#pragma unroll
+        for (int g = 0; g < GROUPS; ++g) t += red[k * RWM_WAVES + g * RWM_QUADS + qd];
+        a.scr[run].part[pass & 1][blockIdx.x][threadIdx.x] = t;
+    }
 }
 
+// Weights at the settled temperature: workgroup b owns the contiguous range
+// [b range, (b+1) range) and leaves the inclusive prefix sums inside it in cum,
+// its total in scr.total; out[0] and the skip flag as reweight_kernel writes
+// them (draw_kernel adds the totals and writes out[1] and out[2]).
+__global__ __launch_bounds__(RWM_THREADS) void rwm_weights_kernel(RwArgs a, int range, double* __restrict__ cum,
+                                                                  double* __restrict__ out) {
+    __shared__ double tot[RWM_SUMS];
+    __shared__ double red[RWM_THREADS];
+    __shared__ double scan[RWM_WAVES + 1];
+    const int run = blockIdx.y;
+    const RwState s = rwm_resume(a, run, RWM_PASSES, tot, red);
+    out += (size_t)run * OUT_SIZE;
+    const bool any = s.lmax > -INFINITY;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        out[0] = s.beta;
+        out[OUT_SKIP] = s.skip != SKIP_NONE ? s.skip
+                      : a.st && (!any || (!(s.beta > s.beta_prev) && s.beta_prev < 1.0)) ? SKIP_STALL : SKIP_NONE;
+    }
+    if (s.skip != SKIP_NONE) return;
+    const double* logl = a.logl + (size_t)run * a.P;
+    cum += (size_t)run * a.P;
+    const double db = s.beta - s.beta_prev;
+    auto weight = [&](int i) {
+        if (!any) return 0.0;
+        const double l = ll_at(logl, i);
+        if (!a.lofs) return incr_weight(db, l - s.lmax);
+        return l > -INFINITY ? exp(s.beta_prev * l - a.lofs[i] - s.gmax + db * (l - s.lmax)) : 0.0;
+    };
+    const int first = blockIdx.x * range, end = min(a.P, first + range);
+    const int ch = (range + RWM_THREADS - 1) / RWM_THREADS;
+    const int i0 = min(end, first + (int)threadIdx.x * ch), i1 = min(end, i0 + ch);
+    double loc = 0.0;
+    for (int i = i0; i < i1; ++i) loc += weight(i);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double inc = loc;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double t = __shfl_up(inc, o);
+        if (lane >= o) inc += t;
+    }
+    __syncthreads();   // red's readers in rwm_resume
+    if (lane == 63) red[wave] = inc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double r = 0.0;
+        for (int w = 0; w < RWM_WAVES; ++w) { scan[w] = r; r += red[w]; }
+    }
+    __syncthreads();
+    double ex = __shfl_up(inc, 1);
+    if (lane == 0) ex = 0.0;
+    double r = scan[wave] + ex;
+    for (int i = i0; i < i1; ++i) {
+        r += weight(i);
+        cum[i] = r;
+    }
+    if (i1 == end && i0 < end) a.scr[run].total[blockIdx.x] = r;   // the range's last point's thread
+    if (first >= a.P && threadIdx.x == 0) a.scr[run].total[blockIdx.x] = 0.0;
+}
+
+// Ancestors and gather.  Particle i's ancestor is the first k with
+// cum_k / cum_{n-1} > u_i among the n_src weights (the last entry counts as 1);
+// its coordinates, log-likelihood, gradient and carry go to the output arrays
+// (not the sources).  cum: inclusive prefix sums in ranges of `range` points,
+// range b offset by the totals of the ranges before it (scr NULL: one range).
+// Run r = blockIdx.y draws n_draw ancestors among its n_src weights with key
+// seed + r and, with a run state, the iteration index state[NEXT].  One
+// workgroup draws DRAW_N particles and copies their rows, one element a thread.
+constexpr int DRAW_LANES = 16;   // a draw's search: 16 probes a round, so 2048 weights take three dependent loads, not 11
+constexpr int DRAW_N = 256 / DRAW_LANES;
+struct DrawArgs {
+    const double* cum;
+    double* out;
+    int n_src, n_draw, D, range, ranges;
+    const RwScratch* scr;
+    uint64_t seed, iteration;
+    const double* st;
+    int32_t* anc;
+    const double *x, *ll, *g;
+    const int32_t* cy;
+    double *xo, *llo, *go;
+    int32_t* cyo;
+};
+
+__global__ __launch_bounds__(256) void draw_kernel(DrawArgs a) {
+    __shared__ int src[DRAW_N];
+    __shared__ double pre[RWM_BLOCKS + 1];
+    const int run = blockIdx.y, tid = threadIdx.x;
+    double* out = a.out + (size_t)run * OUT_SIZE;
+    if (out[OUT_SKIP] != SKIP_NONE) return;
+    if (a.scr) {
+        if (tid < 64) {   // prefix of the range totals, two to a lane
+            static_assert(RWM_BLOCKS <= 128, "two ranges a lane");
+            const double* tot = a.scr[run].total;
+            const double t0 = 2 * tid < a.ranges ? tot[2 * tid] : 0.0, t1 = 2 * tid + 1 < a.ranges ? tot[2 * tid + 1] : 0.0;
+            double inc = t0 + t1;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const double v = __shfl_up(inc, o);
+                if (tid >= o) inc += v;
+            }
+            double ex = __shfl_up(inc, 1);
+            if (tid == 0) ex = 0.0;
+            if (2 * tid < a.ranges) pre[2 * tid] = ex;
+            if (2 * tid + 1 < a.ranges) pre[2 * tid + 1] = ex + t0;
+            if (tid == 63) pre[a.ranges] = inc;
+            if (tid == 63 && blockIdx.x == 0) {
+                const RwState& s = a.scr[run].state[RWM_PASSES & 1];
+                out[1] = s.lmax > -INFINITY ? (s.beta - s.beta_prev) * s.lmax + s.gmax + log(inc) - log((double)a.n_src)
+                                            : -INFINITY;
+                out[2] = inc;
+            }
+        }
+        __syncthreads();
+    }
+    const int first = blockIdx.x * DRAW_N, n = min(DRAW_N, a.n_draw - first);
+    const double* cum = a.cum + (size_t)run * a.n_src;
+    const int t = tid / DRAW_LANES, j = tid % DRAW_LANES;   // this thread's draw (past n: computed, not stored) and probe
+    {
+        const uint64_t it = a.st ? (uint64_t)a.st[(size_t)run * SMCGW_STATE_SIZE + SMCGW_ST_NEXT] : a.iteration;
+        double u, u1;
+        rng_uniform2(a.seed + (uint64_t)run, 0u, (uint32_t)(first + t), it, RNG_RESAMPLE, u, u1);
+        int lo = 0, hi = a.n_src - 1;   // search the first index with normalised cum > u
+        double base = 0.0, total;
+        if (a.scr) {
+            total = pre[a.ranges];
+            int b = 0, bh = a.ranges - 1;   // the range first: its end is where the next one starts
+            while (b < bh) {
+                const int m = (b + bh) >> 1;
+                if (pre[m + 1] / total > u) bh = m; else b = m + 1;
+            }
+            base = pre[b];
+            lo = min(b * a.range, a.n_src - 1);
+            hi = min(a.n_src, lo + a.range) - 1;
+        } else {
+            total = out[2];
+        }
+        const int shift = (tid & 63) & ~(DRAW_LANES - 1);
+        // all lanes of the wavefront take part in a round while any of its draws has an interval left
+        while (__ballot(lo < hi)) {
+            const int len = hi - lo;   // indices lo .. hi - 1 decide
+            auto probe = [&](int q) {   // q = 0..15, rising
+                return len <= DRAW_LANES ? lo + q : lo + (int)(((long long)len * (q + 1)) / (DRAW_LANES + 1));
+            };
+            const int at = probe(j);
+            const bool hit = at < hi && (base + cum[at]) / total > u;
+            const unsigned hits = (unsigned)(__ballot(hit) >> shift) & ((1u << DRAW_LANES) - 1);
+            if (lo < hi) {
+                const int f = hits ? __builtin_ctz(hits) : DRAW_LANES;   // the first probe above u
+                const int nlo = f > 0 ? min(probe(f - 1) + 1, hi) : lo;
+                if (hits) hi = probe(f);
+                lo = nlo;
+            }
+        }
+        if (j == 0 && t < n) {
+            a.anc[(size_t)run * a.n_draw + first + t] = lo;
+            src[t] = lo;
+        }
+    }
+    __syncthreads();
+    const size_t s0 = (size_t)run * a.n_src, d0 = (size_t)run * a.n_draw + first;
+    for (int e = tid; e < n * a.D; e += blockDim.x) {
+        const int r = e / a.D, k = e - r * a.D;
+        const size_t from = (s0 + src[r]) * a.D + k, to = d0 * a.D + e;
+        a.xo[to] = a.x[from];
+        if (a.g) a.go[to] = a.g[from];
+    }
+    if (tid < n) {
+        a.llo[d0 + tid] = a.ll[s0 + src[tid]];
+        if (a.cy) a.cyo[d0 + tid] = a.cy[s0 + src[tid]];
+    }
+}
+
+// The drawn populations back over the sources, one element a thread.
 __global__ __launch_bounds__(256) void copy_back_kernel(int P, int D, const double* __restrict__ xo,
                                                         const double* __restrict__ llo, const double* __restrict__ go,
                                                         const int32_t* __restrict__ cyo, double* __restrict__ x,
                                                         double* __restrict__ ll, double* __restrict__ g,
                                                         int32_t* __restrict__ cy, const double* __restrict__ out) {
     const int run = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= P || out[(size_t)run * OUT_SIZE + OUT_SKIP] != SKIP_NONE) return;
-    const size_t j = (size_t)run * P + i;
-    for (int k = 0; k < D; ++k) x[j * D + k] = xo[j * D + k];
-    ll[j] = llo[j];
-    if (g)
-        for (int k = 0; k < D; ++k) g[j * D + k] = go[j * D + k];
-    if (cy) cy[j] = cyo[j];
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x, n = (size_t)P * D;
+    if (i >= n || out[(size_t)run * OUT_SIZE + OUT_SKIP] != SKIP_NONE) return;
+    x[run * n + i] = xo[run * n + i];
+    if (g) g[run * n + i] = go[run * n + i];
+    if (i < (size_t)P) {
+        const size_t j = (size_t)run * P + i;
+        ll[j] = llo[j];
+        if (cy) cy[j] = cyo[j];
+    }
 }
 
 // Run states after the reweighting (one thread per run): the temperature,
@@ -527,15 +871,6 @@ __global__ __launch_bounds__(REC_THREADS) void record_kernel(int P, const int32_
     }
 }
 
-// log((1/T) sum_t L^beta_t / Z_t) for one point of log-likelihood l.
-__device__ __forceinline__ double log_mixture(double l, const double* betas, const double* logz, int T) {
-    double m = -INFINITY;
-    for (int t = 0; t < T; ++t) m = fmax(m, betas[t] * l - logz[t]);
-    double s = 0.0;
-    for (int t = 0; t < T; ++t) s += exp(betas[t] * l - logz[t] - m);
-    return m + log(s) - log((double)T);
-}
-
 // Sample recycling (Sec. 5, "Samples recycling").  The populations left by
 // the mutations of iterations t = 1..T form a pool read as draws of the
 // mixture (1/T) sum_t p_t, p_t = L^beta_t pi / Z_t.  Point i's weight for the
@@ -558,12 +893,11 @@ __global__ __launch_bounds__(256) void recycle_weights_kernel(const double* __re
 // Log mixture density of the pool at every point (persistent sampling):
 // lofs_i = log((1/T) sum_t L_i^beta_t / Z_t); entries of non-finite logL are
 // not used.
-__global__ __launch_bounds__(256) void pool_logmix_kernel(const double* __restrict__ logl, int n, int T,
-                                                          const double* __restrict__ bz, double* __restrict__ lofs) {
+__global__ __launch_bounds__(256) void pool_logmix_kernel(const double* __restrict__ logl, int n, PoolLadder pool,
+                                                          double* __restrict__ lofs) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const double l = logl[i];
-    lofs[i] = l > -INFINITY ? log_mixture(l, bz, bz + T, T) : 0.0;
+    lofs[i] = pool_mixture(logl[i], pool);
 }
 
 // Rejection sampling over the pool in one workgroup: point i is kept when
@@ -721,6 +1055,53 @@ extern "C" int smcgw_mass_matrix(smcgw_ctx* c, int P, int D, const double* theta
 }
 
 namespace smcgw {
+static size_t rw_scratch_bytes(int n_runs, int P) { return P > RW_SINGLE_MAX ? n_runs * sizeof(RwScratch) : 0; }
+
+// Weights of n_runs runs of P points on the context's stream: cum, out[0] and
+// the skip flags; a pool (one run) passes lofs, its ladder and n_target.
+// Returns what queue_draw needs of them.
+static DrawArgs queue_weights(smcgw_ctx* c, int n_runs, int P, double beta_prev, double alpha, const double* logl,
+                              double* lofs, const PoolLadder* pool, int n_target, double* cum, double* out,
+                              RwScratch* scr, const double* st) {
+    DrawArgs d{};
+    d.cum = cum;
+    d.out = out;
+    d.n_src = P;
+    if (P <= RW_SINGLE_MAX) {
+        if (lofs)
+            hipLaunchKernelGGL(pool_logmix_kernel, dim3((P + 255) / 256), dim3(256), 0, c->stream, logl, P, *pool,
+                               lofs);
+        hipLaunchKernelGGL(reweight_kernel, dim3(1, n_runs), dim3(RW_THREADS), 0, c->stream, logl, P, beta_prev, alpha,
+                           (const double*)lofs, n_target, cum, out, st);
+        return d;
+    }
+    const int blocks = P <= RWM_WIDE ? 64 : RWM_BLOCKS;
+    const RwArgs a{logl, P, beta_prev, alpha, lofs, n_target, st, scr,
+                   std::min(RWM_MAX_BLOCKS, (P + RWM_THREADS - 1) / RWM_THREADS)};
+    const dim3 grid(blocks, n_runs), block(RWM_THREADS);
+    hipLaunchKernelGGL(rwm_max_kernel, dim3(a.max_blocks, n_runs), block, 0, c->stream, a, pool ? *pool : PoolLadder{});
+    for (int pass = 0; pass < RWM_PASSES; ++pass) hipLaunchKernelGGL(rwm_pass_kernel, grid, block, 0, c->stream, a, pass);
+    d.range = (P + blocks - 1) / blocks;
+    d.ranges = blocks;
+    d.scr = scr;
+    hipLaunchKernelGGL(rwm_weights_kernel, grid, block, 0, c->stream, a, d.range, cum, out);
+    return d;
+}
+
+static void queue_draw(smcgw_ctx* c, int n_runs, DrawArgs d, int n_draw, int D, uint64_t seed, uint64_t iteration,
+                       const double* st, int32_t* anc, const double* x, const double* ll, const double* g,
+                       const int32_t* cy, double* xo, double* llo, double* go, int32_t* cyo) {
+    d.n_draw = n_draw;
+    d.D = D;
+    d.seed = seed;
+    d.iteration = iteration;
+    d.st = st;
+    d.anc = anc;
+    d.x = x; d.ll = ll; d.g = g; d.cy = cy;
+    d.xo = xo; d.llo = llo; d.go = go; d.cyo = cyo;
+    hipLaunchKernelGGL(draw_kernel, dim3((n_draw + DRAW_N - 1) / DRAW_N, n_runs), dim3(256), 0, c->stream, d);
+}
+
 // Reweighting, temperature search, resampling and gather of n_runs runs of P
 // particles on the context's stream (run r: particles [r P, (r+1) P)); out
 // (device, [n_runs][OUT_SIZE]) holds beta_next, the evidence increment, the
@@ -740,7 +1121,8 @@ int queue_reweight_resample(smcgw_ctx* c, int n_runs, int P, int D, double beta_
     const size_t off_ll = off_x + n * D * sizeof(double);
     const size_t off_g = off_ll + n * sizeof(double);
     const size_t off_cy = off_g + n * D * sizeof(double);
-    const size_t bytes = off_cy + n * sizeof(int32_t);
+    const size_t off_rw = (off_cy + n * sizeof(int32_t) + 7) & ~(size_t)7;
+    const size_t bytes = off_rw + rw_scratch_bytes(n_runs, P);
     char* s = (char*)sampler_scratch(c, bytes);
     if (!s) return SMCGW_ERR_OOM;
     double* out = (double*)s;
@@ -749,13 +1131,10 @@ int queue_reweight_resample(smcgw_ctx* c, int n_runs, int P, int D, double beta_
     double* llo = (double*)(s + off_ll);
     double* go = (double*)(s + off_g);
     int32_t* cyo = (int32_t*)(s + off_cy);
-    hipLaunchKernelGGL(reweight_kernel, dim3(1, n_runs), dim3(RW_THREADS), 0, c->stream, logl, P, beta_prev, alpha,
-                       (const double*)nullptr, P, cum, out, (const double*)st);
-    const dim3 g((P + 255) / 256, n_runs), b(256);
-    hipLaunchKernelGGL(ancestors_kernel, g, b, 0, c->stream, cum, out, P, P, seed, iteration, ancestors,
-                       (const double*)st);
-    hipLaunchKernelGGL(gather_kernel, g, b, 0, c->stream, ancestors, P, D, P, theta, logl, grad, carry, xo, llo, go,
-                       cyo, (const double*)out);
+    RwScratch* scr = (RwScratch*)(s + off_rw);
+    const DrawArgs d = queue_weights(c, n_runs, P, beta_prev, alpha, logl, nullptr, nullptr, 0, cum, out, scr, st);
+    queue_draw(c, n_runs, d, P, D, seed, iteration, st, ancestors, theta, logl, grad, carry, xo, llo, go, cyo);
+    const dim3 g(((size_t)P * D + 255) / 256, n_runs), b(256);
     hipLaunchKernelGGL(copy_back_kernel, g, b, 0, c->stream, P, D, xo, llo, go, cyo, theta, logl, grad, carry,
                        (const double*)out);
     if (st)
@@ -769,7 +1148,7 @@ int queue_reweight_resample(smcgw_ctx* c, int n_runs, int P, int D, double beta_
 size_t reweight_scratch_bytes(int n_runs, int P, int D) {
     const size_t n = (size_t)n_runs * P;
     return 64 * sizeof(double) * ((n_runs * OUT_SIZE + 63) / 64) + n * (2 * D + 2) * sizeof(double) +
-           n * sizeof(int32_t);
+           ((n * sizeof(int32_t) + 7) & ~(size_t)7) + rw_scratch_bytes(n_runs, P);
 }
 
 // Block partials of the population covariance for n_runs runs of P particles.
@@ -909,7 +1288,8 @@ extern "C" int smcgw_ps_reweight_resample(smcgw_ctx* c, int T, int N, int D, con
     const size_t off_x = off_cum + (size_t)n * sizeof(double);
     const size_t off_ll = off_x + (size_t)N * D * sizeof(double);
     const size_t off_g = off_ll + (size_t)N * sizeof(double);
-    const size_t bytes = off_g + (size_t)N * D * sizeof(double);
+    const size_t off_rw = off_g + (size_t)N * D * sizeof(double);
+    const size_t bytes = off_rw + rw_scratch_bytes(1, n);
     char* s = (char*)sampler_scratch(c, bytes);
     double* hp = pinned(c);
     if (!s || !hp) return SMCGW_ERR_OOM;
@@ -917,22 +1297,40 @@ extern "C" int smcgw_ps_reweight_resample(smcgw_ctx* c, int T, int N, int D, con
     double* bz = (double*)(s + off_bz);
     double* lofs = (double*)(s + off_lofs);
     double* cum = (double*)(s + off_cum);
-    double* xo = (double*)(s + off_x);
-    double* llo = (double*)(s + off_ll);
-    double* go = (double*)(s + off_g);
-    if (hipMemcpyAsync(bz, betas_host, T * sizeof(double), hipMemcpyHostToDevice, c->stream) ||
-        hipMemcpyAsync(bz + T, logz_host, T * sizeof(double), hipMemcpyHostToDevice, c->stream))
-        return SMCGW_ERR_HIP;
-    hipLaunchKernelGGL(pool_logmix_kernel, dim3((n + 255) / 256), dim3(256), 0, c->stream, logl_pool, n, T, bz, lofs);
-    hipLaunchKernelGGL(reweight_kernel, dim3(1), dim3(RW_THREADS), 0, c->stream, logl_pool, n, beta_prev, alpha,
-                       (const double*)lofs, N, cum, out, (const double*)nullptr);
-    const dim3 g((N + 255) / 256), b(256);
-    hipLaunchKernelGGL(ancestors_kernel, g, b, 0, c->stream, cum, out, n, N, seed, iteration, ancestors,
-                       (const double*)nullptr);
-    hipLaunchKernelGGL(gather_kernel, g, b, 0, c->stream, ancestors, N, D, n, theta_pool, logl_pool, grad_pool,
-                       (const int32_t*)nullptr, xo, llo, go, (int32_t*)nullptr, (const double*)out);
-    hipLaunchKernelGGL(copy_back_kernel, g, b, 0, c->stream, N, D, xo, llo, go, (const int32_t*)nullptr, theta, logl,
-                       grad, (int32_t*)nullptr, (const double*)out);
+    PoolLadder pool{};
+    pool.T = T;
+    if (T <= RWM_ARG_T) {
+        std::copy_n(betas_host, T, pool.b);
+        std::copy_n(logz_host, T, pool.z);
+    } else {
+        if (hipMemcpyAsync(bz, betas_host, T * sizeof(double), hipMemcpyHostToDevice, c->stream) ||
+            hipMemcpyAsync(bz + T, logz_host, T * sizeof(double), hipMemcpyHostToDevice, c->stream))
+            return SMCGW_ERR_HIP;
+        pool.dev = bz;
+    }
+    const DrawArgs d = queue_weights(c, 1, n, beta_prev, alpha, logl_pool, lofs, &pool, N, cum, out,
+                                     (RwScratch*)(s + off_rw), nullptr);
+    // straight into the caller's arrays, unless they reach into the pool being read
+    auto apart = [](const void* a, size_t na, const void* b, size_t nb) {
+        return (const char*)a + na <= (const char*)b || (const char*)b + nb <= (const char*)a;
+    };
+    const size_t row = (size_t)D * sizeof(double);
+    bool direct = true;
+    const void* src[3] = {theta_pool, logl_pool, grad_pool};
+    const size_t src_n[3] = {n * row, n * sizeof(double), n * row};
+    const void* dst[3] = {theta, logl, grad};
+    const size_t dst_n[3] = {N * row, N * sizeof(double), N * row};
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j)
+            if (src[i] && dst[j] && !apart(src[i], src_n[i], dst[j], dst_n[j])) direct = false;
+    double* xo = direct ? theta : (double*)(s + off_x);
+    double* llo = direct ? logl : (double*)(s + off_ll);
+    double* go = direct ? grad : (double*)(s + off_g);
+    queue_draw(c, 1, d, N, D, seed, iteration, nullptr, ancestors, theta_pool, logl_pool, grad_pool, nullptr, xo, llo,
+               go, nullptr);
+    if (!direct)
+        hipLaunchKernelGGL(copy_back_kernel, dim3(((size_t)N * D + 255) / 256), dim3(256), 0, c->stream, N, D, xo, llo, go,
+                           (const int32_t*)nullptr, theta, logl, grad, (int32_t*)nullptr, (const double*)out);
     if (hipGetLastError() != hipSuccess) return SMCGW_ERR_HIP;
     if (hipMemcpyAsync(hp, out, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream) ||
         hipStreamSynchronize(c->stream))
