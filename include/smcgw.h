@@ -349,10 +349,11 @@ int smcgw_local_metric(smcgw_ctx *ctx, int P, int D, const double *theta, double
  * (device) is a predicted leapfrog count per particle, for callers that know
  * it (e.g. forced depths): particles start in descending order of
  * floor(log2(hint)) so that the longest trees do not start last.  Without it
- * (NULL) the particles are dealt to the GPU's XCDs in stripes of 16
- * neighbouring indices, each XCD's slots taking their own stripes first and
- * the others' after, so that neighbouring particles, whose inputs and
- * outputs share cache lines, pass through one L2.  The hint changes only
+ * (NULL) the particles are dealt to the GPU's XCDs, in stripes of 16
+ * neighbouring indices when there are more than the launch holds at once,
+ * each XCD's slots taking their own first and the others' after, so that
+ * neighbouring particles, whose inputs and outputs share cache lines, mostly
+ * pass through one L2.  The hint changes only
  * the schedule; every output is the same with or without it.  Per-particle diagnostics (device, each may be NULL): doublings
  * done, leapfrog steps, divergence flag, mean acceptance statistic. */
 int smcgw_nuts_step(smcgw_ctx *ctx, int P, int D, double *theta, double *logl, double *grad, const double *chol,
@@ -490,9 +491,11 @@ int smcgw_recycle(smcgw_ctx *ctx, int T, int N, const double *logl, const double
 /* ------------------------------------------------------------ options
  * Launch-shape options of a context (chosen by the autotuner or by hand).
  *   SMCGW_OPT_NUTS_WAVES: wavefronts that share one particle's bin loop in the
- *     persistent NUTS kernel (2, 4, 6 or 8; 0 = the library default: 2 when
- *     no event of the context has more than 1024 padded bins, as with
- *     relative-binning events, else 4).
+ *     persistent NUTS kernel (2, 4, 6 or 8; 0 = the library default, 4).
+ *     With 4, a launch of more than 1280 particles on events of at most 1024
+ *     padded bins, as with relative binning, advances four particles in each
+ *     workgroup (the outputs are the same either way; an event of at most two
+ *     blocks of 512 bins has the same outputs at every width).
  *   SMCGW_OPT_NUTS_PRIORITY: 1 (default) raises the issue priority of a
  *     slot's wavefronts as its tree deepens, so the longest trajectories of
  *     a transition run ahead of the short ones that share their compute

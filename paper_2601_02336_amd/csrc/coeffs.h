@@ -170,8 +170,10 @@ __device__ __forceinline__ double extrinsic_angle(const DevEvent& ev, const doub
     return k == ANG_PHI ? th[P_RA] - ev.gmst : k == ANG_DEC ? th[P_DEC] : k == ANG_PSI2 ? 2.0 * th[P_PSI] : th[P_IOTA];
 }
 
+constexpr double CAMP_FACTOR = 0.45643546458763842789 /* sqrt(5/24) */ * 0.46619407703541166 /* pi^-2/3 */;
+
 __device__ __forceinline__ double extrinsic_amplitude(const DevEvent& ev, const double th[NPAR]) {
-    const double camp = 0.45643546458763842789 /* sqrt(5/24) */ * 0.46619407703541166 /* pi^-2/3 */
+    const double camp = CAMP_FACTOR
                       * exp((5.0 / 6.0) * log(th[P_MC] * ev.t_sun)) * ev.c_light / (th[P_DL] * ev.mpc_m);
     return camp * ev.u_scale;
 }
