@@ -27,220 +27,275 @@
 
 namespace smcgw {
 
-constexpr int MET_THREADS = 128;   // two wavefronts per particle
-constexpr int NPAIR = NPAR * (NPAR + 1) / 2;
-static_assert(NPAIR <= MET_THREADS && NPAR * NGEO <= MET_THREADS, "one thread per pair and per Jacobian entry");
+// Four particles per wavefront, 16 lanes each: a lane is a tangent or a detector in
+// the prologue, a row of W_d, a column of F and a row of the factor in turn.  Nothing
+// crosses the groups and a workgroup is one wavefront, so there are no barriers, and
+// the matrices stay in registers but for the column that a step of the factorisation
+// broadcasts.  What bounds it is the chain of one particle (29000 cycles: prologue
+// 9800, F 9400, factor 3300, inverse 2300, the rest loads and stores), so particles in flight are
+// what counts: eight workgroups fit a compute unit, 32 particles, where a workgroup of
+// two wavefronts for each held 12 and spent most instructions on a few lanes.  3 x 8033
+// bins' event, 11 parameters, 6144 particles: 71.6 -> 19.8 us a call, 64: 21.2 -> 14.3
+// (of which 9 are the call).
+constexpr int SUB_LANES = 16;
+constexpr int MET_SUBS = 64 / SUB_LANES;
+static_assert(SUB_LANES == MAXDIM && NPAR <= SUB_LANES && NGEO <= SUB_LANES && 2 * MAXDET < SUB_LANES, "lane roles");
 
 struct PrecDesc {
     double prec[MAXDIM];   // prior precision of each sampled coordinate
 };
 
-struct MetricShared {
-    double cb[CB_SIZE];
-    double W[MAXDET * NGEO * NGEO];
-    double gam[NPAR][NGEO];   // d gamma_a / d theta_k for the current detector
-    double wg[NPAR][NGEO];    // W_d gamma_k
+// What F is formed from.
+struct MetricInput {
+    double th[NPAR], cb[CB_SIZE];
+    double wg[NPAR][NGEO];   // W_d gamma_k of the current detector
     double dr[NPAR], di[NPAR], s[NPAR];
-    double F[NPAR * NPAR];
-    double M[MAXDIM * MAXDIM], R[MAXDIM * MAXDIM], Y[MAXDIM * MAXDIM];
     ExtAngles ang;
 };
 
-// Phase derivative of source parameter k on phase function a (cycles),
-// detector d.  The phase is c_0 + sum_b c_{1+b} B_b(f) + f tau_d with
-// c_0 containing -phi_c / (2 pi) and tau_d = t_c + delay_d(ra, dec).
-__device__ __forceinline__ double phase_jac(const double* cb, int d, int k, int a) {
-    if (k < 4) return a < NCOEF ? cb[CB_DC + 4 * a + k] : 0.0;
-    if (a == 0) return k == P_PHIC ? -1.0 / TWO_PI : 0.0;
-    if (a != NGEO - 1) return 0.0;
-    return k == P_TC ? 1.0 : k == P_RA ? cb[CB_DTAU + 2 * d] : k == P_DEC ? cb[CB_DTAU + 2 * d + 1] : 0.0;
+struct MetricState {
+    union {
+        MetricInput in;
+        double Rt[MAXDIM][MAXDIM];   // the factor's columns
+    };
+    union {
+        double F[MAXDIM][MAXDIM];
+        double out[MAXDIM * MAXDIM];
+    };
+    double diag[MAXDIM];
+};
+
+// Groups start 16 of the 64 banks apart: each reads its own copy of an entry.
+struct MetricSub : MetricState {
+    double pad[8 + (256 - (sizeof(MetricState) + 64) % 256 + 64) % 256 / 8];
+};
+static_assert(sizeof(MetricSub) % 256 == 64, "bank offset of the groups");
+
+// Order of one wavefront's LDS accesses across its lanes.
+__device__ __forceinline__ void sub_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-// Pair index e of the upper triangle (k <= l), row by row.
-__device__ __forceinline__ void pair_of(int e, int& k, int& l) {
-    k = 0;
-    while (e >= NPAR - k) { e -= NPAR - k; ++k; }
-    l = k + e;
-}
-
-// Lower Cholesky factor Lo of the D x D matrix A (row stride MAXDIM), one
-// row per thread; false (uniform over the workgroup) when a pivot is not
-// positive.  Each entry is formed in the textbook order: the matrix entry
-// minus the products of the finished columns, k ascending.
-__device__ bool block_cholesky(const double* A, double* Lo, int D, int tid) {
-    for (int i = tid; i < MAXDIM * MAXDIM; i += MET_THREADS) Lo[i] = 0.0;
-    __syncthreads();
-    for (int j = 0; j < D; ++j) {
-        double sjj = A[j * MAXDIM + j];
-        for (int k = 0; k < j; ++k) sjj -= Lo[j * MAXDIM + k] * Lo[j * MAXDIM + k];
-        if (!(sjj > 0.0)) return false;
-        const double ljj = sqrt(sjj);
-        if (tid > j && tid < D) {
-            double t = A[tid * MAXDIM + j];
-            for (int k = 0; k < j; ++k) t -= Lo[tid * MAXDIM + k] * Lo[j * MAXDIM + k];
-            Lo[tid * MAXDIM + j] = t / ljj;
-        }
-        if (tid == j) Lo[j * MAXDIM + j] = ljj;
-        __syncthreads();
+// M = beta F + diag(prior precision) over the sampled coordinates (coordinate a of
+// the sample being row idx[a] of F), then the lower Cholesky factor of M^{-1} into
+// chol[p], or the fallback where M or the factor is not numerically positive definite.
+// The factor comes from the order-reversed matrix: with J the reversal permutation and
+// J M J = R R^T, M^{-1} = (J R^-T J)(J R^-T J)^T and J R^-T J is lower triangular with
+// a positive diagonal, so it is that factor; it needs one Cholesky and one triangular
+// inverse.  Lane i holds row i of J M J, then column i of R^{-1}.  An entry takes its
+// products with the finished columns in column order, as in the textbook's row-by-row
+// form; only they are subtracted as the columns come, for every entry at once.
+// N >= D rows and columns are factored: those beyond D are the identity's, so the steps
+// need no branches and the reads of the next ones are under way early.  own: coordinate
+// D-1-lane's row of F, prec: its prior precision.
+template <int N>
+__device__ __forceinline__ void finish_metric(MetricSub& S, const int* idx, int D, double beta, int own, double prec,
+                                              const double* __restrict__ fallback, double* __restrict__ chol,
+                                              double* __restrict__ fisher, int32_t* __restrict__ status, int p,
+                                              int lane) {
+    if (fisher)
+        for (int i = lane; i < D * D; i += SUB_LANES) fisher[(size_t)p * D * D + i] = S.F[idx[i / D]][idx[i % D]];
+    double A[N], dg[N];   // row `lane`; the diagonal, which every lane follows to have the pivots at hand
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const double f = S.F[own][idx[max(D - 1 - j, 0)]];
+        const double v = fma(beta, f, j == lane ? prec : 0.0);
+        A[j] = j < D && lane < D ? v : j == lane ? 1.0 : 0.0;
+        if (j == lane) S.diag[lane] = A[j];
     }
-    return true;
-}
-
-// M = beta F + diag(prior precision) over the sampled coordinates (F with
-// row stride fs, coordinate a of the sample being row idx[a]), then the lower
-// Cholesky factor of M^{-1} into chol[p], or the fallback where M or the
-// factor is not numerically positive definite.  The factor comes from the
-// order-reversed matrix: with J the reversal permutation and J M J = R R^T,
-// M^{-1} = (J R^-T J)(J R^-T J)^T and J R^-T J is lower triangular with a
-// positive diagonal, so it is that factor; it needs one Cholesky and one
-// triangular inverse.
-__device__ void finish_metric(MetricShared& S, const double* F, int fs, const int* idx, int D, double beta,
-                              const PrecDesc& pd,
-                              const double* __restrict__ fallback, double* __restrict__ chol,
-                              double* __restrict__ fisher, int32_t* __restrict__ status, int p, int tid) {
-    // J M J (rows and columns in reverse order)
-    for (int i = tid; i < MAXDIM * MAXDIM; i += MET_THREADS) {
-        const int a = i / MAXDIM, b = i % MAXDIM;
-        double v = 0.0;
-        if (a < D && b < D) {
-            const int ra = D - 1 - a, rb = D - 1 - b;
-            const double f = F[idx[ra] * fs + idx[rb]];
-            v = beta * f + (a == b ? pd.prec[ra] : 0.0);
-            if (fisher) fisher[(size_t)p * D * D + ra * D + rb] = f;
+    sub_fence();
+#pragma unroll
+    for (int j = 0; j < N; ++j) dg[j] = S.diag[j];
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        ok = ok && dg[k] > 0.0;
+        const double lkk = sqrt(dg[k]);
+        const double l = lane == k ? lkk : A[k] / lkk;
+        S.Rt[k][lane] = l;
+        sub_fence();
+#pragma unroll
+        for (int j = k + 1; j < N; ++j) {
+            const double lj = S.Rt[k][j];
+            dg[j] = fma(-lj, lj, dg[j]);
+            A[j] = fma(-l, lj, A[j]);
         }
-        S.M[i] = v;
     }
-    __syncthreads();
-    bool ok = block_cholesky(S.M, S.R, D, tid);
+    // X = R^{-1}, lane c column c by forward substitution
+    double X[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) X[r] = r == lane ? 1.0 : 0.0;
+    bool finite = true;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        X[k] = k < lane ? 0.0 : X[k] / S.Rt[k][k];
+        finite = finite && isfinite(X[k]);
+#pragma unroll
+        for (int r = k + 1; r < N; ++r) X[r] = fma(-S.Rt[k][r], X[k], X[r]);
+    }
+    // a non-finite entry takes the fallback too
+    const unsigned long long bad = __ballot(lane < D && !finite);
+    ok = ok && !(bad >> (threadIdx.x & ~(SUB_LANES - 1)) & ((1ull << SUB_LANES) - 1));
+    if (status && lane == 0) status[p] = ok ? 0 : 1;
+    // factor L[i][j] = X[D-1-j][D-1-i]: lane c holds row D-1-c
+    if (lane < D) {
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+            if (r < D) S.out[(D - 1 - lane) * D + D - 1 - r] = X[r];
+    }
+    sub_fence();
+    double* o = chol + (size_t)p * D * D;
     if (ok) {
-        // X = R^{-1}, thread c solving column c by forward substitution
-        if (tid < D) {
-            const int c = tid;
-            for (int r = 0; r < D; ++r) {
-                double v = (r == c) ? 1.0 : 0.0;
-                for (int k = c; k < r; ++k) v -= S.R[r * MAXDIM + k] * S.Y[k * MAXDIM + c];
-                S.Y[r * MAXDIM + c] = r < c ? 0.0 : v / S.R[r * MAXDIM + r];
-            }
-        }
-        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < N * N; i += SUB_LANES)
+            if (i + lane < D * D) o[i + lane] = S.out[i + lane];
+    } else {
+        for (int i = lane; i < D * D; i += SUB_LANES) o[i] = fallback ? fallback[i] : (i / D == i % D ? 1.0 : 0.0);
     }
-    // factor L[i][j] = X[D-1-j][D-1-i]; a non-finite entry takes the fallback too
-    bool bad_entry = false;
-    if (ok)
-        for (int i = tid; i < D * D; i += MET_THREADS) {
-            const double v = S.Y[(D - 1 - i % D) * MAXDIM + (D - 1 - i / D)];
-            bad_entry |= !isfinite(v);
-        }
-    ok = ok && !__syncthreads_or(bad_entry);
-    for (int i = tid; i < D * D; i += MET_THREADS) {
-        const int a = i / D, b = i % D;
-        chol[(size_t)p * D * D + i] = ok ? S.Y[(D - 1 - b) * MAXDIM + (D - 1 - a)]
-                                    : fallback ? fallback[i] : (a == b ? 1.0 : 0.0);
-    }
-    if (status && tid == 0) status[p] = ok ? 0 : 1;
 }
 
-// One workgroup of two wavefronts per particle.  The coefficient block is
-// built as in the NUTS leaf: the intrinsic part with one tangent per lane on
-// wavefront 0, the extrinsic part (shared sin / cos in parallel lanes, then
-// one detector and tangent per lane) on wavefront 1.
-__global__ __launch_bounds__(MET_THREADS) void local_metric_kernel(const DevEvent* __restrict__ evs, int n_events,
-                                                                  const int32_t* __restrict__ ev_of_p, ParamMap pm,
-                                                                  PrecDesc pd, int P, const double* __restrict__ theta,
-                                                                  double beta_host, const double* __restrict__ beta_dev,
-                                                                  const double* __restrict__ fallback,
-                                                                  double* __restrict__ chol, double* __restrict__ fisher,
-                                                                  int32_t* __restrict__ status,
-                                                                  const double* __restrict__ st, int run_size) {
-    __shared__ MetricShared S;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int p = blockIdx.x;
+// The coefficient block is built as in the NUTS leaf: the intrinsic part with one
+// tangent per lane, shared sin / cos in parallel lanes, then one detector and tangent
+// per lane.
+__global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __restrict__ evs, int n_events,
+                                                          const int32_t* __restrict__ ev_of_p, ParamMap pm,
+                                                          PrecDesc pd, int P, const double* __restrict__ theta,
+                                                          double beta_host, const double* __restrict__ beta_dev,
+                                                          const double* __restrict__ fallback,
+                                                          double* __restrict__ chol, double* __restrict__ fisher,
+                                                          int32_t* __restrict__ status,
+                                                          const double* __restrict__ st, int run_size) {
+    __shared__ MetricSub sub[MET_SUBS];
+    const int lane = threadIdx.x % SUB_LANES;
+    MetricSub& S = sub[threadIdx.x / SUB_LANES];
+    const int p = blockIdx.x * MET_SUBS + threadIdx.x / SUB_LANES;
     const int D = pm.dim;
+    if (p >= P) return;
     // independent runs: particle p belongs to run p / run_size, whose state gives beta; a finished run is skipped
     const int run = st ? p / run_size : 0;
     if (st && st[(size_t)run * SMCGW_STATE_SIZE + SMCGW_ST_DONE] != 0.0) return;
     if (st && fallback) fallback += (size_t)run * D * D;
     const DevEvent& ev = evs[event_index(ev_of_p, p, n_events)];
     const int n_det = ev.n_det;
+    const double* wmom = ev.wmom;
+    MetricInput& in = S.in;
+    // coordinate D-1-lane, as the factorisation orders them (read here, ahead of its use)
+    const int own = lane < D ? pm.idx[D - 1 - lane] : 0;
+    const double prec = lane < D ? pd.prec[D - 1 - lane] : 0.0;
 
-    for (int i = tid; i < n_det * NGEO * NGEO; i += MET_THREADS) S.W[i] = ev.wmom[i];
-    if (wave == 0 && lane < 4) {
-        double th[NPAR];
-        expand_params(pm, theta + (size_t)p * D, th);
-        prep_intrinsic_n<1>(ev, th, S.cb, lane, lane == 0);
-    } else if (wave == 1) {
-        double th[NPAR];
-        if (lane <= 2 * MAXDET) expand_params(pm, theta + (size_t)p * D, th);
-        if (lane < ANG_COUNT) {
-            double sn, cs;
-            sincos(extrinsic_angle(ev, th, lane), &sn, &cs);
-            S.ang.sc[lane][0] = sn;
-            S.ang.sc[lane][1] = cs;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        if (lane < 2 * MAXDET) {
-            const ExtAngles ang = S.ang;
-            const int k = lane / MAXDET;
-            prep_extrinsic_det_n<1>(ev, th, ang, S.cb, lane - k * MAXDET, k, k == 0);
-        } else if (lane == 2 * MAXDET) {
-            prep_extrinsic_common(ev, th, S.cb);
-        }
+    int from = -1;   // the coordinate that sets parameter `lane` (the last one that names it)
+    for (int k = 0; k < D; ++k) from = pm.idx[k] == lane ? k : from;
+    const double x = theta[(size_t)p * D + min(lane, D - 1)], xp = __shfl(x, max(from, 0), SUB_LANES);
+    if (lane < NPAR) in.th[lane] = from >= 0 ? xp : pm.fixed[lane];
+    sub_fence();
+    if (lane < 4) prep_intrinsic_n<1>(ev, in.th, in.cb, lane, lane == 0);
+    if (lane < ANG_COUNT) {
+        double sn, cs;
+        sincos(extrinsic_angle(ev, in.th, lane), &sn, &cs);
+        in.ang.sc[lane][0] = sn;
+        in.ang.sc[lane][1] = cs;
     }
-    __syncthreads();
-    const double amp = S.cb[CB_AMP];
+    sub_fence();
+    if (lane < 2 * MAXDET) {
+        const ExtAngles ang = in.ang;
+        const int k = lane / MAXDET;
+        prep_extrinsic_det_n<1>(ev, in.th, ang, in.cb, lane - k * MAXDET, k, k == 0);
+    } else if (lane == 2 * MAXDET) {
+        prep_extrinsic_common(ev, in.th, in.cb);
+    }
+    sub_fence();
+    const double* cb = in.cb;
+    const double amp = cb[CB_AMP];
 
-    double acc = 0.0;   // F entry of pair tid (k <= l)
+    // gamma_a derives the phase c_0 + sum_b c_{1+b} B_b(f) + f tau_d, with c_0 containing
+    // -phi_c / (2 pi) and tau_d = t_c + delay_d(ra, dec), so it is sparse: the coefficients' derivatives for the four intrinsic
+    // parameters, one entry for ra, dec, t_c (of f) and phi_c (constant), none for d_L, iota and psi.
+    // Lane a takes row a of W, then lane l the column F_kl, k <= l.
+    const int la = min(lane, NGEO - 1), l = min(lane, NPAR - 1);
+    double acc[NPAR], wnext[NGEO];   // the next detector's row is under way
+#pragma unroll
+    for (int k = 0; k < NPAR; ++k) acc[k] = 0.0;
+#pragma unroll
+    for (int b = 0; b < NGEO; ++b) wnext[b] = wmom[la * NGEO + b];
+    double dc[NCOEF][4];
+#pragma unroll
+    for (int b = 0; b < NCOEF; ++b)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dc[b][k] = cb[CB_DC + 4 * b + k];
+#pragma unroll 1
     for (int d = 0; d < n_det; ++d) {
-        const double* W = S.W + d * NGEO * NGEO;
-        const double qr = amp * S.cb[CB_PR + d], qi = amp * S.cb[CB_PI + d];
-        if (tid < NPAR * NGEO) S.gam[tid / NGEO][tid % NGEO] = phase_jac(S.cb, d, tid / NGEO, tid % NGEO);
-        if (tid < NPAR) {
-            double xr = 0.0, xi = 0.0;
-            if (tid == P_MC || tid == P_DL) {
-                const double g = tid == P_MC ? S.cb[CB_DLNCA_MC] : S.cb[CB_DLNCA_DL];
-                xr = g * qr;
-                xi = g * qi;
-            } else if (tid == P_IOTA || tid == P_PSI || tid == P_RA || tid == P_DEC) {
-                const int m = tid == P_IOTA ? 0 : tid == P_PSI ? 1 : tid == P_RA ? 2 : 3;
-                xr = amp * S.cb[CB_DPR + 4 * d + m];
-                xi = amp * S.cb[CB_DPI + 4 * d + m];
+        double w[NGEO];
+#pragma unroll
+        for (int b = 0; b < NGEO; ++b) {
+            w[b] = wnext[b];
+            wnext[b] = wmom[(min(d + 1, n_det - 1) * NGEO + la) * NGEO + b];
+        }
+        const double W0 = __shfl(w[0], 0, SUB_LANES);
+        const double qr = amp * cb[CB_PR + d], qi = amp * cb[CB_PI + d];
+        const double tra = cb[CB_DTAU + 2 * d], tdec = cb[CB_DTAU + 2 * d + 1];
+        constexpr double GPHIC = -1.0 / TWO_PI;
+        double gk[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int b = 0; b < NCOEF; ++b)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) gk[k] = fma(w[b], dc[b][k], gk[k]);
+        if (lane < NGEO) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) in.wg[k][lane] = gk[k];
+            in.wg[P_DL][lane] = 0.0;
+            in.wg[P_IOTA][lane] = 0.0;
+            in.wg[P_PSI][lane] = 0.0;
+            in.wg[P_RA][lane] = w[NGEO - 1] * tra;
+            in.wg[P_DEC][lane] = w[NGEO - 1] * tdec;
+            in.wg[P_TC][lane] = w[NGEO - 1];
+            in.wg[P_PHIC][lane] = w[0] * GPHIC;
+        }
+        {
+            const bool cam = lane == P_MC || lane == P_DL, proj = lane >= P_IOTA && lane <= P_DEC;
+            const double g = cb[lane == P_MC ? CB_DLNCA_MC : CB_DLNCA_DL];
+            const int m = proj ? lane - P_IOTA : 0;
+            const double xr = cam ? g * qr : proj ? amp * cb[CB_DPR + 4 * d + m] : 0.0;
+            const double xi = cam ? g * qi : proj ? amp * cb[CB_DPI + 4 * d + m] : 0.0;
+            if (lane < NPAR) {
+                in.dr[lane] = xr;
+                in.di[lane] = xi;
+                in.s[lane] = xr * qi - xi * qr;
             }
-            S.dr[tid] = xr;
-            S.di[tid] = xi;
-            S.s[tid] = xr * qi - xi * qr;
         }
-        __syncthreads();
-        if (tid < NPAR * NGEO) {
-            const int k = tid / NGEO, a = tid % NGEO;
-            double v = 0.0;
-            for (int b = 0; b < NGEO; ++b) v = fma(W[a * NGEO + b], S.gam[k][b], v);
-            S.wg[k][a] = v;
-        }
-        __syncthreads();
-        if (tid < NPAIR) {
-            int k, l;
-            pair_of(tid, k, l);
+        sub_fence();
+        double wl[NGEO];
+#pragma unroll
+        for (int b = 0; b < NGEO; ++b) wl[b] = in.wg[l][b];
+        const double drl = in.dr[l], dil = in.di[l], sl = in.s[l];
+#pragma unroll
+        for (int k = 0; k < NPAR; ++k) {
             double gwg = 0.0;
-            for (int a = 0; a < NGEO; ++a) gwg = fma(S.gam[k][a], S.wg[l][a], gwg);
-            acc += W[0] * (S.dr[k] * S.dr[l] + S.di[k] * S.di[l])
-                 + TWO_PI * (S.s[k] * S.wg[l][0] + S.s[l] * S.wg[k][0])
-                 + (4.0 * PI * PI) * (qr * qr + qi * qi) * gwg;
+            if (k < 4) {
+#pragma unroll
+                for (int b = 0; b < NCOEF; ++b) gwg = fma(dc[b][k], wl[b], gwg);
+            } else if (k == P_RA || k == P_DEC || k == P_TC) {
+                gwg = (k == P_RA ? tra : k == P_DEC ? tdec : 1.0) * wl[NGEO - 1];
+            } else if (k == P_PHIC) {
+                gwg = GPHIC * wl[0];
+            }
+            const double wgl0 = wl[0], wgk0 = in.wg[k][0], drk = in.dr[k], dik = in.di[k], sk = in.s[k];
+            acc[k] += W0 * (drk * drl + dik * dil)
+                    + TWO_PI * (sk * wgl0 + sl * wgk0)
+                    + (4.0 * PI * PI) * (qr * qr + qi * qi) * gwg;
         }
-        __syncthreads();
+        sub_fence();
     }
-    if (tid < NPAIR) {
-        int k, l;
-        pair_of(tid, k, l);
-        S.F[k * NPAR + l] = acc;
-        S.F[l * NPAR + k] = acc;
-    }
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NPAR; ++k)
+        if (k <= lane && lane < NPAR) {
+            S.F[k][lane] = acc[k];
+            S.F[lane][k] = acc[k];
+        }
+    sub_fence();
 
     const double beta = st ? st[(size_t)run * SMCGW_STATE_SIZE + SMCGW_ST_BETA] : beta_dev ? *beta_dev : beta_host;
-    finish_metric(S, S.F, NPAR, pm.idx, D, beta, pd, fallback, chol, fisher, status, p, tid);
+    finish_metric<NPAR>(S, pm.idx, D, beta, own, prec, fallback, chol, fisher, status, p, lane);
 }
 
 // The analytic test likelihoods take the exact Hessian of -log L as F: the
@@ -250,25 +305,26 @@ __global__ __launch_bounds__(MET_THREADS) void local_metric_kernel(const DevEven
 // r_i the components' shares at the particle (the shares' mean of the
 // components' Hessians less the shares' covariance of their gradients).
 // Near a mode F is positive definite; across the saddle between the modes it
-// is not, and the particle takes the fallback.  One workgroup per particle.
-__global__ __launch_bounds__(MET_THREADS) void analytic_metric_kernel(TargetDesc tg, PrecDesc pd, int P,
-                                                                     const double* __restrict__ theta,
-                                                                     double beta_host, const double* __restrict__ beta_dev,
-                                                                     const double* __restrict__ fallback,
-                                                                     double* __restrict__ chol, double* __restrict__ fisher,
-                                                                     int32_t* __restrict__ status,
-                                                                     const double* __restrict__ st, int run_size) {
-    __shared__ MetricShared S;
-    __shared__ double F[MAXDIM * MAXDIM];
+// is not, and the particle takes the fallback.
+__global__ __launch_bounds__(64) void analytic_metric_kernel(TargetDesc tg, PrecDesc pd, int P,
+                                                             const double* __restrict__ theta,
+                                                             double beta_host, const double* __restrict__ beta_dev,
+                                                             const double* __restrict__ fallback,
+                                                             double* __restrict__ chol, double* __restrict__ fisher,
+                                                             int32_t* __restrict__ status,
+                                                             const double* __restrict__ st, int run_size) {
+    __shared__ MetricSub sub[MET_SUBS];
     __shared__ int idx[MAXDIM];
-    const int tid = threadIdx.x;
-    const int p = blockIdx.x;
+    const int lane = threadIdx.x % SUB_LANES;
+    MetricSub& S = sub[threadIdx.x / SUB_LANES];
+    const int p = blockIdx.x * MET_SUBS + threadIdx.x / SUB_LANES;
     const int D = tg.dim;
+    idx[lane] = lane;   // the same from every group
+    if (p >= P) return;
     const int run = st ? p / run_size : 0;
     if (st && st[(size_t)run * SMCGW_STATE_SIZE + SMCGW_ST_DONE] != 0.0) return;
     if (st && fallback) fallback += (size_t)run * D * D;
-    if (tid < MAXDIM) idx[tid] = tid;
-    for (int e = tid; e < D * D; e += MET_THREADS) {
+    for (int e = lane; e < D * D; e += SUB_LANES) {
         const int k = e / D, l = e % D;
         double f = 0.0;
         if (tg.kind == SMCGW_TARGET_GAUSS) {
@@ -289,11 +345,12 @@ __global__ __launch_bounds__(MET_THREADS) void analytic_metric_kernel(TargetDesc
             const double r1 = 1.0 / (1.0 + exp(-0.5 * (s2 - s1) / s2g)), r2 = 1.0 - r1;
             f = (k == l ? 1.0 / s2g : 0.0) - r1 * r2 * (m1[k] - m2[k]) * (m1[l] - m2[l]) / (s2g * s2g);
         }
-        F[k * MAXDIM + l] = f;
+        S.F[k][l] = f;
     }
-    __syncthreads();
+    sub_fence();
     const double beta = st ? st[(size_t)run * SMCGW_STATE_SIZE + SMCGW_ST_BETA] : beta_dev ? *beta_dev : beta_host;
-    finish_metric(S, F, MAXDIM, idx, D, beta, pd, fallback, chol, fisher, status, p, tid);
+    const int own = max(D - 1 - lane, 0);
+    finish_metric<MAXDIM>(S, idx, D, beta, own, pd.prec[own], fallback, chol, fisher, status, p, lane);
 }
 
 // Prior precision of each sampled coordinate: 12 / (hi - lo)^2 (uniform),
@@ -341,11 +398,11 @@ static int launch_metric(smcgw_ctx* c, int P, const double* theta, double beta, 
     const PrecDesc pd = prior_precision(c->prior);
     TimedLaunch tl(c, SMCGW_KERNEL_METRIC);
     if (c->target.kind == SMCGW_TARGET_GW)
-        hipLaunchKernelGGL(local_metric_kernel, dim3(P), dim3(MET_THREADS), 0, c->stream, c->d_events,
+        hipLaunchKernelGGL(local_metric_kernel, dim3((P + MET_SUBS - 1) / MET_SUBS), dim3(64), 0, c->stream, c->d_events,
                            (int)c->events.size(), c->ev_of_p, c->pmap, pd, P, theta, beta, beta_dev, fallback, chol,
                            fisher, status, st, run_size);
     else
-        hipLaunchKernelGGL(analytic_metric_kernel, dim3(P), dim3(MET_THREADS), 0, c->stream, c->target, pd, P, theta,
+        hipLaunchKernelGGL(analytic_metric_kernel, dim3((P + MET_SUBS - 1) / MET_SUBS), dim3(64), 0, c->stream, c->target, pd, P, theta,
                            beta, beta_dev, fallback, chol, fisher, status, st, run_size);
     return hipGetLastError() == hipSuccess ? SMCGW_OK : SMCGW_ERR_HIP;
 }
