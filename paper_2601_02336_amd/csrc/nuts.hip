@@ -1117,7 +1117,8 @@ __global__ __launch_bounds__(WAVES * 64, (WAVES == 1 ? 1 : NUTS_WAVES_PER_SIMD))
                 if (PREC == SMCGW_MIXED)
                     bins_mixed_wave<NDET>(t, k, r, WAVES, t.npad / TABLE_PAD, lds_moments<SUBS, WAVES>(s)[r]);
                 else
-                    bins_fp64_wave<NDET>(t, k, r, WAVES, t.npad / TABLE_PAD, lds_moments<SUBS, WAVES>(s)[r]);
+                    // with the library's sin and cos: a deep tree's leaves follow their last bits
+                    bins_fp64_wave<NDET, true, true>(t, k, r, WAVES, t.npad / TABLE_PAD, lds_moments<SUBS, WAVES>(s)[r]);
             }
             __syncthreads();
             if (wave == 0 && mine && (running & (1u << g))) leaf_finish<NDET, WAVES, SUBS>(g, cl);
