@@ -42,19 +42,22 @@ constexpr int LL_WAVES = 4;   // wavefronts per workgroup
 // while lanes 4-7 take the sines and cosines of the four extrinsic angles;
 // then lane 4k + d (k = 0, 1) builds detector d with its ra (k = 0) or dec
 // (k = 1) tangent, and lane 0 the amplitude.  One particle's chain is a
-// quarter of the one-lane prologue's.  Called by every thread of the
-// workgroup (it holds a barrier); ang is the particle's exchange of the angles.
+// quarter of the one-lane prologue's.  Without the gradient there are no tangents:
+// lane 0 has the intrinsic part and lanes 0-3 a detector each.  Called by every thread
+// of the workgroup (it holds a barrier); ang is the particle's exchange of the angles.
 constexpr int PREP_LANES = 8;
 constexpr int PREP_PER_BLOCK = 256 / PREP_LANES;
 static_assert(2 * MAXDET == PREP_LANES && ANG_COUNT == PREP_LANES - 4, "prologue lane split");
 
+template <bool GRAD>
 __device__ __forceinline__ void prologue_lanes(const DevEvent& ev, const ParamMap& pm, const double* __restrict__ x,
                                                double* c, double (*ang_sh)[2], int j, bool live) {
     double th[NPAR];
     if (live) {
         expand_params(pm, x, th);
         if (j < 4) {
-            prep_intrinsic_n<1>(ev, th, c, j, j == 0);
+            if (GRAD) prep_intrinsic_n<1>(ev, th, c, j, j == 0);
+            else if (j == 0) prep_intrinsic_n<0>(ev, th, c, 0, true);
         } else {
             double sn, cs;
             sincos(extrinsic_angle(ev, th, j - 4), &sn, &cs);
@@ -68,8 +71,12 @@ __device__ __forceinline__ void prologue_lanes(const DevEvent& ev, const ParamMa
 #pragma unroll
         for (int k = 0; k < ANG_COUNT; ++k) { ang.sc[k][0] = ang_sh[k][0]; ang.sc[k][1] = ang_sh[k][1]; }
         const int k = j / MAXDET, d = j % MAXDET;
-        prep_extrinsic_det_n<1>(ev, th, ang, c, d, k, k == 0);
-        if (j == 0) prep_extrinsic_common(ev, th, c);
+        if (GRAD) prep_extrinsic_det_n<1>(ev, th, ang, c, d, k, k == 0);
+        else if (k == 0) prep_extrinsic_det_n<0>(ev, th, ang, c, d, 0, true);
+        if (j == 0) {
+            if (GRAD) prep_extrinsic_common(ev, th, c);
+            else c[CB_AMP] = extrinsic_amplitude(ev, th);
+        }
     }
 }
 
@@ -80,8 +87,8 @@ __global__ __launch_bounds__(256) void prep_kernel(const DevEvent* __restrict__ 
     const int g = threadIdx.x / PREP_LANES;
     const int p = blockIdx.x * PREP_PER_BLOCK + g;
     const int q = p < P ? p : 0;
-    prologue_lanes(evs[event_index(ev_of_p, q, n_events)], pm, theta + (size_t)q * pm.dim, cb + (size_t)q * CB_SIZE,
-                   ang_sh[g], threadIdx.x % PREP_LANES, p < P);
+    prologue_lanes<true>(evs[event_index(ev_of_p, q, n_events)], pm, theta + (size_t)q * pm.dim,
+                         cb + (size_t)q * CB_SIZE, ang_sh[g], threadIdx.x % PREP_LANES, p < P);
 }
 
 // logL and gradient of particle p from its coefficient block and moments (one lane).
@@ -103,8 +110,11 @@ __device__ __forceinline__ void write_result(const DevEvent& ev, const ParamMap&
 // of the bin loop; the coefficient blocks and moments stay in LDS, so a call is
 // one launch (a prologue launch of its own cost 6 to 17 us a call: 4096 particles
 // of 3 x 8033 bins took 83.3 us with it and take 77.6 without, 6000 of a folded
-// event 25.0 and 18.0).  GRAD = false leaves the gradient's moments out; logL is
-// the same bit for bit.
+// event 25.0 and 18.0).  The workgroup's first lanes form the results of all its
+// particles together, where a lane of every wavefront took its instructions four
+// times (6000 of a folded event 17.2 -> 16.0 us, 16384 of eight events 974 -> 955).
+// GRAD = false leaves the tangents and the gradient's moments out (20000 values of
+// 1968 bins 50.1 -> 46.7 us without the tangents); logL is the same bit for bit.
 struct LoglikeShared {   // one per particle of the workgroup (dynamic LDS)
     double cb[CB_SIZE];
     double mom[MOM_SIZE];
@@ -129,8 +139,8 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
         const bool live = g < LL_WAVES * per_wave && first + g < P;
         const int i = live ? first + g : 0, p = order ? order[i] : i;
         LoglikeShared& s = sh[live ? g : 0];
-        prologue_lanes(evs[event_index(ev_of_p, p, n_events)], pm, theta + (size_t)p * pm.dim, s.cb, s.ang,
-                       threadIdx.x % PREP_LANES, live);
+        prologue_lanes<GRAD>(evs[event_index(ev_of_p, p, n_events)], pm, theta + (size_t)p * pm.dim, s.cb, s.ang,
+                             threadIdx.x % PREP_LANES, live);
     }
     __syncthreads();
     // wavefront w takes the particles w per_wave, ... of the workgroup
@@ -146,10 +156,11 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
         else
             event_moments<NDET, GRAD, BinPair<NDET, double2>, Fp64Acc<NDET, GRAD>>(t, k, sh[g].mom, sh[g].seg);
     }
-    const int lane = lane_here();
-    if (lane < n) {
-        const LoglikeShared& s = sh[g0 + lane];
-        const int i = first + g0 + lane, p = order ? order[i] : i;
+    __syncthreads();
+    // results: a lane per particle of the workgroup
+    if ((int)threadIdx.x < min(LL_WAVES * per_wave, P - first)) {
+        const LoglikeShared& s = sh[threadIdx.x];
+        const int i = first + threadIdx.x, p = order ? order[i] : i;
         write_result<GRAD>(evs[event_index(ev_of_p, p, n_events)], pm, s.cb, s.mom, p, logl, grad);
     }
 }
@@ -166,7 +177,7 @@ __global__ __launch_bounds__(64 * LL_WAVES, NDET < 4 ? 4 : 3) void bins_mixed_ke
 }
 
 template <int NDET, bool GRAD>
-__global__ __launch_bounds__(64 * LL_WAVES, NDET == 1 || !GRAD ? 4 : 3) void bins_fp64_kernel(
+__global__ __launch_bounds__(64 * LL_WAVES, NDET <= 2 || !GRAD ? 4 : 3) void bins_fp64_kernel(
     const DevEvent* __restrict__ evs, int n_events, const int32_t* __restrict__ ev_of_p,
     const int32_t* __restrict__ order, ParamMap pm, int P, int per_wave, const double* __restrict__ theta,
     double* __restrict__ logl, double* __restrict__ grad) {
