@@ -444,11 +444,6 @@ __host__ __device__ constexpr int segments(int npad) {
 }
 __device__ constexpr int moments(int n_det, bool grad) { return grad ? mom_g(n_det, NCOEF) : 2 * n_det; }
 
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // All segments from one wavefront into mom (LDS; seg: scratch of the same size).
 template <int NDET, bool GRAD, class In, class Acc>
 __device__ __forceinline__ void event_moments(const TableView& t, const BinCoef& k, double* mom, double* seg) {

@@ -254,4 +254,43 @@ hipError_t launch_waveform(const DevEvent* d_events, int event_id, const double*
                            int n_det, hipStream_t s);
 int noalloc_init(int device);   // the fixed scratch of smcgw_loglike_grad_noalloc on this device
 
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Lower Cholesky factor of an N x N matrix on lanes 0 .. N-1, lane i holding row i in A
+// (its lower part), diag[i] its diagonal entry (LDS, N doubles).  Column k of the factor
+// goes to Rt[k][0..N-1] (LDS, entries above the diagonal undefined).  Whether every
+// pivot was positive; the same in all lanes.  An entry is the matrix entry minus the
+// products of the finished columns, k ascending, as in the textbook's row-by-row form,
+// but the products are subtracted as the columns come, for all entries at once; every
+// lane follows the diagonal, so a pivot needs no exchange.
+template <int N>
+__device__ __forceinline__ bool cholesky_rows(double (&A)[N], double (*Rt)[MAXDIM], double* diag, int lane) {
+    double dg[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        if (j == lane) diag[lane] = A[j];
+    wave_lds_fence();
+#pragma unroll
+    for (int j = 0; j < N; ++j) dg[j] = diag[j];
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        ok = ok && dg[k] > 0.0;
+        const double lkk = sqrt(dg[k]);
+        const double l = lane == k ? lkk : A[k] / lkk;
+        Rt[k][lane] = l;
+        wave_lds_fence();
+#pragma unroll
+        for (int j = k + 1; j < N; ++j) {
+            const double lj = Rt[k][j];
+            dg[j] = fma(-lj, lj, dg[j]);
+            A[j] = fma(-l, lj, A[j]);
+        }
+    }
+    return ok;
+}
+
 }  // namespace smcgw

@@ -71,12 +71,6 @@ struct MetricSub : MetricState {
 };
 static_assert(sizeof(MetricSub) % 256 == 64, "bank offset of the groups");
 
-// Order of one wavefront's LDS accesses across its lanes.
-__device__ __forceinline__ void sub_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // M = beta F + diag(prior precision) over the sampled coordinates (coordinate a of
 // the sample being row idx[a] of F), then the lower Cholesky factor of M^{-1} into
 // chol[p], or the fallback where M or the factor is not numerically positive definite.
@@ -85,7 +79,7 @@ __device__ __forceinline__ void sub_fence() {
 // a positive diagonal, so it is that factor; it needs one Cholesky and one triangular
 // inverse.  Lane i holds row i of J M J, then column i of R^{-1}.  An entry takes its
 // products with the finished columns in column order, as in the textbook's row-by-row
-// form; only they are subtracted as the columns come, for every entry at once.
+// form (see cholesky_rows).
 // N >= D rows and columns are factored: those beyond D are the identity's, so the steps
 // need no branches and the reads of the next ones are under way early.  own: coordinate
 // D-1-lane's row of F, prec: its prior precision.
@@ -96,32 +90,14 @@ __device__ __forceinline__ void finish_metric(MetricSub& S, const int* idx, int 
                                               int lane) {
     if (fisher)
         for (int i = lane; i < D * D; i += SUB_LANES) fisher[(size_t)p * D * D + i] = S.F[idx[i / D]][idx[i % D]];
-    double A[N], dg[N];   // row `lane`; the diagonal, which every lane follows to have the pivots at hand
+    double A[N];   // row `lane`
 #pragma unroll
     for (int j = 0; j < N; ++j) {
         const double f = S.F[own][idx[max(D - 1 - j, 0)]];
         const double v = fma(beta, f, j == lane ? prec : 0.0);
         A[j] = j < D && lane < D ? v : j == lane ? 1.0 : 0.0;
-        if (j == lane) S.diag[lane] = A[j];
     }
-    sub_fence();
-#pragma unroll
-    for (int j = 0; j < N; ++j) dg[j] = S.diag[j];
-    bool ok = true;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        ok = ok && dg[k] > 0.0;
-        const double lkk = sqrt(dg[k]);
-        const double l = lane == k ? lkk : A[k] / lkk;
-        S.Rt[k][lane] = l;
-        sub_fence();
-#pragma unroll
-        for (int j = k + 1; j < N; ++j) {
-            const double lj = S.Rt[k][j];
-            dg[j] = fma(-lj, lj, dg[j]);
-            A[j] = fma(-l, lj, A[j]);
-        }
-    }
+    bool ok = cholesky_rows(A, S.Rt, S.diag, lane);
     // X = R^{-1}, lane c column c by forward substitution
     double X[N];
 #pragma unroll
@@ -144,7 +120,7 @@ __device__ __forceinline__ void finish_metric(MetricSub& S, const int* idx, int 
         for (int r = 0; r < N; ++r)
             if (r < D) S.out[(D - 1 - lane) * D + D - 1 - r] = X[r];
     }
-    sub_fence();
+    wave_lds_fence();
     double* o = chol + (size_t)p * D * D;
     if (ok) {
 #pragma unroll
@@ -188,7 +164,7 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
     for (int k = 0; k < D; ++k) from = pm.idx[k] == lane ? k : from;
     const double x = theta[(size_t)p * D + min(lane, D - 1)], xp = __shfl(x, max(from, 0), SUB_LANES);
     if (lane < NPAR) in.th[lane] = from >= 0 ? xp : pm.fixed[lane];
-    sub_fence();
+    wave_lds_fence();
     if (lane < 4) prep_intrinsic_n<1>(ev, in.th, in.cb, lane, lane == 0);
     if (lane < ANG_COUNT) {
         double sn, cs;
@@ -196,7 +172,7 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
         in.ang.sc[lane][0] = sn;
         in.ang.sc[lane][1] = cs;
     }
-    sub_fence();
+    wave_lds_fence();
     if (lane < 2 * MAXDET) {
         const ExtAngles ang = in.ang;
         const int k = lane / MAXDET;
@@ -204,7 +180,7 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
     } else if (lane == 2 * MAXDET) {
         prep_extrinsic_common(ev, in.th, in.cb);
     }
-    sub_fence();
+    wave_lds_fence();
     const double* cb = in.cb;
     const double amp = cb[CB_AMP];
 
@@ -263,7 +239,7 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
                 in.s[lane] = xr * qi - xi * qr;
             }
         }
-        sub_fence();
+        wave_lds_fence();
         double wl[NGEO];
 #pragma unroll
         for (int b = 0; b < NGEO; ++b) wl[b] = in.wg[l][b];
@@ -284,7 +260,7 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
                     + TWO_PI * (sk * wgl0 + sl * wgk0)
                     + (4.0 * PI * PI) * (qr * qr + qi * qi) * gwg;
         }
-        sub_fence();
+        wave_lds_fence();
     }
 #pragma unroll
     for (int k = 0; k < NPAR; ++k)
@@ -292,7 +268,7 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
             S.F[k][lane] = acc[k];
             S.F[lane][k] = acc[k];
         }
-    sub_fence();
+    wave_lds_fence();
 
     const double beta = st ? st[(size_t)run * SMCGW_STATE_SIZE + SMCGW_ST_BETA] : beta_dev ? *beta_dev : beta_host;
     finish_metric<NPAR>(S, pm.idx, D, beta, own, prec, fallback, chol, fisher, status, p, lane);
@@ -347,7 +323,7 @@ __global__ __launch_bounds__(64) void analytic_metric_kernel(TargetDesc tg, Prec
         }
         S.F[k][l] = f;
     }
-    sub_fence();
+    wave_lds_fence();
     const double beta = st ? st[(size_t)run * SMCGW_STATE_SIZE + SMCGW_ST_BETA] : beta_dev ? *beta_dev : beta_host;
     const int own = max(D - 1 - lane, 0);
     finish_metric<MAXDIM>(S, idx, D, beta, own, pd.prec[own], fallback, chol, fisher, status, p, lane);
