@@ -31,12 +31,12 @@ namespace smcgw {
 // the prologue, a row of W_d, a column of F and a row of the factor in turn.  Nothing
 // crosses the groups and a workgroup is one wavefront, so there are no barriers, and
 // the matrices stay in registers but for the column that a step of the factorisation
-// broadcasts.  What bounds it is the chain of one particle (29000 cycles: prologue
-// 9800, F 9400, factor 3300, inverse 2300, the rest loads and stores), so particles in flight are
-// what counts: eight workgroups fit a compute unit, 32 particles, where a workgroup of
-// two wavefronts for each held 12 and spent most instructions on a few lanes.  3 x 8033
-// bins' event, 11 parameters, 6144 particles: 71.6 -> 19.8 us a call, 64: 21.2 -> 14.3
-// (of which 9 are the call).
+// broadcasts.  What bounds it is the chain of one particle (29000 cycles: prologue 9800,
+// F 9400, factor 3300, inverse 2300, the rest loads and stores), so particles in flight
+// are what counts: eight workgroups fit a compute unit, 32 particles, where a workgroup of
+// two wavefronts for each held 12 and spent most instructions on a few lanes.  Event of
+// 3 x 8033 bins, 11 parameters, 6144 particles: 71.5 -> 18.9 us a call, 64: 21.2 -> 14.3
+// (of which 9 are the call).  Every entry is rounded as it was there.
 constexpr int SUB_LANES = 16;
 constexpr int MET_SUBS = 64 / SUB_LANES;
 static_assert(SUB_LANES == MAXDIM && NPAR <= SUB_LANES && NGEO <= SUB_LANES && 2 * MAXDET < SUB_LANES, "lane roles");
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
             }
             const double wgl0 = wl[0], wgk0 = in.wg[k][0], drk = in.dr[k], dik = in.di[k], sk = in.s[k];
             acc[k] += W0 * (drk * drl + dik * dil)
-                    + TWO_PI * (sk * wgl0 + sl * wgk0)
+                    + TWO_PI * fma(sk, wgl0, sl * wgk0)
                     + (4.0 * PI * PI) * (qr * qr + qi * qi) * gwg;
         }
         wave_lds_fence();
