@@ -35,7 +35,7 @@ namespace smcgw {
 // F 9400, factor 3300, inverse 2300, the rest loads and stores), so particles in flight
 // are what counts: eight workgroups fit a compute unit, 32 particles, where a workgroup of
 // two wavefronts for each held 12 and spent most instructions on a few lanes.  Event of
-// 3 x 8033 bins, 11 parameters, 6144 particles: 71.5 -> 18.9 us a call, 64: 21.2 -> 14.3
+// 3 x 8033 bins, 11 parameters, 6144 particles: 71.5 -> 20 us a call, 64: 21.2 -> 14.3
 // (of which 9 are the call).  Every entry is rounded as it was there.
 constexpr int SUB_LANES = 16;
 constexpr int MET_SUBS = 64 / SUB_LANES;
@@ -187,18 +187,15 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
     // gamma_a derives the phase c_0 + sum_b c_{1+b} B_b(f) + f tau_d, with c_0 containing
     // -phi_c / (2 pi) and tau_d = t_c + delay_d(ra, dec), so it is sparse: the coefficients' derivatives for the four intrinsic
     // parameters, one entry for ra, dec, t_c (of f) and phi_c (constant), none for d_L, iota and psi.
-    // Lane a takes row a of W, then lane l the column F_kl, k <= l.
+    // Lane a takes row a of W, then lane l the column F_kl, k <= l.  The coefficients' derivatives are read from
+    // LDS both times: held in registers a call is 1 us shorter, but a wavefront's 224 registers then wait for two
+    // of another stream's NUTS workgroups to leave a SIMD instead of one (2.2 ms a launch there against 1.1).
     const int la = min(lane, NGEO - 1), l = min(lane, NPAR - 1);
     double acc[NPAR], wnext[NGEO];   // the next detector's row is under way
 #pragma unroll
     for (int k = 0; k < NPAR; ++k) acc[k] = 0.0;
 #pragma unroll
     for (int b = 0; b < NGEO; ++b) wnext[b] = wmom[la * NGEO + b];
-    double dc[NCOEF][4];
-#pragma unroll
-    for (int b = 0; b < NCOEF; ++b)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) dc[b][k] = cb[CB_DC + 4 * b + k];
 #pragma unroll 1
     for (int d = 0; d < n_det; ++d) {
         double w[NGEO];
@@ -215,7 +212,7 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
 #pragma unroll
         for (int b = 0; b < NCOEF; ++b)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) gk[k] = fma(w[b], dc[b][k], gk[k]);
+            for (int k = 0; k < 4; ++k) gk[k] = fma(w[b], cb[CB_DC + 4 * b + k], gk[k]);
         if (lane < NGEO) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) in.wg[k][lane] = gk[k];
@@ -249,7 +246,7 @@ __global__ __launch_bounds__(64) void local_metric_kernel(const DevEvent* __rest
             double gwg = 0.0;
             if (k < 4) {
 #pragma unroll
-                for (int b = 0; b < NCOEF; ++b) gwg = fma(dc[b][k], wl[b], gwg);
+                for (int b = 0; b < NCOEF; ++b) gwg = fma(cb[CB_DC + 4 * b + k], wl[b], gwg);
             } else if (k == P_RA || k == P_DEC || k == P_TC) {
                 gwg = (k == P_RA ? tra : k == P_DEC ? tdec : 1.0) * wl[NGEO - 1];
             } else if (k == P_PHIC) {
