@@ -395,7 +395,8 @@ __device__ RwState rwm_resume(const RwArgs& a, int run, int pass, double* tot, d
             }
         }
     }
-    if (s.beta < 0.0 && !(s.it < 100.0 && s.hi - s.lo > 1e-14)) s.beta = s.lo;
+    // not before the first pass has tried beta = 1, however narrow the bracket
+    if (pass > 0 && s.beta < 0.0 && !(s.it < 100.0 && s.hi - s.lo > 1e-14)) s.beta = s.lo;
     if (blockIdx.x == 0 && threadIdx.x == 0) scr.state[pass & 1] = s;
     return s;
 }
