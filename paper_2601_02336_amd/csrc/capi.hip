@@ -75,7 +75,7 @@ int ctx_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta
         if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
             if (sort_need > c->sort_cap) {
                 const int n = std::max(sort_need, std::max(2 * c->sort_cap, 4096));
-                (void)hipFree(c->d_sort);
+                if (c->d_sort) c->outgrown.push_back(c->d_sort);
                 c->d_sort = nullptr;
                 c->sort_cap = 0;
                 if (hipMalloc(&c->d_sort, (size_t)n * sizeof(int32_t)) == hipSuccess) c->sort_cap = n;
@@ -128,6 +128,7 @@ extern "C" int smcgw_destroy(smcgw_ctx* c) {
     (void)hipFree(c->d_cb);
     (void)hipFree(c->d_sort);
     (void)hipFree(c->d_few);
+    for (void* p : c->outgrown) (void)hipFree(p);
     (void)hipFree(c->d_tan);
     c->sweep_free();
     c->sampler_free();
