@@ -105,6 +105,12 @@ __device__ __forceinline__ void write_result(const DevEvent& ev, const ParamMap&
     }
 }
 
+// Particle i of the start order (NULL: index order).  The order lies in scratch that overlapping calls share: an entry
+// of another call's, larger batch must not lead out of this one's arrays.
+__device__ __forceinline__ int ordered_particle(const int32_t* __restrict__ order, int i, int P) {
+    return order ? (int)min((unsigned)order[i], (unsigned)P - 1u) : i;
+}
+
 // Particles [LL_WAVES per_wave blockIdx.x, ...) of the start order (order NULL:
 // index order), per_wave <= 8 for each wavefront.  Bound by the VALU issue rate
 // of the bin loop; the coefficient blocks and moments stay in LDS, so a call is
@@ -137,7 +143,7 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
         // prologue: the workgroup's particles on consecutive groups of eight lanes
         const int g = threadIdx.x / PREP_LANES;
         const bool live = g < LL_WAVES * per_wave && first + g < P;
-        const int i = live ? first + g : 0, p = order ? order[i] : i;
+        const int i = live ? first + g : 0, p = ordered_particle(order, i, P);
         LoglikeShared& s = sh[live ? g : 0];
         prologue_lanes<GRAD>(evs[event_index(ev_of_p, p, n_events)], pm, theta + (size_t)p * pm.dim, s.cb, s.ang,
                              threadIdx.x % PREP_LANES, live);
@@ -147,7 +153,7 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
     const int g0 = wave * per_wave;
     const int n = min(per_wave, P - first - g0);
     for (int g = g0; g < g0 + n; ++g) {
-        const int p = order ? order[first + g] : first + g;
+        const int p = ordered_particle(order, first + g, P);
         const int e = __builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events));
         const BinCoef k = load_coef(sh[g].cb);
         const TableView t = PREC == SMCGW_MIXED ? mixed_tables<NDET>(evs + e) : fp64_tables<NDET>(evs + e);
@@ -160,7 +166,7 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
     // results: a lane per particle of the workgroup
     if ((int)threadIdx.x < min(LL_WAVES * per_wave, P - first)) {
         const LoglikeShared& s = sh[threadIdx.x];
-        const int i = first + threadIdx.x, p = order ? order[i] : i;
+        const int p = ordered_particle(order, first + threadIdx.x, P);
         write_result<GRAD>(evs[event_index(ev_of_p, p, n_events)], pm, s.cb, s.mom, p, logl, grad);
     }
 }
