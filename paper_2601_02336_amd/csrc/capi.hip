@@ -70,23 +70,31 @@ int ctx_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta
     // can be allocated) the call takes the path that needs none, with the same results.
     const int sort_need = lengths_differ(c, ev_of_p) ? P : 0;
     const size_t few_need = loglike_scratch_bytes(c, P, ev_of_p, precision);
-    if (sort_need > c->sort_cap || (few_need && !c->d_few)) {
+    if (sort_need > c->sort_cap || few_need > c->few_cap) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+            void* q = nullptr;
             if (sort_need > c->sort_cap) {
                 const int n = std::max(sort_need, std::max(2 * c->sort_cap, 4096));
-                if (c->d_sort) c->outgrown.push_back(c->d_sort);
-                c->d_sort = nullptr;
-                c->sort_cap = 0;
-                if (hipMalloc(&c->d_sort, (size_t)n * sizeof(int32_t)) == hipSuccess) c->sort_cap = n;
-                else c->d_sort = nullptr;
+                if (hipMalloc(&q, (size_t)n * sizeof(int32_t)) == hipSuccess) {
+                    if (c->d_sort) c->outgrown.push_back(c->d_sort);
+                    c->d_sort = (int32_t*)q;
+                    c->sort_cap = n;
+                }
             }
-            if (few_need && !c->d_few && hipMalloc(&c->d_few, few_need) != hipSuccess) c->d_few = nullptr;
+            if (few_need > c->few_cap) {
+                const size_t n = std::max(few_need, std::max(2 * c->few_cap, (size_t)1 << 17));
+                if (hipMalloc(&q, n) == hipSuccess) {
+                    if (c->d_few) c->outgrown.push_back(c->d_few);
+                    c->d_few = q;
+                    c->few_cap = n;
+                }
+            }
             (void)hipGetLastError();   // a refused allocation is no error of the call
         }
     }
     return queue_loglike(c, P, ev_of_p, theta, logl, grad, precision, sort_need <= c->sort_cap ? c->d_sort : nullptr,
-                         c->d_few);
+                         few_need && few_need <= c->few_cap ? c->d_few : nullptr);
 }
 
 }  // namespace smcgw

@@ -37,10 +37,11 @@ struct smcgw_ctx {
     int cap = 0;
     int32_t* d_sort = nullptr;             // start order of a batch over events of different lengths
     int sort_cap = 0;
-    // start orders a larger batch has replaced: a captured call holds their address, so they stay allocated until the
-    // context ends (each is at most half of the next)
+    void* d_few = nullptr;                 // segments of the few-particle likelihood
+    size_t few_cap = 0;                    // its bytes
+    // start orders and segments' blocks a larger call has replaced: a captured call holds their address, so they stay
+    // allocated until the context ends (each is at most half of the next)
     std::vector<void*> outgrown;
-    void* d_few = nullptr;                 // segments of the few-particle likelihood (13.6 MiB, on its first use)
     double* d_tan = nullptr;               // tangent moment blocks of the plain form, [tan_cap][12]
     int tan_cap = 0;
     // sampler state

@@ -662,14 +662,14 @@ static LoglikePath loglike_path(int P, int longest, int nseg, int precision) {
     return nseg > 1 && P < SEGMENT_MAX_P ? PATH_SEGMENTS : PATH_BATCH;
 }
 
-static size_t segment_scratch_bytes() {
-    return (SEGMENT_MAX * (size_t)MOM_SIZE + SEGMENT_MAX_P * (size_t)CB_SIZE) * sizeof(double);
+static size_t segment_scratch_bytes(int P, int nseg) {
+    return ((size_t)P * nseg * MOM_SIZE + (size_t)P * CB_SIZE) * sizeof(double);
 }
 
 template <int NDET, bool GRAD>
 hipError_t launch_few_ndet(const LoglikeCall& a, LoglikePath path, int precision, void* scratch, hipStream_t s) {
     const int nseg = a.max_seg;
-    SegmentScratch scr{(double*)scratch, (double*)scratch + (size_t)SEGMENT_MAX_P * CB_SIZE, nseg};
+    SegmentScratch scr{(double*)scratch, (double*)scratch + (size_t)a.P * CB_SIZE, nseg};
     const dim3 segs((nseg + LL_WAVES - 1) / LL_WAVES, a.P), block(64 * LL_WAVES);
     if (path == PATH_POINT)
         hipLaunchKernelGGL((point_kernel<NDET, GRAD>), dim3(nseg, a.P), dim3(PT_THREADS), 0, s, a.events, a.n_events,
@@ -733,7 +733,7 @@ static void event_extent(const smcgw_ctx* c, const int32_t* ev_of_p, int& longes
 size_t loglike_scratch_bytes(const smcgw_ctx* c, int P, const int32_t* ev_of_p, int precision) {
     int longest, nseg;
     event_extent(c, ev_of_p, longest, nseg);
-    return loglike_path(P, longest, nseg, precision) != PATH_BATCH && nseg > 1 ? segment_scratch_bytes() : 0;
+    return loglike_path(P, longest, nseg, precision) != PATH_BATCH && nseg > 1 ? segment_scratch_bytes(P, nseg) : 0;
 }
 
 // The batched likelihood on the context's stream; order: scratch for P start

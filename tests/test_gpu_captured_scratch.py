@@ -50,3 +50,26 @@ def test_start_order_of_a_batch(smcgw):
             torch.cuda.synchronize()
             assert torch.equal(ll, ref[0]) and torch.equal(g, ref[1])
     c.close()
+
+
+def test_segments_of_few_particles(smcgw):
+    """A call of few particles on a long event, captured with its segments' scratch; then eager calls that need more."""
+    ev = event(synth.EventSpec(20.0, 20.0 + 20000 * 0.5, 0.5, 2, 20.0, 81))
+    x = torch.tensor(synth.prior_draw(np.random.default_rng(4), 600, synth.gw_prior_for(ev)), device="cuda")
+    c = smcgw.Context(0)
+    c.add_event(ev)
+    for prec in (smcgw.MIXED, smcgw.PLAIN_FP64):
+        xs = x[:5].contiguous()
+        ref = c.loglike_grad(xs, precision=prec)
+        ll, g = torch.zeros(5, dtype=torch.float64, device="cuda"), torch.zeros_like(xs)
+        graph = _capture(lambda: c.loglike_grad(xs, ll, g, precision=prec))
+        for n in (5, 90, 250, 600):
+            big = c.loglike_grad(x[:n].contiguous(), precision=prec)
+            assert torch.equal(big[0][:5], ref[0]) and torch.equal(big[1][:5], ref[1])
+            for _ in range(2):
+                ll.zero_()
+                g.zero_()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(ll, ref[0]) and torch.equal(g, ref[1])
+    c.close()
