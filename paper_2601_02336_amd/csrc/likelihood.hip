@@ -645,21 +645,30 @@ hipError_t launch_loglike(const LoglikeCall& a, int n_det, int precision, hipStr
 // The few-particle paths, and where they end.  POINT: MIXED calls on events of
 // POINT_MIN_BLOCKS blocks and more, while every segment gets a compute unit of
 // its own (256 particles of 8033 bins: 18.7 us, 33.3 with a wavefront each; 400,
-// in two rounds of workgroups: 38 against 31).  SEGMENTS: events of more than one
-// segment while one wavefront per particle does not fill the chip's SIMDs twice
-// (32449 bins, 1500 particles: 254 us against 301; 2500: 430 against 423); their
-// scratch is bounded by SEGMENT_MAX.
+// in two rounds of workgroups: 38 against 31).
+// SEGMENTS: events of more than one segment, as long as a wavefront per particle leaves SIMDs idle and the
+// segments' wavefronts are evenly loaded.  A workgroup walks four segments; where the last ones are short or missing,
+// its wavefronts wait for the longest, so what counts is the share of the workgroups' blocks that hold bins (`fill`).
+// Segments against one wavefront per particle, 3 detectors, us: share 0.28 (18 blocks) 128 particles 21 / 32, 256
+// 31 / 32, 600 40 / 32; 0.38 (24) 256 0.78 of the time, 512 0.95, 600 1.13; 0.53 (34) 512 0.88, 600 1.00, 1024 1.19;
+// 0.77 (49) 700 0.84, 800 1.03, 1024 1.05; 1 (64) 1024 0.87, 1500 0.80, 1800 1.00, 2047 1.02; 1 (508) 1536 856 / 1106,
+// 2047 1120 / 1150 (plain 2657 / 2593).
 constexpr int POINT_MIN_BLOCKS = 8;
 constexpr int POINT_WORKGROUPS = 256;   // compute units
-constexpr int SEGMENT_MAX_P = 2048;
 constexpr int SEGMENT_MAX = 65536;      // segments of a call (192 B each)
+static int segment_max_particles(int npad) {
+    const int blocks = npad / TABLE_PAD;
+    const int wgs = (segments(npad) + LL_WAVES - 1) / LL_WAVES;
+    const double fill = (double)blocks / (wgs * LL_WAVES * segment_blocks(npad));
+    return fill < 0.375 ? 256 : fill < 0.75 ? 512 : fill < 0.875 ? 704 : 1536;
+}
 enum LoglikePath { PATH_BATCH, PATH_POINT, PATH_SEGMENTS };
 
 static LoglikePath loglike_path(int P, int longest, int nseg, int precision) {
     if ((long)P * nseg > SEGMENT_MAX) return PATH_BATCH;
     if (precision == SMCGW_MIXED && longest >= POINT_MIN_BLOCKS * TABLE_PAD && P * nseg <= POINT_WORKGROUPS)
         return PATH_POINT;
-    return nseg > 1 && P < SEGMENT_MAX_P ? PATH_SEGMENTS : PATH_BATCH;
+    return nseg > 1 && P <= segment_max_particles(longest) ? PATH_SEGMENTS : PATH_BATCH;
 }
 
 static size_t segment_scratch_bytes(int P, int nseg) {
