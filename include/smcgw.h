@@ -287,7 +287,7 @@ int smcgw_target_loglike_grad(smcgw_ctx *ctx, int P, const double *theta, double
  * likelihood and gradient of smcgw_loglike_grad, same arguments and results,
  * with its per-particle scratch (the start order of a batch over events of
  * different lengths) in a fixed device array of SMCGW_NOALLOC_MAX_P particles
- * (64 KiB) that each GPU holds from the first context on it until the process
+ * (65 KiB) that each GPU holds from the first context on it until the process
  * ends.
  * It calls no allocation, creates no event and does not synchronise.
  * SMCGW_ERR_SHAPE for P > SMCGW_NOALLOC_MAX_P.  Every call on one GPU shares

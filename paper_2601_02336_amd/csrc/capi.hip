@@ -68,15 +68,15 @@ int ctx_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta
     if (c->events.empty()) return SMCGW_ERR_NOT_INIT;
     // Scratch that only speeds the call up: without it (no memory left, or a stream being captured, where nothing
     // can be allocated) the call takes the path that needs none, with the same results.
-    const int sort_need = lengths_differ(c, ev_of_p) ? P : 0;
+    const size_t sort_need = loglike_order_entries(c, P, ev_of_p);
     const size_t few_need = loglike_scratch_bytes(c, P, ev_of_p, precision);
     if (sort_need > c->sort_cap || few_need > c->few_cap) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
             void* q = nullptr;
             if (sort_need > c->sort_cap) {
-                const int n = std::max(sort_need, std::max(2 * c->sort_cap, 4096));
-                if (hipMalloc(&q, (size_t)n * sizeof(int32_t)) == hipSuccess) {
+                const size_t n = std::max(sort_need, std::max(2 * c->sort_cap, (size_t)4096));
+                if (hipMalloc(&q, n * sizeof(int32_t)) == hipSuccess) {
                     if (c->d_sort) c->outgrown.push_back(c->d_sort);
                     c->d_sort = (int32_t*)q;
                     c->sort_cap = n;
@@ -93,7 +93,7 @@ int ctx_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta
             (void)hipGetLastError();   // a refused allocation is no error of the call
         }
     }
-    return queue_loglike(c, P, ev_of_p, theta, logl, grad, precision, sort_need <= c->sort_cap ? c->d_sort : nullptr,
+    return queue_loglike(c, P, ev_of_p, theta, logl, grad, precision, sort_need && sort_need <= c->sort_cap ? c->d_sort : nullptr,
                          few_need && few_need <= c->few_cap ? c->d_few : nullptr);
 }
 

@@ -36,7 +36,7 @@ struct smcgw_ctx {
     double* d_cb = nullptr;
     int cap = 0;
     int32_t* d_sort = nullptr;             // start order of a batch over events of different lengths
-    int sort_cap = 0;
+    size_t sort_cap = 0;                   // its entries
     void* d_few = nullptr;                 // segments of the few-particle likelihood
     size_t few_cap = 0;                    // its bytes
     // start orders and segments' blocks a larger call has replaced: a captured call holds their address, so they stay
@@ -137,7 +137,7 @@ int tangent_reserve(smcgw_ctx* c, int P);
 int queue_loglike_tangent(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, const uint8_t* active,
                           double* logl, double* grad);
 bool tangent_supported(const smcgw_ctx* c);
-bool lengths_differ(const smcgw_ctx* c, const int32_t* ev_of_p);
+size_t loglike_order_entries(const smcgw_ctx* c, int P, const int32_t* ev_of_p);
 int queue_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
                   int precision, int32_t* order, void* few);
 size_t loglike_scratch_bytes(const smcgw_ctx* c, int P, const int32_t* ev_of_p, int precision);

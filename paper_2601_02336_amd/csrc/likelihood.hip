@@ -490,62 +490,134 @@ __global__ __launch_bounds__(64) void finish_kernel(const DevEvent* __restrict__
 // its longest event: equal lengths side by side leave no wavefront waiting, and
 // with the longest first the short ones fill the end of the launch (16384
 // particles over eight events of 4017 to 64897 bins: 1523 us a call in index
-// order, 1010 sorted, the sort included).  One workgroup; wavefront w owns the
-// contiguous index range w.
-constexpr int SORT_MIN_P = 1024;   // the SIMDs of the GPU
-struct EventRanks { uint8_t rank[SMCGW_MAX_EVENTS]; };
+// order, 955 sorted, the sort included).  A workgroup orders up to SORT_CHUNK particles,
+// its wavefront w the contiguous index range w; larger batches take a workgroup for
+// each chunk, after a launch that counts every chunk's ranks.  Bound by the
+// instructions issued on a compute unit: one workgroup would take 8 us for 2000 particles,
+// 23 for 20000 and 90 for 100000, the chunks 8, 13 and 14.
+//
+// Where it is worth that (index order / sorted, us; events in turn, rising, at random): 16 events of 1 to 16
+// blocks, 1025 particles 31.7 / 36.1, 30.2 / 35.3, 30.0 / 35.0; 1300: 42.3 / 37.5, 34.1 / 37.5, 40.9 / 37.6;
+// 6000: 105 / 77, 72 / 77, 94 / 77.  Not with lengths within a factor of two (8 and 16 blocks, 3000 particles:
+// 52.6 / 55.1, 50.8 / 56.2, 58.7 / 55.3; 16 and 17: 63.8 / 68.0, 61.8 / 69.3, 64.3 / 68.3) and not on short events
+// (1 to 8 blocks, 3000 particles: 30.8 / 33.7, 28.0 / 35.0, 33.8 / 34.7; 1 and 2 blocks, 6000: 17.8 / 26.8).  A
+// caller's own longest-first order costs the launch for nothing (4 to 7 us).
+constexpr int SORT_FROM = 1280;
+constexpr int SORT_BLOCKS = 16;
+bool sort_pays(int P, int longest, int shortest) {
+    return P > SORT_FROM && longest >= SORT_BLOCKS * TABLE_PAD && longest > 2 * shortest;
+}
+
+struct EventRanks { int bits; uint8_t rank[SMCGW_MAX_EVENTS]; };   // ranks below 2^bits
 constexpr int SORT_THREADS = 1024;
 constexpr int SORT_WAVES = SORT_THREADS / 64;
+constexpr int SORT_AHEAD = 8;   // event indices of a lane in flight
+constexpr int SORT_CHUNK = 4096;
+constexpr int sort_chunks(int P) { return (P - 1) / SORT_CHUNK + 1; }
+// entries of the order array: the order, then every chunk's counts where there are several
+constexpr size_t sort_entries(int P) { return P + (sort_chunks(P) > 1 ? (size_t)sort_chunks(P) * SMCGW_MAX_EVENTS : 0); }
 
-__global__ __launch_bounds__(SORT_THREADS) void sort_events_kernel(const int32_t* __restrict__ ev_of_p, int n_events,
-                                                                   EventRanks er, int P, int32_t* __restrict__ order) {
-    // counts, then running positions, of every (rank, wavefront)
-    __shared__ int pos[SMCGW_MAX_EVENTS][SORT_WAVES];
-    __shared__ int part[SORT_WAVES];
-    __shared__ uint8_t rank[SMCGW_MAX_EVENTS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    static_assert(SMCGW_MAX_EVENTS * SORT_WAVES == SORT_THREADS, "one scan entry per thread");
-    (&pos[0][0])[tid] = 0;
-    if (tid < SMCGW_MAX_EVENTS) rank[tid] = er.rank[tid];
-    __syncthreads();
-    const int per = ((P + SORT_WAVES - 1) / SORT_WAVES + 63) & ~63;
-    const int i0 = min(P, wave * per), i1 = min(P, i0 + per);
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int b = i0; b < i1; b += 64) {
-            const int i = b + lane;
-            const bool in = i < i1;
-            const int r = in ? rank[event_index(ev_of_p, i, n_events)] : -1;
-            unsigned long long todo = __ballot(in);
-            while (todo) {   // one turn per rank among the 64 particles
-                const int l = __builtin_ctzll(todo);
-                const int v = __shfl(r, l, 64);
-                const unsigned long long same = __ballot(r == v);
-                const int at = pos[v][wave];   // this wavefront's entry alone
-                if (pass == 1 && r == v) order[at + __popcll(same & ((1ull << lane) - 1))] = i;
-                __builtin_amdgcn_wave_barrier();
-                if (lane == l) pos[v][wave] = at + __popcll(same);
+struct SortShared {
+    int pos[SMCGW_MAX_EVENTS][SORT_WAVES];   // counts, then running positions, of every (rank, wavefront)
+    int part[SORT_WAVES];
+    int before[SMCGW_MAX_EVENTS], others[SMCGW_MAX_EVENTS];   // a rank's entries in the earlier chunks, in all other chunks
+    uint8_t rank[SMCGW_MAX_EVENTS];
+};
+
+// Calls f(particle, whether there is one, its rank, the lanes of its rank) for this wavefront's particles, 64 at a time.
+template <class F>
+__device__ __forceinline__ void sort_each(const SortShared& S, const int32_t* __restrict__ ev_of_p, int n_events,
+                                          const EventRanks& er, int P, F&& f) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c0 = blockIdx.x * SORT_CHUNK, n = min(SORT_CHUNK, P - c0);
+    const int per = ((n + SORT_WAVES - 1) / SORT_WAVES + 63) & ~63;
+    const int i0 = c0 + min(n, wave * per), i1 = c0 + min(n, wave * per + per);
+    for (int b = i0; b < i1; b += 64 * SORT_AHEAD) {
+        int e[SORT_AHEAD];
+#pragma unroll
+        for (int k = 0; k < SORT_AHEAD; ++k) e[k] = event_index(ev_of_p, min(b + 64 * k + lane, P - 1), n_events);
+#pragma unroll
+        for (int k = 0; k < SORT_AHEAD; ++k)
+            if (b + 64 * k < i1) {
+                const int i = b + 64 * k + lane, r = S.rank[e[k]];
+                const bool in = i < i1;
+                unsigned long long same = __ballot(in);
+                for (int q = 0; q < er.bits; ++q) {
+                    const unsigned long long one = __ballot(r >> q & 1);
+                    same &= r >> q & 1 ? one : ~one;
+                }
+                f(i, in, r, same);
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
-                todo &= ~same;
             }
-        }
-        __syncthreads();
-        if (pass == 0) {   // exclusive scan over (rank, wavefront)
-            const int c = (&pos[0][0])[tid];
-            int inc = c;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(inc, o);
-                if (lane >= o) inc += t;
-            }
-            if (lane == 63) part[wave] = inc;
-            __syncthreads();
-            int before = 0;
-            for (int w = 0; w < wave; ++w) before += part[w];
-            (&pos[0][0])[tid] = before + inc - c;
-            __syncthreads();
-        }
     }
+}
+
+// The chunk's counts of every (rank, wavefront) into pos.
+__device__ __forceinline__ void sort_count(SortShared& S, const int32_t* __restrict__ ev_of_p, int n_events,
+                                           const EventRanks& er, int P) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(SMCGW_MAX_EVENTS * SORT_WAVES == SORT_THREADS, "one entry per thread");
+    (&S.pos[0][0])[tid] = 0;
+    if (tid < SMCGW_MAX_EVENTS) S.rank[tid] = er.rank[tid];
+    __syncthreads();
+    sort_each(S, ev_of_p, n_events, er, P, [&](int, bool in, int r, unsigned long long same) {
+        if (in && __builtin_ctzll(same) == lane) S.pos[r][wave] += __popcll(same);   // this wavefront's entries alone
+    });
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(SORT_THREADS) void count_events_kernel(const int32_t* __restrict__ ev_of_p, int n_events,
+                                                                    EventRanks er, int P, int32_t* __restrict__ counts) {
+    __shared__ SortShared S;
+    sort_count(S, ev_of_p, n_events, er, P);
+    const int r = threadIdx.x;
+    if (r >= SMCGW_MAX_EVENTS) return;
+    int n = 0;
+    for (int w = 0; w < SORT_WAVES; ++w) n += S.pos[r][w];
+    counts[blockIdx.x * SMCGW_MAX_EVENTS + r] = n;
+}
+
+__global__ __launch_bounds__(SORT_THREADS) void sort_events_kernel(const int32_t* __restrict__ ev_of_p, int n_events,
+                                                                   EventRanks er, int P,
+                                                                   const int32_t* __restrict__ counts,
+                                                                   int32_t* __restrict__ order) {
+    __shared__ SortShared S;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    sort_count(S, ev_of_p, n_events, er, P);
+    if (tid < SMCGW_MAX_EVENTS) {
+        int before = 0, others = 0;
+        for (int b = 0; b < (int)gridDim.x; ++b) {
+            const int n = gridDim.x > 1 && b != (int)blockIdx.x ? counts[b * SMCGW_MAX_EVENTS + tid] : 0;
+            others += n;
+            if (b < (int)blockIdx.x) before += n;
+        }
+        S.before[tid] = before;
+        S.others[tid] = others;
+    }
+    // exclusive scan over (rank, wavefront) in the chunk
+    const int c = (&S.pos[0][0])[tid];
+    int inc = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(inc, o);
+        if (lane >= o) inc += t;
+    }
+    if (lane == 63) S.part[wave] = inc;
+    __syncthreads();
+    const int r = tid / SORT_WAVES;
+    int at0 = S.before[r] + inc - c;
+    for (int w = 0; w < wave; ++w) at0 += S.part[w];
+    for (int q = 0; q < r; ++q) at0 += S.others[q];
+    (&S.pos[0][0])[tid] = at0;
+    __syncthreads();
+    sort_each(S, ev_of_p, n_events, er, P, [&](int i, bool in, int rk, unsigned long long same) {
+        const int at = S.pos[rk][wave];   // this wavefront's entries alone
+        const int ahead = __popcll(same & ((1ull << lane) - 1));
+        if (in) order[min(at + ahead, P - 1)] = i;
+        __builtin_amdgcn_wave_barrier();
+        if (in && ahead == 0) S.pos[rk][wave] = at + __popcll(same);
+    });
 }
 
 // Projected strain of one parameter point (FP64), h_reim [n_det][N][2].
@@ -578,7 +650,7 @@ __global__ __launch_bounds__(256) void waveform_kernel(const DevEvent* __restric
 // process ends.  Host code must not pass the array's name to a kernel (it is a
 // host-side stand-in there): the device address of each GPU's copy is looked up
 // once per device at context set-up and kept in noalloc_base.
-static __device__ __align__(256) int32_t scratch[SMCGW_NOALLOC_MAX_P];
+static __device__ __align__(256) int32_t scratch[sort_entries(SMCGW_NOALLOC_MAX_P)];
 
 constexpr int NOALLOC_DEVICES = 64;
 static int32_t* noalloc_base[NOALLOC_DEVICES] = {};
@@ -719,12 +791,15 @@ hipError_t launch_waveform(const DevEvent* d_events, int event_id, const double*
 using namespace smcgw;
 
 namespace smcgw {
-// A batch spans events of different table lengths.
-bool lengths_differ(const smcgw_ctx* c, const int32_t* ev_of_p) {
-    if (!ev_of_p) return false;
-    for (const DevEvent& e : c->events)
-        if (e.n_pad != c->events[0].n_pad) return true;
-    return false;
+// int32 entries of the start order a call takes, its scratch (0: index order).
+size_t loglike_order_entries(const smcgw_ctx* c, int P, const int32_t* ev_of_p) {
+    if (!ev_of_p) return 0;
+    int longest = 0, shortest = INT32_MAX;
+    for (const DevEvent& e : c->events) {
+        longest = std::max(longest, e.n_pad);
+        shortest = std::min(shortest, e.n_pad);
+    }
+    return sort_pays(P, longest, shortest) ? sort_entries(P) : 0;
 }
 
 // The longest table and the most segments among the events a call can meet.
@@ -745,8 +820,8 @@ size_t loglike_scratch_bytes(const smcgw_ctx* c, int P, const int32_t* ev_of_p, 
     return loglike_path(P, longest, nseg, precision) != PATH_BATCH && nseg > 1 ? segment_scratch_bytes(P, nseg) : 0;
 }
 
-// The batched likelihood on the context's stream; order: scratch for P start
-// positions (NULL: index order), few: loglike_scratch_bytes of scratch for the
+// The batched likelihood on the context's stream; order: loglike_order_entries of
+// scratch for the start order (NULL: index order), few: loglike_scratch_bytes of scratch for the
 // few-particle paths (NULL: they are taken only where they need none).  Every
 // path gives the same bits.
 int queue_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* theta, double* logl, double* grad,
@@ -758,8 +833,7 @@ int queue_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* the
         TimedLaunch t(c, SMCGW_KERNEL_BINS);
         return launch_few(a, path, c->n_det, precision, few, c->stream) == hipSuccess ? SMCGW_OK : SMCGW_ERR_HIP;
     }
-    // up to one wavefront per SIMD they all start at once, and an order changes nothing
-    if (order && P > SORT_MIN_P && lengths_differ(c, ev_of_p)) {
+    if (order && loglike_order_entries(c, P, ev_of_p)) {
         std::vector<int> len;
         for (const DevEvent& e : c->events) len.push_back(e.n_pad);
         std::sort(len.begin(), len.end(), std::greater<int>());
@@ -767,9 +841,13 @@ int queue_loglike(smcgw_ctx* c, int P, const int32_t* ev_of_p, const double* the
         EventRanks er{};
         for (size_t e = 0; e < c->events.size(); ++e)
             er.rank[e] = (uint8_t)(std::find(len.begin(), len.end(), c->events[e].n_pad) - len.begin());
+        while (1 << er.bits < (int)len.size()) ++er.bits;
+        const dim3 grid(sort_chunks(P)), block(SORT_THREADS);
         TimedLaunch t(c, SMCGW_KERNEL_PREP);
-        hipLaunchKernelGGL(sort_events_kernel, dim3(1), dim3(SORT_THREADS), 0, c->stream, ev_of_p, a.n_events, er, P,
-                           order);
+        if (grid.x > 1)
+            hipLaunchKernelGGL(count_events_kernel, grid, block, 0, c->stream, ev_of_p, a.n_events, er, P, order + P);
+        hipLaunchKernelGGL(sort_events_kernel, grid, block, 0, c->stream, ev_of_p, a.n_events, er, P,
+                           (const int32_t*)(order + P), order);
         if (hipGetLastError() != hipSuccess) return SMCGW_ERR_HIP;
         a.order = order;
     }

@@ -28,7 +28,7 @@ def _capture(call):
 def test_start_order_of_a_batch(smcgw):
     """A batch over events of different lengths, captured with its start order in scratch; then two eager batches
     that need a larger one (the first holds 4096 particles)."""
-    evs = [event(synth.EventSpec(20.0, 20.0 + (n - 1) * 0.5, 0.5, 2, 20.0, 70 + n)) for n in (700, 5200, 100)]
+    evs = [event(synth.EventSpec(20.0, 20.0 + (n - 1) * 0.5, 0.5, 2, 20.0, 70 + n)) for n in (700, 9000, 100)]
     rng = np.random.default_rng(3)
     x = torch.tensor(synth.prior_draw(rng, 9000, synth.gw_prior_for(evs[0])), device="cuda")
     of = torch.tensor(rng.integers(0, 3, 9000).astype(np.int32), device="cuda")
