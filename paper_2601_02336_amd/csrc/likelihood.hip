@@ -675,17 +675,18 @@ hipError_t launch_prep(const DevEvent* d_events, int n_events, const int32_t* ev
 }
 
 // Particles per wavefront of the batched likelihood.  One keeps the most
-// wavefronts in flight, and while they do not fill the chip that is what counts:
+// wavefronts in flight, and up to four of them per SIMD (4096 particles) that is what counts:
 // on a folded event of 310 edges 700 particles take 10.7 us with one per
-// wavefront, 12.4 with two, 16.3 with four.  Once the chip is full, more of them
+// wavefront, 12.4 with two, 16.3 with four; 3000 of 1969 bins 22.0, 27.5 and 32.9.  Once the chip is full, more of them
 // share a prologue (eight lanes each, so a wavefront's instructions serve up to
 // eight particles): 6000 particles take 23.4, 18.0 and 21.8 us, 20000 take 61.6,
-// 44.7 and 39.9.  On events of more than SHORT_BINS bins the prologue is a few
-// per cent of a wavefront's work and one per wavefront stays.
-constexpr int SHORT_BINS = 4 * TABLE_PAD;
+// 44.7 and 39.9.  On events of four to eight blocks the prologue weighs less and the grain of the launch more: with
+// two per wavefront 5000 particles of 4017 bins take 59.5 us (53.1 with one), 100000 take 959 (995).  On longer
+// ones the prologue is a few per cent of a wavefront's work and one per wavefront stays.
 int per_wave_of(int P, int longest) {
-    if (longest > SHORT_BINS) return 1;
-    return P >= 16384 ? 4 : P >= 2048 ? 2 : 1;
+    if (longest > 8 * TABLE_PAD) return 1;
+    if (longest > 4 * TABLE_PAD) return P >= 16384 ? 2 : 1;
+    return P >= 16384 ? 4 : P > 4096 ? 2 : 1;
 }
 
 template <int NDET, bool GRAD>
