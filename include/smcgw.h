@@ -491,11 +491,14 @@ int smcgw_recycle(smcgw_ctx *ctx, int T, int N, const double *logl, const double
 /* ------------------------------------------------------------ options
  * Launch-shape options of a context (chosen by the autotuner or by hand).
  *   SMCGW_OPT_NUTS_WAVES: wavefronts that share one particle's bin loop in the
- *     persistent NUTS kernel (2, 4, 6 or 8; 0 = the library default, 4).
- *     With 4, a launch of more than 1280 particles on events of at most 1024
- *     padded bins, as with relative binning, advances four particles in each
- *     workgroup (the outputs are the same either way; an event of at most two
- *     blocks of 512 bins has the same outputs at every width).
+ *     persistent NUTS kernel (2, 4, 6 or 8; 0 = the library default: 4, or 2
+ *     for more than 1536 particles in SMCGW_PLAIN_FP64 on events of 513 to
+ *     1024 padded bins).  With 4, a launch on short events, as with relative
+ *     binning, advances four particles in each workgroup: more than 1280
+ *     particles on events of at most 512 padded bins, in SMCGW_MIXED more than
+ *     2560 on events of at most 1024.  The outputs are the same either way; an
+ *     event of at most two blocks of 512 bins has the same outputs at every
+ *     width.
  *   SMCGW_OPT_NUTS_PRIORITY: 1 (default) raises the issue priority of a
  *     slot's wavefronts as its tree deepens, so the longest trajectories of
  *     a transition run ahead of the short ones that share their compute

@@ -1,0 +1,39 @@
+"""Transitions on events of two blocks of 512 bins on both sides of the sizes where the launch changes its form (one
+particle to a workgroup, four, or one to two wavefronts): the same outputs as at every other slot width."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_02336_amd import synth
+from oracle import oracle as O
+
+from helpers import event
+
+pytestmark = pytest.mark.gpu
+
+OUT = ("n_leapfrog", "depth", "divergent", "accept_stat")
+
+
+@pytest.mark.parametrize("P,precision", [(1536, 0), (1537, 0), (2561, 0), (2560, 1), (2561, 1)])
+def test_two_blocks(P, precision):
+    from paper_2601_02336_amd import smcgw
+    ev = event(synth.EventSpec(20.0, 20.0 + 899 * 1.0, 1.0, 3, 20.0, 77))
+    b = synth.gw_prior_for(ev)
+    c = smcgw.Context(0)
+    c.add_event(ev)
+    c.set_prior(b)
+    c.set_target(synth.TARGET_GW, 11)
+    x = torch.tensor(synth.prior_draw(np.random.default_rng(P), P, b), device="cuda")
+    ll, g = c.loglike_grad(x, precision=precision)
+    _, _, L = O.mass_matrix(x.cpu().numpy(), 0.0)
+    chol = torch.tensor(L * 0.05, device="cuda")
+    ref = None
+    for width in (0, 2, 4, 8):
+        c.set_option(smcgw.OPT_NUTS_WAVES, width)
+        y = [x.clone(), ll.clone(), g.clone()]
+        o = c.nuts_step(*y, chol, step=0.2, beta=0.1, seed=7, iteration=3, max_depth=5, precision=precision)
+        torch.cuda.synchronize()
+        y += [o[k] for k in OUT]
+        ref = ref or y
+        assert all(torch.equal(u, v) for u, v in zip(ref, y)), width
+    c.close()
