@@ -360,6 +360,14 @@ struct SegmentScratch {
     int max_seg;
 };
 
+// The point kernel's static LDS of NDET detectors: with four, 2.8 % below a compute unit's.
+constexpr int LDS_BYTES = 160 * 1024;
+template <int NDET>
+constexpr size_t point_lds() {
+    return sizeof(PointShared) + PT_BLOCKS * (sizeof(PointPartials<NDET>) + TABLE_PAD * (sizeof(float) + sizeof(double)));
+}
+static_assert(point_lds<MAXDET>() <= LDS_BYTES, "LDS of the point kernel");
+
 // Segment blockIdx.x of particle blockIdx.y.
 template <int NDET, bool GRAD>
 __global__ __launch_bounds__(PT_THREADS) void point_kernel(const DevEvent* __restrict__ evs, int n_events,
