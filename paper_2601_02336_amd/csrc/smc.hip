@@ -254,9 +254,14 @@ constexpr int RW_SINGLE_MAX = 2560;
 constexpr int RWM_LEVELS = 6;
 constexpr int RWM_CAND = 1 << RWM_LEVELS;
 constexpr int RWM_PASSES = 8;      // 48 levels: [0, 1] is below the 1e-14 width after 47
-constexpr int RWM_BLOCKS = 128;      // most workgroups of a pass (64 up to RWM_WIDE points: fewer partials to add)
+constexpr int RWM_BLOCKS = 128;      // most workgroups of a pass
 constexpr int RWM_WIDE = 32768;
 constexpr int RWM_MAX_BLOCKS = 256;  // most workgroups of the maxima
+// Workgroups of a pass: few on a small population, since each adds all their partials and ends with a reduction of its
+// own; with 64 runs in one call the launches fill the chip many times over (64 runs of 2561 particles with 64 for each
+// 2427 us an iteration, with 16 2170, on one workgroup each 2180; of 6000 with 64 5030, with 32 4850, 4780).
+// The runs' number has no part in it: a run's sums are the same whatever else is in the call.
+int rwm_blocks(int P) { return P <= 4096 ? 16 : P <= 8192 ? 32 : P <= RWM_WIDE ? 64 : RWM_BLOCKS; }
 constexpr int RWM_THREADS = 512;
 constexpr int RWM_WAVES = RWM_THREADS / 64;
 constexpr int RWM_QUADS = RWM_CAND / RW_CAND;   // wavefronts that share a point
@@ -341,6 +346,20 @@ __global__ __launch_bounds__(RWM_THREADS) void rwm_max_kernel(RwArgs a, PoolLadd
     }
 }
 
+// Sum k over `times` N workgroups' partials from the b-th on, in order, the loads of N in flight together.
+template <int N>
+__device__ __forceinline__ double rwm_quarter(const double (*part)[RWM_SUMS], int b, int k, int times = 1) {
+    double v = 0.0;
+    for (const int end = b + times * N; b < end; b += N) {
+        double x[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = part[b + i][k];
+#pragma unroll
+        for (int i = 0; i < N; ++i) v += x[i];
+    }
+    return v;
+}
+
 // The run's state at the start of launch `pass` (RWM_PASSES: the weights), from
 // the previous launch's state and partials; all threads, uniform.  tot:
 // RWM_SUMS doubles, red: RWM_THREADS doubles of LDS.
@@ -368,11 +387,11 @@ __device__ RwState rwm_resume(const RwArgs& a, int run, int pass, double* tot, d
         // sum k from four threads, each a quarter of the workgroups in order, then the quarters in order (read
         // before the state says whether they are needed: one round trip less)
         const int k = threadIdx.x % RWM_SUMS, q = threadIdx.x / RWM_SUMS;
-        const int n = gridDim.x, b0 = q * n / 4, b1 = (q + 1) * n / 4;
+        const double (*part)[RWM_SUMS] = scr.part[(pass - 1) & 1];
         s = scr.state[(pass - 1) & 1];
-        double v = 0.0;
-#pragma unroll 16
-        for (int b = b0; b < b1; ++b) v += scr.part[(pass - 1) & 1][b][k];
+        const int n = gridDim.x;
+        const double v = n == 16 ? rwm_quarter<4>(part, q * 4, k) : n == 32 ? rwm_quarter<8>(part, q * 8, k)
+                       : rwm_quarter<16>(part, q * (n / 4), k, n / 64);
         if (s.beta < 0.0) {
             red[threadIdx.x] = v;
             __syncthreads();
@@ -1071,7 +1090,7 @@ static DrawArgs queue_weights(smcgw_ctx* c, int n_runs, int P, double beta_prev,
                            (const double*)lofs, n_target, cum, out, st);
         return d;
     }
-    const int blocks = P <= RWM_WIDE ? 64 : RWM_BLOCKS;
+    const int blocks = rwm_blocks(P);
     const RwArgs a{logl, P, beta_prev, alpha, lofs, n_target, st, scr,
                    std::min(RWM_MAX_BLOCKS, (P + RWM_THREADS - 1) / RWM_THREADS)};
     const dim3 grid(blocks, n_runs), block(RWM_THREADS);
