@@ -10,6 +10,7 @@
 #pragma once
 
 #include "common.h"
+#include "trig.h"
 
 namespace smcgw {
 
@@ -36,39 +37,6 @@ __device__ __forceinline__ float uniform_f(float v) {
 __device__ __forceinline__ void sincos_rev_hw(float x, float& s, float& c) {
     s = __builtin_amdgcn_sinf(x);
     c = __builtin_amdgcn_cosf(x);
-}
-
-// sin and cos of x revolutions: the nearest quarter turn off, polynomials on an eighth
-// of a turn to either side (interpolated at Chebyshev nodes: 1e-19 and 9e-18 from the
-// functions).  The quarter turns' number sits in the low bits of r's sum with 1.5 2^52,
-// and the turn is a swap and two sign bits.  Error 1.04e-16 at most, 2.6e-17 rms
-// (sincospi: 0.97e-16, 2.6e-17), far below the phase's own rounding; the likelihood's
-// against 64-bit sums is unchanged (4.9e-14 before, 4.8e-14 after at 16 s).  The plain
-// bin loop is bound by its instructions: 142 a bin of two detectors with sincospi, 27 of
-// them a detector's range checks and selections; 1001 particles of 2 x 32257 bins
-// 150 -> 125 us.
-__device__ __forceinline__ void sincos_rev(double x, double& s, double& c) {
-    const double r = x - rint(x);
-    const double m = fma(4.0, r, 0x1.8p52);
-    const double z = fma(-0.25, m - 0x1.8p52, r);
-    const unsigned n = (unsigned)__double2loint(m);
-    const double z2 = z * z;
-    double p = fma(z2, 0x1.e4a9d9166f052p+1, -0x1.e3027dea82bd7p+3);
-    p = fma(z2, p, 0x1.50783208843ebp+5);
-    p = fma(z2, p, -0x1.32d2cce500387p+6);
-    p = fma(z2, p, 0x1.466bc6775a476p+6);
-    p = fma(z2, p, -0x1.4abbce625be52p+5);
-    p = fma(z2, p, 0x1.1a62633145c07p-52);
-    double q = fma(z2, -0x1.b2f3eb054afcdp+0, 0x1.f9ce245cada0bp+2);
-    q = fma(z2, q, -0x1.a6d1eef479be1p+4);
-    q = fma(z2, q, 0x1.e1f5068688d5bp+5);
-    q = fma(z2, q, -0x1.55d3c7e3cb241p+6);
-    q = fma(z2, q, 0x1.03c1f081b5ac0p+6);
-    const double sz = fma(z, 0x1.921fb54442d18p+2, z * p);
-    const double cz = fma(z, fma(z, -0x1.3bd3cc9be45dep+4, z * z2 * q), 1.0);
-    const double a = n & 1 ? cz : sz, b = n & 1 ? sz : cz;
-    s = __hiloint2double(__double2hiint(a) ^ (int)((n << 30) & 0x80000000u), __double2loint(a));
-    c = __hiloint2double(__double2hiint(b) ^ (int)(((n + 1) << 30) & 0x80000000u), __double2loint(b));
 }
 
 // Coefficients of one particle from a coefficient block in any address space.
