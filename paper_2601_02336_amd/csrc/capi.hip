@@ -51,10 +51,37 @@ TimedLaunch::~TimedLaunch() {
     c->ev_pending[cls].push_back({a, b});
 }
 
+void note_capture(smcgw_ctx* c) {
+    if (c->captured) return;
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &s) != hipSuccess) (void)hipGetLastError();
+    c->captured = s != hipStreamCaptureStatusNone;
+}
+
+void give_up(smcgw_ctx* c, void* p) {
+    c->sweep_key.clear();   // the sweeps' own graph is captured anew
+    if (p && c->captured) c->outgrown.push_back(p);
+    else (void)hipFree(p);
+}
+
+void* replace_scratch(smcgw_ctx* c, void* p, size_t& have, size_t need) {
+    give_up(c, p);
+    // doubled where the old one stays, so that together they are no more than the new one
+    size_t n = c->captured ? std::max(need, 2 * have) : need;
+    have = 0;
+    if (hipMalloc(&p, n) != hipSuccess) {
+        (void)hipGetLastError();
+        if (n == need || hipMalloc(&p, n = need) != hipSuccess) return nullptr;
+    }
+    have = n;
+    return p;
+}
+
 int ctx_reserve(smcgw_ctx* c, int P) {
+    note_capture(c);
     if (P <= c->cap) return SMCGW_OK;
     const int cap = std::max(P, std::max(2 * c->cap, 256));
-    (void)hipFree(c->d_cb);
+    give_up(c, c->d_cb);
     c->d_cb = nullptr;
     c->cap = 0;
     if (hipMalloc(&c->d_cb, (size_t)cap * CB_SIZE * sizeof(double)) != hipSuccess) return SMCGW_ERR_OOM;

@@ -39,9 +39,11 @@ struct smcgw_ctx {
     size_t sort_cap = 0;                   // its entries
     void* d_few = nullptr;                 // segments of the few-particle likelihood
     size_t few_cap = 0;                    // its bytes
-    // start orders and segments' blocks a larger call has replaced: a captured call holds their address, so they stay
-    // allocated until the context ends (each is at most half of the next)
+    // scratch that a larger call has replaced and whose address a graph may hold: it stays allocated until the context
+    // ends.  The start order and the segments' blocks are always kept (each is at most half of the next); other scratch
+    // once a call of the context has been captured.
     std::vector<void*> outgrown;
+    bool captured = false;
     double* d_tan = nullptr;               // tangent moment blocks of the plain form, [tan_cap][12]
     int tan_cap = 0;
     // sampler state
@@ -116,6 +118,12 @@ struct TimedLaunch {
     ~TimedLaunch();
 };
 int ctx_reserve(smcgw_ctx* c, int P);
+// Notes that the stream is being captured, if it is: called wherever a call takes scratch of the context.
+void note_capture(smcgw_ctx* c);
+// Gives up outgrown scratch: freed, or kept for the graphs that hold its address.
+void give_up(smcgw_ctx* c, void* p);
+// Replaces scratch p of `have` bytes by one of at least `need`; p is NULL and `have` 0 where there is no memory.
+void* replace_scratch(smcgw_ctx* c, void* p, size_t& have, size_t need);
 // SMC pieces queued by smcgw_smc_iteration (smc.hip, metric.hip, nuts.hip).
 void* sampler_scratch(smcgw_ctx* c, size_t bytes);
 double* pinned(smcgw_ctx* c);

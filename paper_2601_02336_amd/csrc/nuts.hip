@@ -1439,9 +1439,10 @@ int launch_analytic(smcgw_ctx* c, const NutsArgs& a, const PriorDesc& pri, const
 
 // The work-queue counter and the start-order buffer for P particles.
 int smcgw::nuts_reserve(smcgw_ctx* c, int P, bool hint) {
+    note_capture(c);
     if (!c->d_queue && hipMalloc(&c->d_queue, 256) != hipSuccess) return SMCGW_ERR_OOM;
     if (hint && P > c->order_cap) {
-        (void)hipFree(c->d_order);
+        give_up(c, c->d_order);
         c->d_order = nullptr;
         c->order_cap = 0;
         if (hipMalloc(&c->d_order, (size_t)P * sizeof(int32_t)) != hipSuccess) return SMCGW_ERR_OOM;

@@ -160,7 +160,7 @@ int tangent_reserve(smcgw_ctx* c, int P) {
     int rc = ctx_reserve(c, P);
     if (rc) return rc;
     if (P <= c->tan_cap) return SMCGW_OK;
-    (void)hipFree(c->d_tan);
+    give_up(c, c->d_tan);
     c->d_tan = nullptr;
     c->tan_cap = 0;
     const int cap = std::max(P, c->cap);

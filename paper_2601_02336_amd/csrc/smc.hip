@@ -979,13 +979,9 @@ __global__ void export_pair_kernel(const double* __restrict__ out, double* __res
 
 // Scratch of the sampler entry points (device), grown on demand.
 void* sampler_scratch(smcgw_ctx* c, size_t bytes) {
+    note_capture(c);
     if (bytes <= c->sampler_bytes) return c->d_sampler;
-    (void)hipFree(c->d_sampler);
-    c->d_sampler = nullptr;
-    c->sampler_bytes = 0;
-    const size_t cap = std::max(bytes, (size_t)1 << 20);
-    if (hipMalloc(&c->d_sampler, cap) != hipSuccess) return nullptr;
-    c->sampler_bytes = cap;
+    c->d_sampler = replace_scratch(c, c->d_sampler, c->sampler_bytes, std::max(bytes, (size_t)1 << 20));
     return c->d_sampler;
 }
 
@@ -1170,13 +1166,10 @@ size_t reweight_scratch_bytes(int n_runs, int P, int D) {
 int mm_reserve(smcgw_ctx* c, int n_runs, int P) {
     const int nblk = (P + MMB - 1) / MMB;
     const size_t need = (size_t)n_runs * nblk * MM_SUMS * sizeof(double);
+    note_capture(c);
     if (need <= c->mm_bytes) return SMCGW_OK;
-    (void)hipFree(c->d_mm);
-    c->d_mm = nullptr;
-    c->mm_bytes = 0;
-    if (hipMalloc(&c->d_mm, need) != hipSuccess) return SMCGW_ERR_OOM;
-    c->mm_bytes = need;
-    return SMCGW_OK;
+    c->d_mm = (double*)replace_scratch(c, c->d_mm, c->mm_bytes, need);
+    return c->d_mm ? SMCGW_OK : SMCGW_ERR_OOM;
 }
 
 // Covariance, shrinkage and factor of every run (run r: particles [r P, (r+1) P),

@@ -73,3 +73,62 @@ def test_segments_of_few_particles(smcgw):
                 torch.cuda.synchronize()
                 assert torch.equal(ll, ref[0]) and torch.equal(g, ref[1])
     c.close()
+
+
+def test_iteration_graph(smcgw):
+    """The graph of an iteration, and between its replays eager work on the same context that needs larger scratch: a
+    larger population (the covariance's and the reweighting's) and a pool."""
+    D = 3
+    bounds = [synth.Bound(-5.0, 5.0, synth.BND_REFLECT, synth.PRIOR_UNIFORM)] * D
+    kw = dict(alpha=0.9, step=0.3, max_depth=3, shrink=0.0, seed=5, precision=smcgw.PLAIN_FP64, history_cap=8)
+
+    def context():
+        c = smcgw.Context(0)
+        c.set_prior(bounds)
+        c.set_target(synth.TARGET_GAUSS, D)
+        return c
+    x = torch.tensor(synth.prior_draw(np.random.default_rng(1), 400, bounds), device="cuda")
+    a, b = context(), context()
+    graphed, eager = smcgw.SmcRuns(a, x, 2, **kw), smcgw.SmcRuns(b, x, 2, **kw)
+    graph = graphed.graph()
+    for n in (0, 60000, 300000, 300000):
+        if n:
+            big = smcgw.SmcRuns(a, torch.tensor(synth.prior_draw(np.random.default_rng(n), n, bounds), device="cuda"), 1, **kw)
+            big.step()
+            out = [torch.empty((1000, D), dtype=torch.float64, device="cuda"),
+                   torch.empty(1000, dtype=torch.float64, device="cuda")]
+            a.ps_reweight_resample(big.theta[:50000].contiguous(), big.logl[:50000].contiguous(), None, [0.1] * 50,
+                                   [0.0] * 50, 0.5, 1, 1, *out, None)
+        graph.launch()
+        eager.step()
+        torch.cuda.synchronize()
+        assert torch.equal(graphed.theta, eager.theta) and torch.equal(graphed.logl, eager.logl)
+        assert np.array_equal(graphed.state(), eager.state()) and np.array_equal(graphed.history(), eager.history())
+    graph.close()
+    a.close()
+    b.close()
+
+
+def test_sweeps_graph(smcgw):
+    """The sweeps keep a graph of their own between calls: a larger batch of the plain form in between."""
+    ev = event(synth.EventSpec(20.0, 20.0 + 999 * 0.5, 0.5, 2, 20.0, 83))
+    b = synth.gw_prior_for(ev)
+    c = smcgw.Context(0)
+    c.add_event(ev)
+    c.set_prior(b)
+    c.set_target(synth.TARGET_GW, 11)
+    x = torch.tensor(synth.prior_draw(np.random.default_rng(6), 3000, b), device="cuda")
+    x0 = x[:40].contiguous()
+    ll0, g0 = c.loglike_grad_tangent(x0)
+    chol = torch.diag(torch.tensor([(q.hi - q.lo) * 0.01 for q in b], dtype=torch.float64, device="cuda"))
+    y = [x0.clone(), ll0.clone(), g0.clone()]
+    ref = None
+    for n in (40, 600, 3000):
+        c.loglike_grad_tangent(x[:n].contiguous())
+        for dst, src in zip(y, (x0, ll0, g0)):
+            dst.copy_(src)
+        c.nuts_step_sweeps(*y, chol, step=0.2, beta=0.1, seed=1, iteration=1, max_depth=4)
+        torch.cuda.synchronize()
+        ref = ref or [t.clone() for t in y]
+        assert all(torch.equal(u, v) for u, v in zip(y, ref))
+    c.close()
