@@ -7,7 +7,7 @@ import torch
 from paper_2601_02336_amd import synth
 from oracle import oracle as O
 
-from helpers import event
+from helpers import TOL, event, grad_err, logl_rel_err, widths
 
 pytestmark = pytest.mark.gpu
 
@@ -36,4 +36,29 @@ def test_two_blocks(P, precision):
         y += [o[k] for k in OUT]
         ref = ref or y
         assert all(torch.equal(u, v) for u, v in zip(ref, y)), width
+    c.close()
+
+
+@pytest.mark.parametrize("n_det", [1, 2, 3])
+def test_fp64_points_agree_with_the_batch(n_det):
+    """The transition keeps the library's sine and cosine in FP64, the batched likelihood has its own: at the points a
+    transition leaves, both give the same log-likelihood and gradient within the tolerance that either has against the
+    oracle."""
+    from paper_2601_02336_amd import smcgw
+    ev = event(synth.EventSpec(20.0, 1024.0, 0.25, n_det, 20.0, 78))
+    b = synth.gw_prior_for(ev)
+    c = smcgw.Context(0)
+    c.add_event(ev)
+    c.set_prior(b)
+    c.set_target(synth.TARGET_GW, 11)
+    x = torch.tensor(synth.prior_draw(np.random.default_rng(n_det), 300, b), device="cuda")
+    ll, g = c.loglike_grad(x, precision=smcgw.PLAIN_FP64)
+    _, _, L = O.mass_matrix(x.cpu().numpy(), 0.0)
+    o = c.nuts_step(x, ll, g, torch.tensor(L * 0.05, device="cuda"), step=0.2, beta=0.1, seed=7, iteration=3, max_depth=4,
+                    precision=smcgw.PLAIN_FP64)
+    ll2, g2 = c.loglike_grad(x, precision=smcgw.PLAIN_FP64)
+    moved = o["n_leapfrog"].cpu().numpy() > 0
+    assert moved.all()
+    assert logl_rel_err(ll.cpu().numpy(), ll2.cpu().numpy()) <= TOL["plain"]["logl"]
+    assert grad_err(g.cpu().numpy(), g2.cpu().numpy(), widths(b)) <= TOL["plain"]["grad"]
     c.close()
