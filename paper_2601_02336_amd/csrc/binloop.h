@@ -105,38 +105,42 @@ __device__ __forceinline__ double2 buf_f64x2(__amdgpu_buffer_rsrc_t r, unsigned 
     return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, lane_bytes, uniform_bytes, 0));
 }
 
-// One chunk starting at bin `base` (wave-uniform).
+// One chunk starting at bin `base` (wave-uniform) + ch CHUNK_BINS (ch known to the compiler:
+// the loads' own offsets hold it, so a block's chunks share their scalar addresses).
 template <int NDET>
-__device__ __forceinline__ void load_chunk(BinPair<NDET, float2>& x, const TableView& t, int base, unsigned lane) {
+__device__ __forceinline__ void load_chunk(BinPair<NDET, float2>& x, const TableView& t, int base, unsigned lane,
+                                           unsigned ch = 0) {
     const int np8 = t.npad * 8;
-    const double2 f = buf_f64x2(t.fwl, lane * 16u, ROW_F * np8 + base * 8);
-    const double2 w = buf_f64x2(t.fwl, lane * 16u, ROW_W * np8 + base * 8);
-    const double2 l = buf_f64x2(t.fwl, lane * 16u, ROW_LN * np8 + base * 8);
+    const unsigned at = lane * 16u + ch * (CHUNK_BINS * 8u);
+    const double2 f = buf_f64x2(t.fwl, at, ROW_F * np8 + base * 8);
+    const double2 w = buf_f64x2(t.fwl, at, ROW_W * np8 + base * 8);
+    const double2 l = buf_f64x2(t.fwl, at, ROW_LN * np8 + base * 8);
     x.b[0].f = f.x; x.b[1].f = f.y;
     x.b[0].w = w.x; x.b[1].w = w.y;
     x.b[0].l = l.x; x.b[1].l = l.y;
 #pragma unroll
     for (int d = 0; d < NDET; ++d) {
-        const float4 u = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(t.u, lane * 16u,
-                                                                                          d * np8 + base * 8, 0));
+        const float4 u = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(t.u, at, d * np8 + base * 8, 0));
         x.b[0].u[d] = make_float2(u.x, u.y);
         x.b[1].u[d] = make_float2(u.z, u.w);
     }
 }
 
 template <int NDET>
-__device__ __forceinline__ void load_chunk(BinPair<NDET, double2>& x, const TableView& t, int base, unsigned lane) {
+__device__ __forceinline__ void load_chunk(BinPair<NDET, double2>& x, const TableView& t, int base, unsigned lane,
+                                           unsigned ch = 0) {
     const int np8 = t.npad * 8;
-    const double2 f = buf_f64x2(t.fwl, lane * 16u, ROW_F * np8 + base * 8);
-    const double2 w = buf_f64x2(t.fwl, lane * 16u, ROW_W * np8 + base * 8);
-    const double2 l = buf_f64x2(t.fwl, lane * 16u, ROW_LN * np8 + base * 8);
+    const unsigned at = lane * 16u + ch * (CHUNK_BINS * 8u), at2 = lane * 32u + ch * (CHUNK_BINS * 16u);
+    const double2 f = buf_f64x2(t.fwl, at, ROW_F * np8 + base * 8);
+    const double2 w = buf_f64x2(t.fwl, at, ROW_W * np8 + base * 8);
+    const double2 l = buf_f64x2(t.fwl, at, ROW_LN * np8 + base * 8);
     x.b[0].f = f.x; x.b[1].f = f.y;
     x.b[0].w = w.x; x.b[1].w = w.y;
     x.b[0].l = l.x; x.b[1].l = l.y;
 #pragma unroll
     for (int d = 0; d < NDET; ++d) {
-        x.b[0].u[d] = buf_f64x2(t.u, lane * 32u, 2 * (d * np8 + base * 8));
-        x.b[1].u[d] = buf_f64x2(t.u, lane * 32u + 16u, 2 * (d * np8 + base * 8));
+        x.b[0].u[d] = buf_f64x2(t.u, at2, 2 * (d * np8 + base * 8));
+        x.b[1].u[d] = buf_f64x2(t.u, at2 + 16u, 2 * (d * np8 + base * 8));
     }
 }
 
@@ -154,9 +158,14 @@ __device__ __forceinline__ void load_chunk(BinPair<NDET, double2>& x, const Tabl
 // folded event's ~310 edges that skips one chunk in four, of the 8033-bin
 // grid's 64 chunks one.
 //
-// SEG: after every `seg` blocks, except the last one's, end_segment() is called:
-// it takes A's sums and clears them.
-template <class In, bool SEG, class Acc, class F>
+// LOOP_SEGMENTS, LOOP_TIGHT: after every `seg` blocks, except the last one's, end_segment() is called:
+// it takes A's sums and clears them.  The test for it inside the loop costs 0.5 to 1.5 % of long events' batches;
+// LOOP_TIGHT has a segment's blocks in a loop of their own, with a block's scalar addresses made once, which costs
+// nothing where the compiler keeps the loads as early as they are written: MIXED with the gradient of up to three
+// detectors (3 x 259585 bins, 2048 particles 1141 -> 1118 us, 4096 2203 -> 2180; four detectors 1.0 % slower, values of
+// three 1.4 times).
+enum BinLoop { LOOP_ALL, LOOP_SEGMENTS, LOOP_TIGHT };
+template <class In, BinLoop LOOP, class Acc, class F>
 __device__ __forceinline__ void bin_loop(Acc& A, const BinCoef& k, const TableView& t, int blk0, int blk_step,
                                          int blk_end, int seg, F&& end_segment) {
     static_assert(BLK_CHUNKS % 2 == 0, "a block holds a whole number of buffer pairs");
@@ -172,19 +181,43 @@ __device__ __forceinline__ void bin_loop(Acc& A, const BinCoef& k, const TableVi
     };
     In a, b;
     load_chunk(a, t, base_of(0), lane);
-    for (int blk = 0; blk < full; ++blk) {
+    if constexpr (LOOP == LOOP_TIGHT) {
+        const int step = blk_step * TABLE_PAD, end = base_of(last);
+        int at = blk0 * TABLE_PAD;
+        for (int blk = 0; blk < full;) {
+            const int stop = min(full, blk + seg);
+            for (; blk < stop; ++blk) {
+                const int next = min(at + step, end);
 #pragma unroll
-        for (int pr = 0; pr < BLK_CHUNKS / 2; ++pr) {
-            const int c = blk * BLK_CHUNKS + 2 * pr;
-            load_chunk(b, t, base_of(c + 1), lane);
-            A.bin(k, a.b[0], pr == 0);
-            A.bin(k, a.b[1], false);
-            load_chunk(a, t, base_of(min(c + 2, last)), lane);
-            A.bin(k, b.b[0], false);
-            A.bin(k, b.b[1], false);
+                for (int pr = 0; pr < BLK_CHUNKS / 2; ++pr) {
+                    load_chunk(b, t, at, lane, 2 * pr + 1);
+                    A.bin(k, a.b[0], pr == 0);
+                    A.bin(k, a.b[1], false);
+                    if (pr + 1 < BLK_CHUNKS / 2) load_chunk(a, t, at, lane, 2 * pr + 2);
+                    else load_chunk(a, t, next, lane);
+                    A.bin(k, b.b[0], false);
+                    A.bin(k, b.b[1], false);
+                }
+                A.flush();
+                at = next;
+            }
+            if (blk < nb && blk % seg == 0) end_segment();
         }
-        A.flush();
-        if (SEG && (blk + 1) % seg == 0 && blk + 1 < nb) end_segment();
+    } else {
+        for (int blk = 0; blk < full; ++blk) {
+#pragma unroll
+            for (int pr = 0; pr < BLK_CHUNKS / 2; ++pr) {
+                const int c = blk * BLK_CHUNKS + 2 * pr;
+                load_chunk(b, t, base_of(c + 1), lane);
+                A.bin(k, a.b[0], pr == 0);
+                A.bin(k, a.b[1], false);
+                load_chunk(a, t, base_of(min(c + 2, last)), lane);
+                A.bin(k, b.b[0], false);
+                A.bin(k, b.b[1], false);
+            }
+            A.flush();
+            if (LOOP == LOOP_SEGMENTS && (blk + 1) % seg == 0 && blk + 1 < nb) end_segment();
+        }
     }
     if (full < nb) {
         A.clear();
@@ -201,36 +234,35 @@ __device__ __forceinline__ void bin_loop(Acc& A, const BinCoef& k, const TableVi
     }
 }
 
-// Moments of NDET detectors from a wavefront's per-lane sums into a moment
-// block.
-template <int NDET>
-__device__ __forceinline__ void store_moments(const double (&Zr)[NDET], const double (&Zi)[NDET],
-                                              const double (&T)[NDET], const double (&G)[NCOEF], double* out) {
-    constexpr int K = mom_g(NDET, NCOEF);
-    double v[K];
+// Totals over the lanes of a wavefront's per-lane sums (mom_* order) into, or onto, a moment
+// block.  Without the gradient (Z alone) each is summed over the lanes in the order of its
+// place in the full list, so that the value is the same with and without the gradient.
+template <int NDET, bool GRAD>
+__device__ __forceinline__ void store_totals(const double (&v)[moments(NDET, GRAD)], double* out, bool add = false) {
+    if constexpr (GRAD) {
+        wave_totals_to<moments(NDET, true)>(v, out, 1, add);
+    } else {
+        const int lane = lane_here();
 #pragma unroll
-    for (int d = 0; d < NDET; ++d) {
-        v[mom_zr(NDET, d)] = Zr[d];
-        v[mom_zi(NDET, d)] = Zi[d];
-        v[mom_t(NDET, d)] = T[d];
+        for (int k = 0; k < 2 * NDET; ++k) {
+            const double t = wave_total_as<moments(NDET, true)>(v[k], k);
+            if (lane == 0) out[k] = add ? out[k] + t : t;
+        }
     }
-#pragma unroll
-    for (int b = 0; b < NCOEF; ++b) v[mom_g(NDET, b)] = G[b];
-    wave_totals_to<K>(v, out);
 }
 
-// The Z moments alone (a value without its gradient), each summed over the
-// lanes in the order of its place in store_moments' list, so that the value is
-// the same with and without the gradient.
-template <int NDET>
-__device__ __forceinline__ void store_values(const double (&Zr)[NDET], const double (&Zi)[NDET], double* out) {
-    constexpr int K = mom_g(NDET, NCOEF);
-    const int lane = lane_here();
+// The per-lane sums of an accumulator in mom_* order.
+template <int NDET, bool GRAD, class Acc>
+__device__ __forceinline__ void lane_sums(const Acc& A, double (&v)[moments(NDET, GRAD)]) {
 #pragma unroll
-    for (int k = 0; k < 2 * NDET; ++k) {   // mom_zr, then mom_zi
-        const double t = wave_total_as<K>(k < NDET ? Zr[k % NDET] : Zi[k % NDET], k);
-        if (lane == 0) out[k] = t;
+    for (int d = 0; d < NDET; ++d) {
+        v[mom_zr(NDET, d)] = A.Zr[d];
+        v[mom_zi(NDET, d)] = A.Zi[d];
+        if (GRAD) v[mom_t(NDET, d)] = A.T[d];
     }
+    if (GRAD)
+#pragma unroll
+        for (int b = 0; b < NCOEF; ++b) v[mom_g(NDET, b)] = A.G[b];
 }
 
 // MIXED: FP64 phase and argument reduction, FP32 sin/cos, complex products and
@@ -244,17 +276,15 @@ struct MixedAcc {
 
     __device__ __forceinline__ void start(const BinCoef& k) {
 #pragma unroll
-        for (int d = 0; d < NDET; ++d) {
-            pr[d] = uniform_f((float)k.pr[d]); pim[d] = uniform_f((float)k.pi[d]);
-            Zr[d] = 0.0; Zi[d] = 0.0; T[d] = 0.0;
-        }
-#pragma unroll
-        for (int b = 0; b < NCOEF; ++b) G[b] = 0.0;
+        for (int d = 0; d < NDET; ++d) { pr[d] = uniform_f((float)k.pr[d]); pim[d] = uniform_f((float)k.pi[d]); }
+        zero();
     }
 
-    __device__ __forceinline__ void store(double* mom) const {
-        if (GRAD) store_moments<NDET>(Zr, Zi, T, G, mom);
-        else store_values<NDET>(Zr, Zi, mom);
+    __device__ __forceinline__ void zero() {
+#pragma unroll
+        for (int d = 0; d < NDET; ++d) { Zr[d] = 0.0; Zi[d] = 0.0; T[d] = 0.0; }
+#pragma unroll
+        for (int b = 0; b < NCOEF; ++b) G[b] = 0.0;
     }
 
     // One bin's FP32 terms into the partial sums; returns psibar_j.  B: the bin's basis rows.
@@ -328,8 +358,10 @@ __device__ __forceinline__ void bins_mixed_wave(const TableView& t, const BinCoe
                                                 int blk_end, double* mom) {
     MixedAcc<NDET, GRAD> A;
     A.start(k);
-    bin_loop<BinPair<NDET, float2>, false>(A, k, t, blk0, blk_step, blk_end, 0, [] {});
-    A.store(mom);
+    bin_loop<BinPair<NDET, float2>, LOOP_ALL>(A, k, t, blk0, blk_step, blk_end, 0, [] {});
+    double v[moments(NDET, GRAD)];
+    lane_sums<NDET, GRAD>(A, v);
+    store_totals<NDET, GRAD>(v, mom);
 }
 
 // PLAIN_FP64: the same algebra in FP64 throughout.  LIBM: sin and cos from sincospi.
@@ -337,16 +369,13 @@ template <int NDET, bool GRAD = true, bool LIBM = false>
 struct Fp64Acc {
     double Zr[NDET], Zi[NDET], T[NDET], G[NCOEF];
 
-    __device__ __forceinline__ void start(const BinCoef&) {
+    __device__ __forceinline__ void start(const BinCoef&) { zero(); }
+
+    __device__ __forceinline__ void zero() {
 #pragma unroll
         for (int d = 0; d < NDET; ++d) { Zr[d] = 0.0; Zi[d] = 0.0; T[d] = 0.0; }
 #pragma unroll
         for (int b = 0; b < NCOEF; ++b) G[b] = 0.0;
-    }
-
-    __device__ __forceinline__ void store(double* mom) const {
-        if (GRAD) store_moments<NDET>(Zr, Zi, T, G, mom);
-        else store_values<NDET>(Zr, Zi, mom);
     }
 
     __device__ __forceinline__ void bin(const BinCoef& k, const BinIn<NDET, double2>& x, bool) {
@@ -395,44 +424,68 @@ __device__ __forceinline__ void bins_fp64_wave(const TableView& t, const BinCoef
                                                int blk_end, double* mom) {
     Fp64Acc<NDET, GRAD, LIBM> A;
     A.start(k);
-    bin_loop<BinPair<NDET, double2>, false>(A, k, t, blk0, blk_step, blk_end, 0, [] {});
-    A.store(mom);
+    bin_loop<BinPair<NDET, double2>, LOOP_ALL>(A, k, t, blk0, blk_step, blk_end, 0, [] {});
+    double v[moments(NDET, GRAD)];
+    lane_sums<NDET, GRAD>(A, v);
+    store_totals<NDET, GRAD>(v, mom);
 }
 
-// A particle's moments are summed in segments of blocks of bins: a segment's
-// moments over one wavefront's lanes, then the segments in order.  So they come
-// out the same, bit for bit, whether one wavefront walks them all or each has a
+// A particle's moments are summed in segments of blocks of bins, and the segments in groups
+// of SEG_GROUP: each lane adds its segments' sums in order, a group's sums are totalled over
+// the lanes, then the groups are added in order.  So they come
+// out the same, bit for bit, whether one wavefront walks them all or each segment has a
 // wavefront of its own (a particle's value may not depend on the size of its
-// batch).  Events of up to 8192 bins are one segment.  A segment's end costs its
-// wavefront about 200 of the 9000 (or 18000) instructions of its bins, so longer
-// tables take longer segments.
+// batch).  Events of up to 8192 bins are one segment.  In a wavefront that walks them all a segment's end costs 18 of
+// the 9000 (or 18000) vector instructions of its bins, the resets of its sums, and a group's end a reduction of 150
+// (one at every segment's end costs the 128 s batch 0.6 % more).
+constexpr int SEG_GROUP = 4;
 __host__ __device__ constexpr int segment_blocks(int npad) { return npad <= 64 * TABLE_PAD ? 16 : 32; }
 __host__ __device__ constexpr int segments(int npad) {
     return (npad / TABLE_PAD + segment_blocks(npad) - 1) / segment_blocks(npad);
 }
-__device__ constexpr int moments(int n_det, bool grad) { return grad ? mom_g(n_det, NCOEF) : 2 * n_det; }
+__host__ __device__ constexpr int segment_groups(int npad) { return (segments(npad) + SEG_GROUP - 1) / SEG_GROUP; }
 
-// All segments from one wavefront into mom (LDS; seg: scratch of the same size).
-template <int NDET, bool GRAD, class In, class Acc>
-__device__ __forceinline__ void event_moments(const TableView& t, const BinCoef& k, double* mom, double* seg) {
+// All segments from one wavefront into mom (LDS).  LOOP_ALL: events of one segment; else col holds LDS columns of the
+// lanes' sums, [moments][64] doubles.
+template <int NDET, bool GRAD, BinLoop LOOP, class In, class Acc>
+__device__ __forceinline__ void event_moments(const TableView& t, const BinCoef& k, double* mom, double* col) {
+    constexpr int K = moments(NDET, GRAD);
     Acc A;
     A.start(k);
-    bool first = true;
-    auto end = [&] {
-        if (first) {
-            A.store(mom);
-        } else {
-            A.store(seg);
-            wave_lds_fence();
-            const int l = lane_here();
-            if (l < moments(NDET, GRAD)) mom[l] += seg[l];
+    int done = 0;   // segments
+    auto finish = [&] {
+        double v[K];
+        lane_sums<NDET, GRAD>(A, v);
+        if (LOOP != LOOP_ALL && done % SEG_GROUP != 0) {
+            const double* c = col + lane_here();
+#pragma unroll
+            for (int q = 0; q < K; ++q) v[q] = c[64 * q] + v[q];
         }
-        wave_lds_fence();
-        first = false;
-        A.start(k);
+        store_totals<NDET, GRAD>(v, mom, LOOP != LOOP_ALL && done >= SEG_GROUP);
     };
-    bin_loop<In, true>(A, k, t, 0, 1, t.npad / TABLE_PAD, segment_blocks(t.npad), end);
-    end();
+    auto end = [&] {
+        if (done % SEG_GROUP == SEG_GROUP - 1) {
+            finish();
+        } else {
+            double v[K];
+            lane_sums<NDET, GRAD>(A, v);
+            double* c = col + lane_here();
+            if (done % SEG_GROUP == 0) {
+#pragma unroll
+                for (int q = 0; q < K; ++q) c[64 * q] = v[q];
+            } else {
+                // an LDS addition, one instruction and no answer to wait for; a lane's own entries, so in order
+#pragma unroll
+                for (int q = 0; q < K; ++q)
+                    (void)__hip_atomic_fetch_add(c + 64 * q, v[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+        ++done;
+        A.zero();
+    };
+    bin_loop<In, LOOP>(A, k, t, 0, 1, t.npad / TABLE_PAD, segment_blocks(t.npad), end);
+    finish();
+    wave_lds_fence();
 }
 
 // logL from the Z moments alone (the sum of finish_particle, term by term).

@@ -76,8 +76,8 @@ __device__ __forceinline__ double wave_total(double v) {
     return v;
 }
 
-// Wavefront totals of K per-lane values, entry k written to out[k stride] (any
-// address space) by lanes 0..7.  Three halving steps over lane bits 0-2 scatter the
+// Wavefront totals of K per-lane values, entry k written to (or added to) out[k stride]
+// (any address space) by lanes 0..7.  Three halving steps over lane bits 0-2 scatter the
 // values: at each step a lane keeps one half of its list (by its lane bit) and
 // adds the partner lane's copy of that half, the partner being the lane with the
 // opposite bit and the same lower bits (xor 1, xor 2, a rotation by 4 inside
@@ -90,7 +90,7 @@ __device__ __forceinline__ double wave_total(double v) {
 // 7 (K/2 + K/4 + K/8) + 9 K/8 instructions instead of 18 K for K separate
 // wavefront sums.
 template <int K>
-__device__ __forceinline__ void wave_totals_to(const double (&v)[K], double* out, int stride = 1) {
+__device__ __forceinline__ void wave_totals_to(const double (&v)[K], double* out, int stride = 1, bool add = false) {
     constexpr int M1 = (K + 1) / 2, M2 = (M1 + 1) / 2, M3 = (M2 + 1) / 2;
     const int lane = lane_here();
     const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
@@ -126,7 +126,10 @@ __device__ __forceinline__ void wave_totals_to(const double (&v)[K], double* out
         const int p2 = b2 ? M3 : 0, p1 = p2 + (b1 ? M2 : 0), p0 = p1 + (b0 ? M1 : 0);
 #pragma unroll
         for (int k = 0; k < M3; ++k)
-            if (p2 + k < M2 && p1 + k < M1 && p0 + k < K) out[(p0 + k) * stride] = c3[k];
+            if (p2 + k < M2 && p1 + k < M1 && p0 + k < K) {
+                double* o = out + (p0 + k) * stride;
+                *o = add ? *o + c3[k] : c3[k];
+            }
     }
 }
 
@@ -210,11 +213,12 @@ static_assert(CB_AMP < CB_SIZE, "coefficient block overflow");
 // the order in which store_moments reduces them:
 //   Re Z_d, Im Z_d (d < n; Z_d = sum_j u_dj e^{-2 pi i Phi_dj}), T_d = sum_j q_dj f_j,
 //   then NCOEF basis sums G_b = sum_j psibar_j B_b(f_j), the constant first.
-__device__ constexpr int mom_zr(int, int d) { return d; }
-__device__ constexpr int mom_zi(int n, int d) { return n + d; }
-__device__ constexpr int mom_t(int n, int d) { return 2 * n + d; }
-__device__ constexpr int mom_g(int n, int b) { return 3 * n + b; }
+__host__ __device__ constexpr int mom_zr(int, int d) { return d; }
+__host__ __device__ constexpr int mom_zi(int n, int d) { return n + d; }
+__host__ __device__ constexpr int mom_t(int n, int d) { return 2 * n + d; }
+__host__ __device__ constexpr int mom_g(int n, int b) { return 3 * n + b; }
 constexpr int MOM_SIZE = 24;
+__host__ __device__ constexpr int moments(int n_det, bool grad) { return grad ? mom_g(n_det, NCOEF) : 2 * n_det; }
 static_assert(mom_g(MAXDET, NCOEF) <= MOM_SIZE, "moment block overflow");
 
 // Event index of particle p (out-of-range indices are clamped to a valid event).

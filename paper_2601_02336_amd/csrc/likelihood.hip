@@ -19,7 +19,7 @@
 //        of its particles (lanes stride the frequency bins, the shared per-bin
 //        tables are read coalesced, each lane keeps its own partial sums) and one
 //        lane per particle forms logL and the gradient from the moments.
-//   point, segment, finish (few particles): a particle's bins spread over
+//   point, segment, finish, finish_point (few particles): a particle's bins spread over
 //        wavefronts.
 //   prep: the coefficient blocks alone, in global memory, for the plain
 //        comparison form and the waveform.
@@ -36,6 +36,7 @@
 namespace smcgw {
 
 constexpr int LL_WAVES = 4;   // wavefronts per workgroup
+constexpr int LDS_BYTES = 160 * 1024;   // of a compute unit
 
 // Eight lanes per particle, as the persistent NUTS kernel splits a leaf's
 // prologue: lanes 0-3 carry one intrinsic tangent each (Mc, q, chi1, chi2)
@@ -121,22 +122,33 @@ __device__ __forceinline__ int ordered_particle(const int32_t* __restrict__ orde
 // times (6000 of a folded event 17.2 -> 16.0 us, 16384 of eight events 974 -> 955).
 // GRAD = false leaves the tangents and the gradient's moments out (20000 values of
 // 1968 bins 50.1 -> 46.7 us without the tangents); logL is the same bit for bit.
-struct LoglikeShared {   // one per particle of the workgroup (dynamic LDS)
+//
+// MULTI: events of several segments, whose wavefronts keep columns of lane sums behind the particles in LDS; with
+// three detectors four workgroups just fit a compute unit, as many as its registers hold.  Without them a particle's
+// block is spread over the banks.
+struct LoglikeParticle {
     double cb[CB_SIZE];
-    double mom[MOM_SIZE];
     union {
         double ang[ANG_COUNT][2];   // prologue
-        double seg[MOM_SIZE];       // bins
+        double mom[MOM_SIZE];       // bins
     };
 };
+template <bool MULTI> struct LoglikeShared : LoglikeParticle {};
+template <> struct LoglikeShared<false> : LoglikeParticle { double pad[MOM_SIZE]; };
+template <bool MULTI>
+size_t loglike_lds(int per_wave, int n_moments) {
+    return LL_WAVES * (per_wave * sizeof(LoglikeShared<MULTI>) + (MULTI ? 64 * n_moments * sizeof(double) : 0));
+}
+static_assert(4 * LL_WAVES * (sizeof(LoglikeShared<true>) + 64 * moments(3, true) * sizeof(double)) <= LDS_BYTES, "four fit");
 
-template <int NDET, int PREC, bool GRAD>
+template <int NDET, int PREC, bool GRAD, bool MULTI>
 __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ evs, int n_events,
                                                   const int32_t* __restrict__ ev_of_p,
                                                   const int32_t* __restrict__ order, const ParamMap& pm, int P,
                                                   int per_wave, const double* __restrict__ theta,
                                                   double* __restrict__ logl, double* __restrict__ grad) {
-    extern __shared__ LoglikeShared sh[];
+    extern __shared__ double lds[];
+    LoglikeShared<MULTI>* sh = (LoglikeShared<MULTI>*)lds;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int first = blockIdx.x * LL_WAVES * per_wave;
     {
@@ -144,7 +156,7 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
         const int g = threadIdx.x / PREP_LANES;
         const bool live = g < LL_WAVES * per_wave && first + g < P;
         const int i = live ? first + g : 0, p = ordered_particle(order, i, P);
-        LoglikeShared& s = sh[live ? g : 0];
+        LoglikeParticle& s = sh[live ? g : 0];
         prologue_lanes<GRAD>(evs[event_index(ev_of_p, p, n_events)], pm, theta + (size_t)p * pm.dim, s.cb, s.ang,
                              threadIdx.x % PREP_LANES, live);
     }
@@ -152,20 +164,25 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
     // wavefront w takes the particles w per_wave, ... of the workgroup
     const int g0 = wave * per_wave;
     const int n = min(per_wave, P - first - g0);
+    double* col = (double*)(sh + LL_WAVES * per_wave) + wave * 64 * moments(NDET, GRAD);
     for (int g = g0; g < g0 + n; ++g) {
         const int p = ordered_particle(order, first + g, P);
         const int e = __builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events));
         const BinCoef k = load_coef(sh[g].cb);
         const TableView t = PREC == SMCGW_MIXED ? mixed_tables<NDET>(evs + e) : fp64_tables<NDET>(evs + e);
+        // (values alone: without the test in the loop the compiler moves the loads behind their block's arithmetic, 1024
+        // particles of 4 x 8033 bins 26.5 -> 32.7 us)
+        constexpr BinLoop LOOP = MULTI && PREC == SMCGW_MIXED && GRAD && NDET <= 3 ? LOOP_TIGHT
+                               : MULTI || !GRAD ? LOOP_SEGMENTS : LOOP_ALL;
         if (PREC == SMCGW_MIXED)
-            event_moments<NDET, GRAD, BinPair<NDET, float2>, MixedAcc<NDET, GRAD>>(t, k, sh[g].mom, sh[g].seg);
+            event_moments<NDET, GRAD, LOOP, BinPair<NDET, float2>, MixedAcc<NDET, GRAD>>(t, k, sh[g].mom, col);
         else
-            event_moments<NDET, GRAD, BinPair<NDET, double2>, Fp64Acc<NDET, GRAD>>(t, k, sh[g].mom, sh[g].seg);
+            event_moments<NDET, GRAD, LOOP, BinPair<NDET, double2>, Fp64Acc<NDET, GRAD>>(t, k, sh[g].mom, col);
     }
     __syncthreads();
     // results: a lane per particle of the workgroup
     if ((int)threadIdx.x < min(LL_WAVES * per_wave, P - first)) {
-        const LoglikeShared& s = sh[threadIdx.x];
+        const LoglikeParticle& s = sh[threadIdx.x];
         const int p = ordered_particle(order, first + threadIdx.x, P);
         write_result<GRAD>(evs[event_index(ev_of_p, p, n_events)], pm, s.cb, s.mom, p, logl, grad);
     }
@@ -174,20 +191,22 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
 // Wavefronts per SIMD the register budget is sized for: four (128 registers)
 // where the loop's sums fit, so that a launch of one particle per wavefront
 // keeps 4096 particles on the chip at once.
-template <int NDET, bool GRAD>
+template <int NDET, bool GRAD, bool MULTI>
 __global__ __launch_bounds__(64 * LL_WAVES, NDET < 4 ? 4 : 3) void bins_mixed_kernel(
     const DevEvent* __restrict__ evs, int n_events, const int32_t* __restrict__ ev_of_p,
     const int32_t* __restrict__ order, ParamMap pm, int P, int per_wave, const double* __restrict__ theta,
     double* __restrict__ logl, double* __restrict__ grad) {
-    loglike_workgroup<NDET, SMCGW_MIXED, GRAD>(evs, n_events, ev_of_p, order, pm, P, per_wave, theta, logl, grad);
+    loglike_workgroup<NDET, SMCGW_MIXED, GRAD, MULTI>(evs, n_events, ev_of_p, order, pm, P, per_wave, theta, logl,
+                                             grad);
 }
 
-template <int NDET, bool GRAD>
+template <int NDET, bool GRAD, bool MULTI>
 __global__ __launch_bounds__(64 * LL_WAVES, NDET <= 2 || !GRAD ? 4 : 3) void bins_fp64_kernel(
     const DevEvent* __restrict__ evs, int n_events, const int32_t* __restrict__ ev_of_p,
     const int32_t* __restrict__ order, ParamMap pm, int P, int per_wave, const double* __restrict__ theta,
     double* __restrict__ logl, double* __restrict__ grad) {
-    loglike_workgroup<NDET, SMCGW_PLAIN_FP64, GRAD>(evs, n_events, ev_of_p, order, pm, P, per_wave, theta, logl, grad);
+    loglike_workgroup<NDET, SMCGW_PLAIN_FP64, GRAD, MULTI>(evs, n_events, ev_of_p, order, pm, P, per_wave, theta, logl,
+                                             grad);
 }
 
 // ------------------------------------------------------------ few particles
@@ -203,7 +222,9 @@ __global__ __launch_bounds__(64 * LL_WAVES, NDET <= 2 || !GRAD ? 4 : 3) void bin
 //       kind: first every wavefront takes one block's bins (FP32 terms, their
 //       partial sums over the block, psibar of every bin, all into LDS), then one
 //       wavefront per moment adds its lanes' terms in block order.
-// Events of one segment finish there; of more, finish_kernel adds the segments.
+// Events of one segment finish there.  Of more, a segment_kernel workgroup leaves the moments of its group of
+// segments and finish_kernel adds the groups; point_kernel leaves the lanes' sums of its segment and
+// finish_point_kernel does both.
 constexpr int PT_WAVES = 16;
 constexpr int PT_BLOCKS = PT_WAVES;   // blocks in LDS at once; a segment is one or two such rounds
 constexpr int PT_THREADS = 64 * PT_WAVES;
@@ -352,16 +373,15 @@ struct PointShared {
     double row[mom_g(MAXDET, NCOEF)][64];   // lane sums of every moment
 };
 
-// Where the few-particle kernels leave what finish_kernel needs, for calls on
-// events of more than one segment: per particle a coefficient block and max_seg
-// moment blocks.
+// Where the few-particle kernels leave what the finishing kernels need, for calls on
+// events of more than one segment: per particle a coefficient block, and moment blocks of its max_group groups of
+// segments (segment_kernel) or the lanes' sums of its max_seg segments (point_kernel).
 struct SegmentScratch {
-    double *cb, *mom;
-    int max_seg;
+    double *cb, *sums;
+    int max_seg, max_group;
 };
 
 // The point kernel's static LDS of NDET detectors: with four, 2.8 % below a compute unit's.
-constexpr int LDS_BYTES = 160 * 1024;
 template <int NDET>
 constexpr size_t point_lds() {
     return sizeof(PointShared) + PT_BLOCKS * (sizeof(PointPartials<NDET>) + TABLE_PAD * (sizeof(float) + sizeof(double)));
@@ -421,56 +441,73 @@ __global__ __launch_bounds__(PT_THREADS) void point_kernel(const DevEvent* __res
         }
     }
     __syncthreads();
-    if (wave != 0) {
-        if (scr.max_seg > 1 && seg == 0 && wave == 1)
-            for (int e = lane; e < CB_SIZE; e += 64) scr.cb[(size_t)p * CB_SIZE + e] = S.cb[e];
+    constexpr int K = moments(NDET, GRAD);
+    if (scr.max_seg > 1) {
+        double* out = scr.sums + ((size_t)p * scr.max_seg + seg) * K * 64;
+        for (int e = threadIdx.x; e < K * 64; e += PT_THREADS) out[e] = (&S.row[0][0])[e];
+        if (seg == 0 && (int)threadIdx.x < CB_SIZE) scr.cb[(size_t)p * CB_SIZE + threadIdx.x] = S.cb[threadIdx.x];
         return;
     }
-    double* mom = scr.max_seg > 1 ? scr.mom + ((size_t)p * scr.max_seg + seg) * MOM_SIZE : S.mom;
-    if (GRAD) {
-        constexpr int K = mom_g(NDET, NCOEF);
-        double v[K];
+    if (wave != 0) return;
+    double v[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = S.row[k][lane];
-        wave_totals_to<K>(v, mom);
-    } else {
-        double zr[NDET], zi[NDET];
-#pragma unroll
-        for (int d = 0; d < NDET; ++d) { zr[d] = S.row[mom_zr(NDET, d)][lane]; zi[d] = S.row[mom_zi(NDET, d)][lane]; }
-        store_values<NDET>(zr, zi, mom);
-    }
-    if (scr.max_seg > 1) return;
+    for (int k = 0; k < K; ++k) v[k] = S.row[k][lane];
+    store_totals<NDET, GRAD>(v, S.mom);
     wave_lds_fence();
     if (lane == 0) write_result<GRAD>(ev, pm, S.cb, S.mom, p, logl, grad);
 }
 
-// Segments [LL_WAVES blockIdx.x, ...) of particle blockIdx.y, one per wavefront.
+// Group blockIdx.x of the segments of particle blockIdx.y, a segment per wavefront; the
+// first wavefront then adds the lanes' sums in segment order and totals them.
+static_assert(LL_WAVES == SEG_GROUP, "a workgroup takes a group");
 template <int NDET, int PREC, bool GRAD>
 __global__ __launch_bounds__(64 * LL_WAVES, 3) void segment_kernel(
     const DevEvent* __restrict__ evs, int n_events, const int32_t* __restrict__ ev_of_p, ParamMap pm,
     SegmentScratch scr, const double* __restrict__ theta) {
+    constexpr int K = moments(NDET, GRAD);
     __shared__ double cb[CB_SIZE], ang[ANG_COUNT][2];
+    __shared__ double col[SEG_GROUP][K][64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int p = blockIdx.y, seg = blockIdx.x * LL_WAVES + wave;
+    const int p = blockIdx.y, seg = blockIdx.x * SEG_GROUP + wave;
     const DevEvent& ev = evs[__builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events))];
     const TableView t = PREC == SMCGW_MIXED ? mixed_tables<NDET>(&ev) : fp64_tables<NDET>(&ev);
-    const int nseg = segments(t.npad);
-    if ((int)blockIdx.x * LL_WAVES >= nseg) return;
+    const int nseg = segments(t.npad), n = min(SEG_GROUP, nseg - (int)blockIdx.x * SEG_GROUP);
+    if (n <= 0) return;
     point_prologue(ev, pm, theta + (size_t)p * pm.dim, cb, ang, wave, lane);
     __syncthreads();
     if (blockIdx.x == 0)
         for (int e = threadIdx.x; e < CB_SIZE; e += 64 * LL_WAVES) scr.cb[(size_t)p * CB_SIZE + e] = cb[e];
-    if (seg >= nseg) return;
-    double* mom = scr.mom + ((size_t)p * scr.max_seg + seg) * MOM_SIZE;
-    const int b0 = seg * segment_blocks(t.npad), b1 = min(t.npad / TABLE_PAD, b0 + segment_blocks(t.npad));
-    if (PREC == SMCGW_MIXED)
-        bins_mixed_wave<NDET, GRAD>(t, load_coef(cb), b0, 1, b1, mom);
-    else
-        bins_fp64_wave<NDET, GRAD>(t, load_coef(cb), b0, 1, b1, mom);
+    double v[K];
+    if (wave < n) {
+        const int b0 = seg * segment_blocks(t.npad), b1 = min(t.npad / TABLE_PAD, b0 + segment_blocks(t.npad));
+        const BinCoef k = load_coef(cb);
+        if constexpr (PREC == SMCGW_MIXED) {
+            MixedAcc<NDET, GRAD> A;
+            A.start(k);
+            bin_loop<BinPair<NDET, float2>, LOOP_ALL>(A, k, t, b0, 1, b1, 0, [] {});
+            lane_sums<NDET, GRAD>(A, v);
+        } else {
+            Fp64Acc<NDET, GRAD> A;
+            A.start(k);
+            bin_loop<BinPair<NDET, double2>, LOOP_ALL>(A, k, t, b0, 1, b1, 0, [] {});
+            lane_sums<NDET, GRAD>(A, v);
+        }
+        if (wave != 0)
+#pragma unroll
+            for (int q = 0; q < K; ++q) col[wave][q][lane] = v[q];
+    }
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int w = 1; w < SEG_GROUP; ++w)
+        if (w < n)
+#pragma unroll
+            for (int q = 0; q < K; ++q) v[q] += col[w][q][lane];
+    store_totals<NDET, GRAD>(v, scr.sums + ((size_t)p * scr.max_group + blockIdx.x) * MOM_SIZE);
 }
 
-// Results of the particles whose segments the kernels above left in scratch:
-// a wavefront per particle adds the segments in order, one lane finishes.
+// Results of the particles whose groups segment_kernel left in scratch:
+// a wavefront per particle adds the groups in order, one lane finishes.
 template <bool GRAD>
 __global__ __launch_bounds__(64) void finish_kernel(const DevEvent* __restrict__ evs, int n_events,
                                                     const int32_t* __restrict__ ev_of_p, ParamMap pm,
@@ -480,16 +517,57 @@ __global__ __launch_bounds__(64) void finish_kernel(const DevEvent* __restrict__
     const int lane = threadIdx.x, p = blockIdx.x;
     const DevEvent& ev = evs[__builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events))];
     for (int e = lane; e < CB_SIZE; e += 64) cb[e] = scr.cb[(size_t)p * CB_SIZE + e];
-    const double* m = scr.mom + (size_t)p * scr.max_seg * MOM_SIZE;
+    const double* m = scr.sums + (size_t)p * scr.max_group * MOM_SIZE;
     if (lane < moments(ev.n_det, GRAD)) {
         double s = m[lane];
-        const int n = segments(ev.n_pad);
+        const int n = segment_groups(ev.n_pad);
 #pragma unroll 8
         for (int k = 1; k < n; ++k) s += m[(size_t)k * MOM_SIZE + lane];
         mom[lane] = s;
     }
     wave_lds_fence();
     if (lane == 0) write_result<GRAD>(ev, pm, cb, mom, p, logl, grad);
+}
+
+// The same from the lanes' sums of point_kernel: a workgroup per particle, its wavefronts
+// taking the groups of segments in turn.
+constexpr int PF_WAVES = 4;
+constexpr int POINT_WORKGROUPS = 256;   // of a point call: compute units
+constexpr int PF_GROUPS = (POINT_WORKGROUPS + SEG_GROUP - 1) / SEG_GROUP;
+template <int NDET, bool GRAD>
+__global__ __launch_bounds__(64 * PF_WAVES) void finish_point_kernel(const DevEvent* __restrict__ evs, int n_events,
+                                                                     const int32_t* __restrict__ ev_of_p, ParamMap pm,
+                                                                     SegmentScratch scr, double* __restrict__ logl,
+                                                                     double* __restrict__ grad) {
+    constexpr int K = moments(NDET, GRAD);
+    __shared__ double cb[CB_SIZE], mom[PF_GROUPS][MOM_SIZE];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, p = blockIdx.x;
+    const DevEvent& ev = evs[__builtin_amdgcn_readfirstlane(event_index(ev_of_p, p, n_events))];
+    const int nseg = segments(ev.n_pad), groups = segment_groups(ev.n_pad);
+    if ((int)threadIdx.x < CB_SIZE) cb[threadIdx.x] = scr.cb[(size_t)p * CB_SIZE + threadIdx.x];
+    for (int g = wave; g < groups; g += PF_WAVES) {
+        const double* s = scr.sums + ((size_t)p * scr.max_seg + g * SEG_GROUP) * K * 64 + lane;
+        const int n = min(SEG_GROUP, nseg - g * SEG_GROUP);
+        double x[SEG_GROUP][K];   // in flight together; a missing segment reads the group's first and is not added
+#pragma unroll
+        for (int w = 0; w < SEG_GROUP; ++w)
+#pragma unroll
+            for (int q = 0; q < K; ++q) x[w][q] = s[((w < n ? w : 0) * K + q) * 64];
+#pragma unroll
+        for (int w = 1; w < SEG_GROUP; ++w)
+#pragma unroll
+            for (int q = 0; q < K; ++q) x[0][q] = w < n ? x[0][q] + x[w][q] : x[0][q];
+        store_totals<NDET, GRAD>(x[0], mom[g]);
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    if (lane < K) {
+        double s = mom[0][lane];
+        for (int g = 1; g < groups; ++g) s += mom[g][lane];
+        mom[0][lane] = s;
+    }
+    wave_lds_fence();
+    if (lane == 0) write_result<GRAD>(ev, pm, cb, mom[0], p, logl, grad);
 }
 
 // Start order of a batch whose events differ in length: particles by falling
@@ -697,19 +775,25 @@ int per_wave_of(int P, int longest) {
     return P >= 16384 ? 4 : P > 4096 ? 2 : 1;
 }
 
-template <int NDET, bool GRAD>
-hipError_t launch_loglike_ndet(const LoglikeCall& a, int precision, hipStream_t s) {
+template <int NDET, bool GRAD, bool MULTI>
+hipError_t launch_loglike_multi(const LoglikeCall& a, int precision, hipStream_t s) {
     const int per_wave = per_wave_of(a.P, a.longest);
     const int n = LL_WAVES * per_wave;
     const dim3 grid((a.P + n - 1) / n), block(64 * LL_WAVES);
-    const size_t lds = n * sizeof(LoglikeShared);
+    const size_t lds = loglike_lds<MULTI>(per_wave, moments(NDET, GRAD));
     if (precision == SMCGW_MIXED)
-        hipLaunchKernelGGL((bins_mixed_kernel<NDET, GRAD>), grid, block, lds, s, a.events, a.n_events,
+        hipLaunchKernelGGL((bins_mixed_kernel<NDET, GRAD, MULTI>), grid, block, lds, s, a.events, a.n_events,
                            a.ev_of_p, a.order, a.pm, a.P, per_wave, a.theta, a.logl, a.grad);
     else
-        hipLaunchKernelGGL((bins_fp64_kernel<NDET, GRAD>), grid, block, lds, s, a.events, a.n_events,
+        hipLaunchKernelGGL((bins_fp64_kernel<NDET, GRAD, MULTI>), grid, block, lds, s, a.events, a.n_events,
                            a.ev_of_p, a.order, a.pm, a.P, per_wave, a.theta, a.logl, a.grad);
     return hipGetLastError();
+}
+
+template <int NDET, bool GRAD>
+hipError_t launch_loglike_ndet(const LoglikeCall& a, int precision, hipStream_t s) {
+    return a.max_seg > 1 ? launch_loglike_multi<NDET, GRAD, true>(a, precision, s)
+                         : launch_loglike_multi<NDET, GRAD, false>(a, precision, s);
 }
 
 hipError_t launch_loglike(const LoglikeCall& a, int n_det, int precision, hipStream_t s) {
@@ -735,8 +819,7 @@ hipError_t launch_loglike(const LoglikeCall& a, int n_det, int precision, hipStr
 // 0.77 (49) 700 0.84, 800 1.03, 1024 1.05; 1 (64) 1024 0.87, 1500 0.80, 1800 1.00, 2047 1.02; 1 (508) 1536 856 / 1106,
 // 2047 1120 / 1150 (plain 2657 / 2593).
 constexpr int POINT_MIN_BLOCKS = 8;
-constexpr int POINT_WORKGROUPS = 256;   // compute units
-constexpr int SEGMENT_MAX = 65536;      // segments of a call (192 B each)
+constexpr int GROUP_MAX = 65536;        // groups of segments of a call (192 B each)
 static int segment_max_particles(int npad) {
     const int blocks = npad / TABLE_PAD;
     const int wgs = (segments(npad) + LL_WAVES - 1) / LL_WAVES;
@@ -746,21 +829,25 @@ static int segment_max_particles(int npad) {
 enum LoglikePath { PATH_BATCH, PATH_POINT, PATH_SEGMENTS };
 
 static LoglikePath loglike_path(int P, int longest, int nseg, int precision) {
-    if ((long)P * nseg > SEGMENT_MAX) return PATH_BATCH;
+    if ((long)P * nseg > GROUP_MAX) return PATH_BATCH;
     if (precision == SMCGW_MIXED && longest >= POINT_MIN_BLOCKS * TABLE_PAD && P * nseg <= POINT_WORKGROUPS)
         return PATH_POINT;
     return nseg > 1 && P <= segment_max_particles(longest) ? PATH_SEGMENTS : PATH_BATCH;
 }
 
-static size_t segment_scratch_bytes(int P, int nseg) {
-    return ((size_t)P * nseg * MOM_SIZE + (size_t)P * CB_SIZE) * sizeof(double);
+// Bytes of the few-particle scratch: coefficient blocks, then groups' moments or segments' lane sums.
+static size_t segment_scratch_bytes(LoglikePath path, int P, int nseg, int n_det) {
+    const size_t each = path == PATH_POINT ? (size_t)nseg * 64 * moments(n_det, true)
+                                           : (size_t)((nseg + SEG_GROUP - 1) / SEG_GROUP) * MOM_SIZE;
+    return P * (CB_SIZE + each) * sizeof(double);
 }
 
 template <int NDET, bool GRAD>
 hipError_t launch_few_ndet(const LoglikeCall& a, LoglikePath path, int precision, void* scratch, hipStream_t s) {
     const int nseg = a.max_seg;
-    SegmentScratch scr{(double*)scratch, (double*)scratch + (size_t)a.P * CB_SIZE, nseg};
-    const dim3 segs((nseg + LL_WAVES - 1) / LL_WAVES, a.P), block(64 * LL_WAVES);
+    const int groups = (nseg + SEG_GROUP - 1) / SEG_GROUP;
+    SegmentScratch scr{(double*)scratch, (double*)scratch + (size_t)a.P * CB_SIZE, nseg, groups};
+    const dim3 segs(groups, a.P), block(64 * LL_WAVES);
     if (path == PATH_POINT)
         hipLaunchKernelGGL((point_kernel<NDET, GRAD>), dim3(nseg, a.P), dim3(PT_THREADS), 0, s, a.events, a.n_events,
                            a.ev_of_p, a.pm, scr, a.theta, a.logl, a.grad);
@@ -770,7 +857,10 @@ hipError_t launch_few_ndet(const LoglikeCall& a, LoglikePath path, int precision
     else
         hipLaunchKernelGGL((segment_kernel<NDET, SMCGW_PLAIN_FP64, GRAD>), segs, block, 0, s, a.events, a.n_events,
                            a.ev_of_p, a.pm, scr, a.theta);
-    if (nseg > 1)
+    if (nseg > 1 && path == PATH_POINT)
+        hipLaunchKernelGGL((finish_point_kernel<NDET, GRAD>), dim3(a.P), dim3(64 * PF_WAVES), 0, s, a.events, a.n_events,
+                           a.ev_of_p, a.pm, scr, a.logl, a.grad);
+    else if (nseg > 1)
         hipLaunchKernelGGL(finish_kernel<GRAD>, dim3(a.P), dim3(64), 0, s, a.events, a.n_events, a.ev_of_p, a.pm, scr,
                            a.logl, a.grad);
     return hipGetLastError();
@@ -826,7 +916,8 @@ static void event_extent(const smcgw_ctx* c, const int32_t* ev_of_p, int& longes
 size_t loglike_scratch_bytes(const smcgw_ctx* c, int P, const int32_t* ev_of_p, int precision) {
     int longest, nseg;
     event_extent(c, ev_of_p, longest, nseg);
-    return loglike_path(P, longest, nseg, precision) != PATH_BATCH && nseg > 1 ? segment_scratch_bytes(P, nseg) : 0;
+    const LoglikePath path = loglike_path(P, longest, nseg, precision);
+    return path != PATH_BATCH && nseg > 1 ? segment_scratch_bytes(path, P, nseg, c->n_det) : 0;
 }
 
 // The batched likelihood on the context's stream; order: loglike_order_entries of
