@@ -190,9 +190,13 @@ __device__ __forceinline__ void loglike_workgroup(const DevEvent* __restrict__ e
 
 // Wavefronts per SIMD the register budget is sized for: four (128 registers)
 // where the loop's sums fit, so that a launch of one particle per wavefront
-// keeps 4096 particles on the chip at once.
+// keeps 4096 particles on the chip at once, else three.
+__host__ __device__ constexpr int ll_residents(int n_det, bool grad, int precision) {
+    return precision == SMCGW_MIXED ? (n_det < 4 ? 4 : 3) : n_det <= 2 || !grad ? 4 : 3;
+}
+
 template <int NDET, bool GRAD, bool MULTI>
-__global__ __launch_bounds__(64 * LL_WAVES, NDET < 4 ? 4 : 3) void bins_mixed_kernel(
+__global__ __launch_bounds__(64 * LL_WAVES, ll_residents(NDET, GRAD, SMCGW_MIXED)) void bins_mixed_kernel(
     const DevEvent* __restrict__ evs, int n_events, const int32_t* __restrict__ ev_of_p,
     const int32_t* __restrict__ order, ParamMap pm, int P, int per_wave, const double* __restrict__ theta,
     double* __restrict__ logl, double* __restrict__ grad) {
@@ -201,7 +205,7 @@ __global__ __launch_bounds__(64 * LL_WAVES, NDET < 4 ? 4 : 3) void bins_mixed_ke
 }
 
 template <int NDET, bool GRAD, bool MULTI>
-__global__ __launch_bounds__(64 * LL_WAVES, NDET <= 2 || !GRAD ? 4 : 3) void bins_fp64_kernel(
+__global__ __launch_bounds__(64 * LL_WAVES, ll_residents(NDET, GRAD, SMCGW_PLAIN_FP64)) void bins_fp64_kernel(
     const DevEvent* __restrict__ evs, int n_events, const int32_t* __restrict__ ev_of_p,
     const int32_t* __restrict__ order, ParamMap pm, int P, int per_wave, const double* __restrict__ theta,
     double* __restrict__ logl, double* __restrict__ grad) {
@@ -761,23 +765,25 @@ hipError_t launch_prep(const DevEvent* d_events, int n_events, const int32_t* ev
 }
 
 // Particles per wavefront of the batched likelihood.  One keeps the most
-// wavefronts in flight, and up to four of them per SIMD (4096 particles) that is what counts:
+// wavefronts in flight, and as long as the SIMDs hold them all (`residents` each, 4096 particles or 3072) that is what
+// counts:
 // on a folded event of 310 edges 700 particles take 10.7 us with one per
 // wavefront, 12.4 with two, 16.3 with four; 3000 of 1969 bins 22.0, 27.5 and 32.9.  Once the chip is full, more of them
 // share a prologue (eight lanes each, so a wavefront's instructions serve up to
 // eight particles): 6000 particles take 23.4, 18.0 and 21.8 us, 20000 take 61.6,
-// 44.7 and 39.9.  On events of four to eight blocks the prologue weighs less and the grain of the launch more: with
+// 44.7 and 39.9.  Kernels of three wavefronts per SIMD are full at 3072: 4096 of 100 bins and four detectors take
+// 16.5 us with one (two rounds of workgroups), 12.2 with two.  On events of four to eight blocks the prologue weighs less and the grain of the launch more: with
 // two per wavefront 5000 particles of 4017 bins take 59.5 us (53.1 with one), 100000 take 959 (995).  On longer
 // ones the prologue is a few per cent of a wavefront's work and one per wavefront stays.
-int per_wave_of(int P, int longest) {
+int per_wave_of(int P, int longest, int residents) {
     if (longest > 8 * TABLE_PAD) return 1;
     if (longest > 4 * TABLE_PAD) return P >= 16384 ? 2 : 1;
-    return P >= 16384 ? 4 : P > 4096 ? 2 : 1;
+    return P >= 16384 ? 4 : P > 1024 * residents ? 2 : 1;
 }
 
 template <int NDET, bool GRAD, bool MULTI>
 hipError_t launch_loglike_multi(const LoglikeCall& a, int precision, hipStream_t s) {
-    const int per_wave = per_wave_of(a.P, a.longest);
+    const int per_wave = per_wave_of(a.P, a.longest, ll_residents(NDET, GRAD, precision));
     const int n = LL_WAVES * per_wave;
     const dim3 grid((a.P + n - 1) / n), block(64 * LL_WAVES);
     const size_t lds = loglike_lds<MULTI>(per_wave, moments(NDET, GRAD));
