@@ -496,7 +496,8 @@ int smcgw_recycle(smcgw_ctx *ctx, int T, int N, const double *logl, const double
  *     1024 padded bins).  With 4, a launch on short events, as with relative
  *     binning, advances four particles in each workgroup: more than 1280
  *     particles on events of at most 512 padded bins, in SMCGW_MIXED more than
- *     2560 on events of at most 1024.  The outputs are the same either way; an
+ *     2560 on events of at most 1024, and as many in SMCGW_PLAIN_FP64 with
+ *     one or two detectors (there in place of 2 wavefronts).  The outputs are the same either way; an
  *     event of at most two blocks of 512 bins has the same outputs at every
  *     width.
  *   SMCGW_OPT_NUTS_PRIORITY: 1 (default) raises the issue priority of a

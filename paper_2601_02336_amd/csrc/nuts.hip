@@ -1394,20 +1394,23 @@ int launch_gw_w(smcgw_ctx* c, int precision, const NutsArgs& a, const PriorDesc&
 // and of up to 255 leaves, four wavefronts / packed / two wavefronts, us: 1536 particles 240 / 270 / 232 and 2061 /
 // 2263 / 2404; 2048 279 / 292 / 239 and 2104 / 2390 / 2821; 3000 352 / 268 / 310 and 2274 / 2836 / 2903; in FP64,
 // where the bins weigh more, 1536 341 / 400 / 312 and 3202 / 3585 / 3603; 2048 401 / 448 / 339 and 3283 / 3991 / 4486;
-// 4096 665 / 490 / 531 and 4142 / 5286 / 4645.  So MIXED packs from 2560 particles, and FP64, where a packed leaf waits
-// too long for its neighbours' bins, takes two wavefronts from 1536, twice the trees in flight: the better of the
-// other two on short trees.  With four blocks the packed
+// 4096 665 / 490 / 531 and 4142 / 5286 / 4645.  So MIXED packs from 2560 particles, and FP64 of three and four
+// detectors, where a packed leaf waits too long for its neighbours' bins, takes two wavefronts from 1536, twice the
+// trees in flight: the better of the other two on short trees.  With one and two detectors in FP64 the bins weigh
+// less and packing is the better again from 2560 (900 bins of two, trees of up to 15 leaves: 4096 particles 530 / 396 /
+// 472).  With four blocks the packed
 // particles wait for each other's bins, most of all the long trees at the end: 2048 take
 // 10.9 / 11.8, and 6144 21.8 / 20.7.  The classes are the same either way, so the bits are.
 enum NutsForm { FORM_SINGLE, FORM_PACKED, FORM_NARROW };
 constexpr int PACK_FROM = 1280;
 constexpr int PACK_FROM_2 = 2560;     // two blocks
-constexpr int NARROW_FROM_2 = 1536;   // two blocks in FP64
+constexpr int NARROW_FROM_2 = 1536;   // two blocks in FP64: up to PACK_FROM_2 with one or two detectors
 
-NutsForm nuts_form(int P, int blocks, int precision) {
+NutsForm nuts_form(int P, int blocks, int precision, int n_det) {
     if (blocks <= 1) return P > PACK_FROM ? FORM_PACKED : FORM_SINGLE;
     if (blocks > 2) return FORM_SINGLE;
-    if (precision == SMCGW_PLAIN_FP64) return P > NARROW_FROM_2 ? FORM_NARROW : FORM_SINGLE;
+    if (precision == SMCGW_PLAIN_FP64 && (n_det > 2 || P <= PACK_FROM_2))
+        return P > NARROW_FROM_2 ? FORM_NARROW : FORM_SINGLE;
     return P > PACK_FROM_2 ? FORM_PACKED : FORM_SINGLE;
 }
 
@@ -1422,7 +1425,7 @@ int launch_gw(smcgw_ctx* c, int precision, const NutsArgs& a, const PriorDesc& p
     case 8: return launch_gw_w<NDET, 1, 8>(c, precision, a, pri, pm, t);
     default: break;
     }
-    const NutsForm form = nuts_form(a.P, blocks, precision);
+    const NutsForm form = nuts_form(a.P, blocks, precision, NDET);
     if (form == FORM_PACKED) return launch_gw_w<NDET, PACKED, 4>(c, precision, a, pri, pm, t);
     if (form == FORM_NARROW && !c->nuts_waves) return launch_gw_w<NDET, 1, 2>(c, precision, a, pri, pm, t);
     return launch_gw_w<NDET, 1, 4>(c, precision, a, pri, pm, t);
@@ -1430,7 +1433,7 @@ int launch_gw(smcgw_ctx* c, int precision, const NutsArgs& a, const PriorDesc& p
 
 template <int TK>
 int launch_analytic(smcgw_ctx* c, const NutsArgs& a, const PriorDesc& pri, const ParamMap& pm, const TargetDesc& t) {
-    if (nuts_form(a.P, 0, SMCGW_PLAIN_FP64) == FORM_PACKED)
+    if (nuts_form(a.P, 0, SMCGW_PLAIN_FP64, 1) == FORM_PACKED)
         return launch_persistent(c, nuts_kernel<1, SMCGW_PLAIN_FP64, TK, PACKED, 1>, PACKED, 64, a, pri, pm, t);
     return launch_persistent(c, nuts_kernel<1, SMCGW_PLAIN_FP64, TK, 1, 1>, 1, 64, a, pri, pm, t);
 }

@@ -14,10 +14,11 @@ pytestmark = pytest.mark.gpu
 OUT = ("n_leapfrog", "depth", "divergent", "accept_stat")
 
 
-@pytest.mark.parametrize("P,precision", [(1536, 0), (1537, 0), (2561, 0), (2560, 1), (2561, 1)])
-def test_two_blocks(P, precision):
+@pytest.mark.parametrize("P,precision,n_det", [(1536, 0, 3), (1537, 0, 3), (2561, 0, 3), (2560, 1, 3), (2561, 1, 3),
+                                               (2560, 0, 2), (2561, 0, 2), (2561, 0, 1)])
+def test_two_blocks(P, precision, n_det):
     from paper_2601_02336_amd import smcgw
-    ev = event(synth.EventSpec(20.0, 20.0 + 899 * 1.0, 1.0, 3, 20.0, 77))
+    ev = event(synth.EventSpec(20.0, 20.0 + 899 * 1.0, 1.0, n_det, 20.0, 77))
     b = synth.gw_prior_for(ev)
     c = smcgw.Context(0)
     c.add_event(ev)
