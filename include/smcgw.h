@@ -497,9 +497,9 @@ int smcgw_recycle(smcgw_ctx *ctx, int T, int N, const double *logl, const double
  *     binning, advances four particles in each workgroup: more than 1280
  *     particles on events of at most 512 padded bins, in SMCGW_MIXED more than
  *     2560 on events of at most 1024, and as many in SMCGW_PLAIN_FP64 with
- *     one or two detectors (there in place of 2 wavefronts).  The outputs are the same either way; an
- *     event of at most two blocks of 512 bins has the same outputs at every
- *     width.
+ *     one or two detectors (there in place of 2 wavefronts).  The outputs are
+ *     the same either way; an event of at most two blocks of 512 bins has the
+ *     same outputs at every width.
  *   SMCGW_OPT_NUTS_PRIORITY: 1 (default) raises the issue priority of a
  *     slot's wavefronts as its tree deepens, so the longest trajectories of
  *     a transition run ahead of the short ones that share their compute

@@ -121,7 +121,7 @@ __device__ __forceinline__ int ordered_particle(const int32_t* __restrict__ orde
 // particles together, where a lane of every wavefront took its instructions four
 // times (6000 of a folded event 17.2 -> 16.0 us, 16384 of eight events 974 -> 955).
 // GRAD = false leaves the tangents and the gradient's moments out (20000 values of
-// 1968 bins 50.1 -> 46.7 us without the tangents); logL is the same bit for bit.
+// 1969 bins 50.1 -> 46.7 us without the tangents); logL is the same bit for bit.
 //
 // MULTI: events of several segments, whose wavefronts keep columns of lane sums behind the particles in LDS; with
 // three detectors four workgroups just fit a compute unit, as many as its registers hold.  Without them a particle's
@@ -772,9 +772,10 @@ hipError_t launch_prep(const DevEvent* d_events, int n_events, const int32_t* ev
 // share a prologue (eight lanes each, so a wavefront's instructions serve up to
 // eight particles): 6000 particles take 23.4, 18.0 and 21.8 us, 20000 take 61.6,
 // 44.7 and 39.9.  Kernels of three wavefronts per SIMD are full at 3072: 4096 of 100 bins and four detectors take
-// 16.5 us with one (two rounds of workgroups), 12.2 with two.  On events of four to eight blocks the prologue weighs less and the grain of the launch more: with
-// two per wavefront 5000 particles of 4017 bins take 59.5 us (53.1 with one), 100000 take 959 (995).  On longer
-// ones the prologue is a few per cent of a wavefront's work and one per wavefront stays.
+// 16.5 us with one (two rounds of workgroups), 12.2 with two.  On events of five to eight blocks the prologue weighs
+// less and the grain of the launch more: with two per wavefront 5000 particles of 4017 bins take 59.5 us (53.1 with
+// one), 100000 take 959 (995).  On longer ones the prologue is a few per cent of a wavefront's work and one per
+// wavefront stays.
 int per_wave_of(int P, int longest, int residents) {
     if (longest > 8 * TABLE_PAD) return 1;
     if (longest > 4 * TABLE_PAD) return P >= 16384 ? 2 : 1;

@@ -23,7 +23,7 @@
 // 10.6 us a leaf before the reads of each were put in flight together, the branches on
 // single values taken out and the logarithms and divisions of the auxiliary wavefront
 // merged, 10.3 us after), and with three trees on each compute unit the arithmetic of the
-// bins again (47 M leaves/s of the 54 M evaluations/s of the batched likelihood).  On a
+// bins again (45 to 47 M leaves/s of the 51 to 54 M evaluations/s of the batched likelihood).  On a
 // folded event of ~310 edges the serial parts are nine tenths of a leaf's instructions:
 // four particles to a workgroup share them (300 M leaves/s against 130 M with one).
 // Random numbers come from Philox4x32-10 with counter (index, particle,
@@ -731,7 +731,10 @@ __device__ __noinline__ void write_outputs(int sub, int lane) {
 
 // Issue priority of the slot's wavefronts while doubling j runs: a tree that
 // has reached 2^3, 2^4, 2^5 leaves outranks the shallower trees sharing its
-// SIMDs, so the transitions that decide when the launch ends go first.
+// SIMDs, so the transitions that decide when the launch ends go first.  Trees
+// past 2^5 leaves share the top level and are not ordered among themselves; where
+// most trees are that deep (3 x 8033 bins, mean depth 5.7 to 7.4) the levels change
+// nothing that can be measured.
 __device__ __forceinline__ void tree_priority(int j) {
     if (j >= 5) __builtin_amdgcn_s_setprio(3);
     else if (j == 4) __builtin_amdgcn_s_setprio(2);
@@ -1398,9 +1401,8 @@ int launch_gw_w(smcgw_ctx* c, int precision, const NutsArgs& a, const PriorDesc&
 // detectors, where a packed leaf waits too long for its neighbours' bins, takes two wavefronts from 1536, twice the
 // trees in flight: the better of the other two on short trees.  With one and two detectors in FP64 the bins weigh
 // less and packing is the better again from 2560 (900 bins of two, trees of up to 15 leaves: 4096 particles 530 / 396 /
-// 472).  With four blocks the packed
-// particles wait for each other's bins, most of all the long trees at the end: 2048 take
-// 10.9 / 11.8, and 6144 21.8 / 20.7.  The classes are the same either way, so the bits are.
+// 472).  With four blocks the packed particles wait for each other's bins, most of all the long trees at the end, ms:
+// 2048 take 10.9 / 11.8, and 6144 21.8 / 20.7.  The classes are the same either way, so the bits are.
 enum NutsForm { FORM_SINGLE, FORM_PACKED, FORM_NARROW };
 constexpr int PACK_FROM = 1280;
 constexpr int PACK_FROM_2 = 2560;     // two blocks

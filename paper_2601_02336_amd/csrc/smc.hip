@@ -240,7 +240,7 @@ __global__ __launch_bounds__(RW_THREADS) void reweight_kernel(const double* __re
 // One workgroup walks a population of two thousand points quickly, a pool of many
 // populations slowly (61440 points: 1131 us, most of it serial sweeps of 120
 // exponentials a thread).  Above RW_SINGLE_MAX points the same
-// computation runs as a chain of launches over RWM_BLOCKS workgroups: the
+// computation runs as a chain of launches over 16 to 128 workgroups: the
 // maxima, RWM_PASSES passes of the bisection and the weights.  Each launch
 // begins by adding the previous one's partials in workgroup order, every
 // workgroup for itself (same order, same result), so a pass is one launch
@@ -248,8 +248,8 @@ __global__ __launch_bounds__(RW_THREADS) void reweight_kernel(const double* __re
 // bisection levels: four wavefronts share a point's RWM_CAND grid slots, 16
 // each.  The walk compares as the sequential bisection does; only the order of
 // the sums differs from the one-workgroup kernel's.  A whole call with its draw:
-// 4096 points 115 -> 72 us, 61440 points 961 -> 105, a pool of 30 x 2048 1205 ->
-// 128; at 2048 points both take 69.  Bound by the launches: a pass is 6 to 9 us.
+// 4096 points 115 -> 67 us, 61440 points 961 -> 105, a pool of 30 x 2048 1205 ->
+// 124; at 2048 points both take 68.  Bound by the launches: a pass is 6 to 9 us.
 constexpr int RW_SINGLE_MAX = 2560;
 constexpr int RWM_LEVELS = 6;
 constexpr int RWM_CAND = 1 << RWM_LEVELS;
